@@ -550,14 +550,14 @@ struct Args {
   int64_t seg_blocks; // histogram-pass workgroups (the grid), from the host offsets
   int64_t seg_wgs;    // sample-pass workgroups (the grid), from the host offsets
   int seg_k;          // tiles per sample workgroup
-  int seg_align;      // vector loads in use: every segment must start at a multiple of 4
+  int seg_align;      // the host's offsets are multiples of 4 (and g 16-byte aligned): the device's must be too
   size_t ws_bytes;    // the workspace's size (the candidate buffers take what the rest leaves)
   int64_t cand_region;  // candidate keys per statistics workgroup (cand_cap / nb, a multiple of 64)
 };
 
 // Start and length of row r: row r of a strided batch (offset r * ld, length d), or segment r of a
 // segmented call. A segment whose device offsets break the bounds the host checked (order, end,
-// length, alignment of the vector path) reads as empty and returns false.
+// length, alignment where the host's offsets are aligned) reads as empty and returns false.
 __device__ __forceinline__ bool row_span(const Args& a, int64_t r, int64_t& base, int64_t& len) {
   if (!a.seg) {
     base = r * a.ld;
@@ -621,13 +621,51 @@ __device__ __forceinline__ uint32_t* creg_of(const Args& a, int64_t r) { return 
 
 
 
+// Streaming accesses: g is read once per pass and the outputs are written once, so those loads,
+// the probabilities' stores and the compaction's staged stores (whole runs of consecutive words)
+// carry the non-temporal hint and do not displace what the caches keep (the level-1 copies,
+// windows and status words). Stores that lanes make one word at a time to scattered places (the
+// other emission paths, the hybrid coding's lists, the candidate band) keep the default policy:
+// there the hint made the hybrid coding's sampling pass a third slower at rho = 0.1. On 2^28
+// coordinates the hint takes the statistics pass from about 213 to 192 microseconds per call.
+//
+// A row may start at any float (odd leading dimensions, segments, views): global memory takes
+// 16-byte accesses at any multiple of 4 bytes, so the vector type below asks for no more and every
+// row streams through the same loops: 5 rows of 300,007 in a packed matrix take 70 us a call with
+// them against 77 with a scalar-load copy of every loop, one odd row of a few million coordinates
+// whose solver refines 98 against 159 us; rows on 16-byte boundaries issue the same instructions.
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef float gs_f4v __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load_vec(const float* p) {
+  const gs_f4v v = *reinterpret_cast<const gs_f4v*>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float4 load_stream(const float* p) {
+  const gs_f4v v = __builtin_nontemporal_load(reinterpret_cast<const gs_f4v*>(p));
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void store_stream(float* p, float4 x) {
+  const gs_f4v v = {x.x, x.y, x.z, x.w};
+  __builtin_nontemporal_store(v, reinterpret_cast<gs_f4v*>(p));
+}
+#define GS_STORE_STREAM(ptr, v) __builtin_nontemporal_store((v), (ptr))
+#else
+GS_HD float4 load_vec(const float* p) {
+  float4 x;
+  memcpy(&x, p, sizeof(x));
+  return x;
+}
+GS_HD float4 load_stream(const float* p) { return load_vec(p); }
+GS_HD void store_stream(float* p, float4 x) { memcpy(p, &x, sizeof(x)); }
+#define GS_STORE_STREAM(ptr, v) (*(ptr) = (v))
+#endif
+
 // Four consecutive coordinates 4q..4q+3 of a row; entries at or beyond `end` read as 0 and are
 // flagged invalid in the returned mask (bit c set = coordinate 4q+c exists).
-template <bool VEC>
 __device__ __forceinline__ uint32_t load4(const float* __restrict__ row, int64_t q, int64_t end, float v[4]) {
-  int64_t i = 4 * q;
-  if (VEC && i + 3 < end) {
-    float4 x = *reinterpret_cast<const float4*>(row + i);
+  const int64_t i = 4 * q;
+  if (i + 3 < end) {
+    const float4 x = load_vec(row + i);
     v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
     return 0xF;
   }
@@ -641,48 +679,16 @@ __device__ __forceinline__ uint32_t load4(const float* __restrict__ row, int64_t
   return m;
 }
 
-// Streaming accesses: g is read once per pass and the outputs are written once, so those loads,
-// the probabilities' stores and the compaction's staged stores (whole runs of consecutive words)
-// carry the non-temporal hint and do not displace what the caches keep (the level-1 copies,
-// windows and status words). Stores that lanes make one word at a time to scattered places (the
-// other emission paths, the hybrid coding's lists, the candidate band) keep the default policy:
-// there the hint made the hybrid coding's sampling pass a third slower at rho = 0.1. On 2^28
-// coordinates the hint takes the statistics pass from about 213 to 192 microseconds per call.
-#if defined(__HIP_DEVICE_COMPILE__)
-typedef float gs_f4v __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float4 load_stream(const float* p) {
-  const gs_f4v v = __builtin_nontemporal_load(reinterpret_cast<const gs_f4v*>(p));
-  return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ void store_stream(float* p, float4 x) {
-  const gs_f4v v = {x.x, x.y, x.z, x.w};
-  __builtin_nontemporal_store(v, reinterpret_cast<gs_f4v*>(p));
-}
-#define GS_STORE_STREAM(ptr, v) __builtin_nontemporal_store((v), (ptr))
-#else
-GS_HD float4 load_stream(const float* p) { return *reinterpret_cast<const float4*>(p); }
-GS_HD void store_stream(float* p, float4 x) { *reinterpret_cast<float4*>(p) = x; }
-#define GS_STORE_STREAM(ptr, v) (*(ptr) = (v))
-#endif
 
 // Visits the coordinates [beg, end) of one row (beg a multiple of 4) with the NT threads of a
 // workgroup, calling f(q, v, m) for each float4 group q (m: bit c set when coordinate 4q+c exists).
-// With vector loads, blocks of U groups per thread are loaded unconditionally, all issued before
-// any group is processed, so U loads per thread stay in flight; the last block clamps its addresses
+// Blocks of U groups per thread are loaded unconditionally, all issued before any group is processed, so U loads per thread stay in flight; the last block clamps its addresses
 // to the last whole group and masks the values, and a trailing partial group is loaded by one
 // thread with scalar loads and visited by the whole first wave. No memory access sits under a
-// divergent branch, which would make the compiler wait for every outstanding load. With vector
-// loads every call of f is made by whole waves, so f may use cross-lane operations.
-template <bool VEC, int U, int NT, typename F>
+// divergent branch, which would make the compiler wait for every outstanding load. Every call of f
+// is made by whole waves, so f may use cross-lane operations.
+template <int U, int NT, typename F>
 __device__ __forceinline__ void stream_groups(const float* __restrict__ row, int64_t beg, int64_t end, F&& f) {
-  if (!VEC) {
-    for (int64_t q = beg / 4 + threadIdx.x; 4 * q < end; q += NT) {
-      float v[4];
-      const uint32_t m = load4<false>(row, q, end, v);
-      f(q, v, m);
-    }
-    return;
-  }
   const int64_t qfull = end / 4;  // groups [beg/4, qfull) lie entirely inside [beg, end)
   int64_t qb = beg / 4;
   for (; qb + (int64_t)U * NT <= qfull; qb += (int64_t)U * NT) {
@@ -701,7 +707,7 @@ __device__ __forceinline__ void stream_groups(const float* __restrict__ row, int
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t q = qb + threadIdx.x + u * NT;
-      x[u] = *reinterpret_cast<const float4*>(row + 4 * (q < qfull ? q : qfull - 1));
+      x[u] = load_vec(row + 4 * (q < qfull ? q : qfull - 1));
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -717,7 +723,7 @@ __device__ __forceinline__ void stream_groups(const float* __restrict__ row, int
     // coordinates), so a visitor may use cross-lane operations
     float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     uint32_t m = 0;
-    if (threadIdx.x == 0) m = load4<false>(row, qfull, end, v);
+    if (threadIdx.x == 0) m = load4(row, qfull, end, v);
     f(qfull, v, m);
   }
 }
@@ -1977,7 +1983,7 @@ __global__ void __launch_bounds__(256) k_presample(Args a) {
   for (int j = 0; j < kRounds; ++j) {
     const int64_t i = (int64_t)p * kPreLines + j * 64 + (t >> 2);  // sample index
     const int64_t line = (i < ns ? i : ns - 1) * nl / ns;             // < nl
-    x[j] = *reinterpret_cast<const float4*>(gr + 16 * line + 4 * (t & 3));
+    x[j] = load_vec(gr + 16 * line + 4 * (t & 3));
   }
   __builtin_amdgcn_sched_barrier(0);
   const int lc = t & (kCopies - 1);
@@ -2115,9 +2121,8 @@ GS_DI void cand_band(const Args& a, const PreHist* ph, double B, int64_t len, Ba
 // histogram over binades (count, exact significand sum, maximum key), kept in kLaneCopies copies
 // by lane to spread same-address LDS atomics, and adds its nonempty bins into one of the row's kC1
 // global copies (chosen by workgroup index) with atomics. k_solve runs next.
-template <bool VEC, bool SQ, bool CAND>
+template <bool SQ, bool CAND>
 __global__ void __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) k_stats(Args a) {
-  static_assert(VEC || !CAND, "candidates are collected with whole waves (vector loads)");
   __shared__ StatsLdsT<SQ> sm_st;
   StatsLdsT<SQ>& sm = sm_st;
   __shared__ BandLds s_band;
@@ -2217,13 +2222,13 @@ __global__ void __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) k
   // fewer they cost 1-3)
   constexpr int kU = CAND ? 8 : 4;
   if (CAND && bspan != 0) {
-    stream_groups<VEC, kU, kNT>(gr, beg, end, [&](int64_t, const float v[4], uint32_t) {
+    stream_groups<kU, kNT>(gr, beg, end, [&](int64_t, const float v[4], uint32_t) {
       hist(v);
       collect(v);
     });
   } else {
     // no band (or none predicted for this row): the plain statistics loop
-    stream_groups<VEC, kU, kNT>(gr, beg, end, [&](int64_t, const float v[4], uint32_t) { hist(v); });
+    stream_groups<kU, kNT>(gr, beg, end, [&](int64_t, const float v[4], uint32_t) { hist(v); });
   }
   if constexpr (CAND) {
     if (__ballot(lcnt != 0)) flush();
@@ -2279,7 +2284,7 @@ __global__ void __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) k
 }
 
 // Refinement pass over one window of keys, for the rows whose solver asked for one.
-template <bool VEC, bool SQ>
+template <bool SQ>
 __global__ void __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) k_refine(Args a) {
   __shared__ WinLdsT<SQ> sm_w;
   WinLdsT<SQ>& sm = sm_w;
@@ -2371,8 +2376,8 @@ __global__ void __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) k
     }
   };
   // (the variance-budget solver never collects candidates)
-  if (!SQ && from_cand) stream_groups<VEC, SQ ? 4 : kCandLoads, kNT>(gr, beg, end, visit);
-  else stream_groups<VEC, 4, kNT>(gr, beg, end, visit);
+  if (!SQ && from_cand) stream_groups<SQ ? 4 : kCandLoads, kNT>(gr, beg, end, visit);
+  else stream_groups<4, kNT>(gr, beg, end, visit);
   if (l2) {
     for (int o = 32; o > 0; o >>= 1) {
       qc += __shfl_xor(qc, o);
@@ -2493,21 +2498,19 @@ __device__ __forceinline__ void decide_values(const TileCtx& c, int64_t q, const
 }
 
 // The same for group q loaded here (entries past the row's end read as 0).
-template <bool VEC>
 __device__ __forceinline__ void decide_group(const TileCtx& c, int64_t q, float v[4], uint32_t& z, uint32_t& cz) {
-  const uint32_t m = load4<VEC>(c.row, q, c.d, v);
+  const uint32_t m = load4(c.row, q, c.d, v);
   decide_values(c, q, v, m, z, cz);
 }
 
 // Aggregate (capped << 31 | survivors) of tile `part` computed by one wave (fallback path).
-template <bool VEC>
 __device__ uint64_t wave_tile_aggregate(const TileCtx& c, int64_t part, int lane) {
   uint64_t n = 0, nc = 0;
   for (int j = 0; j < kTileElems / 4 / 64; ++j) {
     const int64_t q = part * (kTileElems / 4) + j * 64 + lane;
     float v[4];
     uint32_t z, cz;
-    decide_group<VEC>(c, q, v, z, cz);
+    decide_group(c, q, v, z, cz);
     n += __popc(z);
     nc += __popc(cz);
   }
@@ -2596,7 +2599,7 @@ __device__ __forceinline__ void byte_nibbles(uint32_t w0, uint32_t w1, uint32_t&
   hi = ((ev >> 4) & 0x0F0F0F0Fu) | (od & 0xF0F0F0F0u);
 }
 
-template <bool VEC, bool HYB, int K>
+template <bool HYB, int K>
 __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
   __shared__ float s_capl[K][kTileThreads / 64][64 * kLaneStride];
   __shared__ alignas(16) uint8_t s_code[K][kTileElems / 4];  // per group: selection | sign << 4
@@ -2676,7 +2679,7 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
         }
       }
     };
-    if (VEC && fast && (part + 1) * (int64_t)kTileElems <= c.d) {
+    if (fast && (part + 1) * (int64_t)kTileElems <= c.d) {
       // whole tile inside the row: kSampleBatch unconditional loads in flight per lane
 #pragma unroll
       for (int jb = 0; jb < kTileGroups; jb += kSampleBatch) {
@@ -2699,7 +2702,7 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
         uint32_t z = 0, cz = 0;
         // groups past the row's end (the tail of the last tile, and whole tiles past the end of a
         // shorter segment) hold no coordinates
-        if (c.live && 4 * (q0 + 64 * j) < c.d) decide_group<VEC>(c, q0 + 64 * j, v, z, cz);
+        if (c.live && 4 * (q0 + 64 * j) < c.d) decide_group(c, q0 + 64 * j, v, z, cz);
         else v[0] = v[1] = v[2] = v[3] = 0.0f;
         record(j, v, z, cz);
       }
@@ -2757,7 +2760,7 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
         // predecessors up to `stop` that never published: count them here
         while (missing) {
           const int m = __ffsll((unsigned long long)missing) - 1;
-          const uint64_t val = wave_tile_aggregate<VEC>(c, (look - m) - first, lane);
+          const uint64_t val = wave_tile_aggregate(c, (look - m) - first, lane);
           if (lane == m) sw = kStAgg | val;
           missing &= missing - 1;
         }
@@ -3107,7 +3110,6 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
 
 // p_i = min(lambda |g_i|, 1), exactly 1 on the capped set. Grid: rows * nb workgroups. Capped
 // coordinates are counted per workgroup and added into one of eight per-row lines.
-template <bool VEC>
 __global__ void __launch_bounds__(256) k_probs(Args a) {
   __shared__ uint32_t s_cnt[4];
   int64_t row, blk;
@@ -3125,7 +3127,7 @@ __global__ void __launch_bounds__(256) k_probs(Args a) {
   float* __restrict__ pr = a.p ? a.p + base : nullptr;
   const int64_t end = min(len, beg + a.chunk);
   uint32_t kc = 0;
-  stream_groups<VEC, 4, 256>(gr, beg, end, [&](int64_t q, const float v[4], uint32_t m) {
+  stream_groups<4, 256>(gr, beg, end, [&](int64_t q, const float v[4], uint32_t m) {
     float o[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -3137,7 +3139,7 @@ __global__ void __launch_bounds__(256) k_probs(Args a) {
       kc += capped && ((m >> c) & 1);
     }
     if (pr) {
-      if (VEC && m == 0xF) {
+      if (m == 0xF) {
         store_stream(pr + 4 * q, make_float4(o[0], o[1], o[2], o[3]));
       } else {
         for (int c = 0; c < 4; ++c)
@@ -3224,13 +3226,13 @@ static int check_common(const float* g, int64_t rows, int64_t d, int64_t ld, int
   return GSPAR_OK;
 }
 
-static bool vec_ok(const Args& a);
+static bool rows_aligned(const Args& a);
 
 // Candidate keys per row: the full capacity for rows long enough to predict a band, within what
-// the workspace holds beyond its fixed part, on the vector path of a strided batch with a density
+// the workspace holds beyond its fixed part, on aligned rows of a strided batch with a density
 // budget; 0 otherwise.
 static int64_t cand_cap_of(const Args& a) {
-  if (a.seg || a.solver == GSPAR_VARIANCE || !vec_ok(a)) return 0;
+  if (a.seg || a.solver == GSPAR_VARIANCE || !rows_aligned(a)) return 0;
   const int64_t full = cand_cap_full(a.d);
   if (full == 0) return 0;
   const size_t fixed = layout_of(a.rows, a.d, 0).total;
@@ -3265,13 +3267,10 @@ static void plan(Args& a) {
   if (a.cand_region == 0) a.lay.cand_cap = 0;  // no room for a band
 }
 
-static bool vec_ok(const Args& a) {
-  if (a.seg) return a.seg_align != 0;
-  return ((uintptr_t)a.g % 16 == 0) && (a.ld % 4 == 0);
-}
+// Every row of a strided batch starts on a 16-byte boundary.
+static bool rows_aligned(const Args& a) { return ((uintptr_t)a.g % 16 == 0) && (a.ld % 4 == 0); }
 
 static int launch_solve(Args& a, hipStream_t s) {
-  const bool vec = vec_ok(a);
   const int64_t zero_items = a.rows * kC1 * (int64_t)(sizeof(Hist1) / 8) + a.rows * a.lay.tiles;
   const bool sq = a.solver == GSPAR_VARIANCE;  // histogram passes that also sum squares
   int ib = (int)((zero_items + 255) / 256);
@@ -3286,9 +3285,7 @@ static int launch_solve(Args& a, hipStream_t s) {
   const int64_t nblocks = a.seg ? a.seg_blocks : a.rows * a.nb;
   const dim3 grid((unsigned)nblocks);
   if (nblocks > 0) {
-    if (sq) launch(kcStats, vec ? k_stats<true, true, false> : k_stats<false, true, false>, grid, dim3(kNT), s, a);
-    else if (cand) launch(kcStats, k_stats<true, false, true>, grid, dim3(kNT), s, a);  // cand implies vec
-    else launch(kcStats, vec ? k_stats<true, false, false> : k_stats<false, false, false>, grid, dim3(kNT), s, a);
+    launch(kcStats, sq ? k_stats<true, false> : cand ? k_stats<false, true> : k_stats<false, false>, grid, dim3(kNT), s, a);
   }
   a.first = 1;
   launch(kcSolve, sq ? k_solve<true> : k_solve<false>, dim3((unsigned)a.rows), dim3(kNT), s, a);
@@ -3298,8 +3295,7 @@ static int launch_solve(Args& a, hipStream_t s) {
   for (int r = 0; r < R; ++r) {
     a.first = 0;
     if (nblocks > 0) {
-      if (sq) launch(kcRefine, vec ? k_refine<true, true> : k_refine<false, true>, grid, dim3(kNT), s, a);
-      else launch(kcRefine, vec ? k_refine<true, false> : k_refine<false, false>, grid, dim3(kNT), s, a);
+      launch(kcRefine, sq ? k_refine<true> : k_refine<false>, grid, dim3(kNT), s, a);
     }
     launch(kcSolve, sq ? k_solve<true> : k_solve<false>, dim3((unsigned)a.rows), dim3(kNT), s, a);
   }
@@ -3307,10 +3303,9 @@ static int launch_solve(Args& a, hipStream_t s) {
 }
 
 template <int K>
-static void launch_sample(const Args& a, bool vec, hipStream_t s) {
+static void launch_sample(const Args& a, hipStream_t s) {
   const dim3 grid((unsigned)(a.seg ? a.seg_wgs : a.rows * ((a.lay.tiles + K - 1) / K)));
-  if (a.code_b) launch(kcSample, vec ? k_sample<true, true, K> : k_sample<false, true, K>, grid, dim3(kTileThreads), s, a);
-  else launch(kcSample, vec ? k_sample<true, false, K> : k_sample<false, false, K>, grid, dim3(kTileThreads), s, a);
+  launch(kcSample, a.code_b ? k_sample<true, K> : k_sample<false, K>, grid, dim3(kTileThreads), s, a);
 }
 
 static int run_sample(Args& a, hipStream_t s) {
@@ -3318,12 +3313,11 @@ static int run_sample(Args& a, hipStream_t s) {
   if ((double)a.rows * (double)a.nb >= 2147483647.0) return GSPAR_ERR_ARG;
   int rc = launch_solve(a, s);
   if (rc) return rc;
-  const bool vec = vec_ok(a);
   // tiles per workgroup: 1 while every tile can be resident at once, else 2, so that a
   // workgroup's wait for its predecessors' prefix overlaps the decide phase of its second tile
   const int64_t tiles = a.seg ? a.seg_tiles : a.rows * a.lay.tiles;
-  if (a.seg ? a.seg_k == 1 : tiles <= kSampleResident) launch_sample<1>(a, vec, s);
-  else launch_sample<2>(a, vec, s);
+  if (a.seg ? a.seg_k == 1 : tiles <= kSampleResident) launch_sample<1>(a, s);
+  else launch_sample<2>(a, s);
   return hipGetLastError() == hipSuccess ? GSPAR_OK : GSPAR_ERR_HIP;
 }
 
@@ -3332,10 +3326,9 @@ static int run_probs(Args& a, hipStream_t s) {
   if ((double)a.rows * (double)a.nb >= 2147483647.0) return GSPAR_ERR_ARG;
   int rc = launch_solve(a, s);
   if (rc) return rc;
-  const bool vec = vec_ok(a) && (!a.p || (uintptr_t)a.p % 16 == 0);
   const int64_t nblocks = a.seg ? a.seg_blocks : a.rows * a.nb;
   const dim3 grid((unsigned)nblocks);
-  if (nblocks > 0) launch(kcProbs, vec ? k_probs<true> : k_probs<false>, grid, dim3(256), s, a);
+  if (nblocks > 0) launch(kcProbs, k_probs, grid, dim3(256), s, a);
   launch(kcProbsOut, k_probs_out, dim3((unsigned)((a.rows + 63) / 64)), dim3(64), s, a);
   return hipGetLastError() == hipSuccess ? GSPAR_OK : GSPAR_ERR_HIP;
 }
@@ -3501,7 +3494,7 @@ __global__ void __launch_bounds__(kNT) k_probe_read(const float* __restrict__ sr
   const int64_t beg = (int64_t)blockIdx.x * chunk, end = min(n, beg + chunk);
   float acc = 0.0f;
   if (beg < end)
-    stream_groups<true, 4, kNT>(src, beg, end, [&](int64_t, const float v[4], uint32_t) {
+    stream_groups<4, kNT>(src, beg, end, [&](int64_t, const float v[4], uint32_t) {
       acc += (v[0] + v[1]) + (v[2] + v[3]);
     });
   for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
@@ -3511,7 +3504,7 @@ __global__ void __launch_bounds__(kNT) k_probe_copy(const float* __restrict__ sr
   const int64_t chunk = ((n + kProbeGroups - 1) / kProbeGroups + 3) & ~(int64_t)3;
   const int64_t beg = (int64_t)blockIdx.x * chunk, end = min(n, beg + chunk);
   if (beg < end)
-    stream_groups<true, 4, kNT>(src, beg, end, [&](int64_t q, const float v[4], uint32_t m) {
+    stream_groups<4, kNT>(src, beg, end, [&](int64_t q, const float v[4], uint32_t m) {
       if (m == 0xFu) *reinterpret_cast<float4*>(dst + 4 * q) = make_float4(v[0], v[1], v[2], v[3]);
     });
 }
@@ -3705,7 +3698,7 @@ int sparsify_sample_compact_batched_noalloc(const float* g, int64_t rows, int64_
 
 // Host check of segment offsets (off[0] >= 0, nondecreasing, every length below 2^31): the longest
 // length (at least 1, the row length the workspace is sized for), the total length, and whether
-// vector loads may be used (g 16-byte aligned and every start a multiple of 4).
+// every segment is aligned (g 16-byte aligned and every start a multiple of 4).
 static int check_segments(const float* g, const int64_t* off, const int64_t* off_dev, int64_t segs, int64_t& maxlen,
                           int64_t& total, bool& aligned) {
   if (!g || !off || !off_dev || segs < 1 || segs > ((int64_t)1 << 24) || off[0] < 0) return GSPAR_ERR_ARG;

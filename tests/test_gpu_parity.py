@@ -515,6 +515,28 @@ def test_unaligned_scalar_path(gs):
         assert torch.equal(a.idx[:na], b.idx[:nb]) and torch.equal(a.val[:na], b.val[:nb])
 
 
+@pytest.mark.parametrize("shift", [1, 2, 3])
+@pytest.mark.parametrize("d", [1, 5, 16384, 16387, 300007])
+def test_rows_at_any_float_boundary(gs, d, shift):
+    """A row 4, 8 or 12 bytes past a 16-byte boundary (the same vector loads, misaligned) against the
+    same row on one: compaction and probabilities bit for bit, for every solver."""
+    g = torch.from_numpy(W.t_mixture(d, 62)).cuda()
+    buf = torch.zeros(d + 8, device="cuda")
+    view = buf[shift:shift + d]
+    view.copy_(g)
+    assert view.data_ptr() % 16 == 4 * shift
+    _say(f"[shifted] d={d} shift={shift}")
+    for solver, rho in (("greedy", 0.05), ("exact", 0.05), ("variance", 1.0)):
+        a = gs.sparsify_sample_compact(view, rho, seed=5, solver=solver, capacity=d)
+        b = gs.sparsify_sample_compact(g, rho, seed=5, solver=solver, capacity=d)
+        pa, pb = gs.sparsify_probs(view, rho, solver=solver), gs.sparsify_probs(g, rho, solver=solver)
+        torch.cuda.synchronize()
+        n = int(a.nnz.item())
+        assert n == int(b.nnz.item()) and float(a.lam.item()) == float(b.lam.item())
+        assert torch.equal(a.idx[:n], b.idx[:n]) and torch.equal(a.val[:n], b.val[:n])
+        assert torch.equal(pa.p, pb.p) and int(pa.k.item()) == int(pb.k.item())
+
+
 def test_batched_equals_rows_and_oracle(gs):
     rows, d = 12, 50003
     rng = np.random.default_rng(71)
