@@ -1,21 +1,18 @@
 // gspar: gradient sparsification (Wangni, Wang, Liu, Zhang; arXiv 1710.09854) for MI355X / gfx950.
 //
-// Pipeline per call (all launches on the caller's stream, no host synchronisation). Workgroups
-// never wait on one another inside a histogram pass: every cross-workgroup hand-off is a kernel
-// boundary, because device-scope fences are expensive on a multi-XCD part.
+// Pipeline per call (all launches on the caller's stream, no host synchronisation). The streaming
+// passes hand over to the next kernel at its boundary, because device-scope fences are expensive on
+// a multi-XCD part.
 //   k_init     clears the per-call workspace and writes each row's budget B = rho*d (for a
 //              segmented call, one row per segment, also the maps that give each workgroup of the
 //              later passes its segment, so that only workgroups holding coordinates are launched).
 //   k_stats    one streaming pass over g: an LDS histogram over binades of the magnitude bit pattern
 //              (count, exact significand sum, max), added into per-row global copies.
-//   k_solve    one workgroup per row: sums the copies and runs the solver (Proposition 1;
-//              Algorithm 2's criterion with a density budget, or Algorithm 3), which either
-//              finishes the row or asks for a refinement window.
-//   k_refine   (launched a fixed number of times, each followed by k_solve; exits at once unless
-//              the solver asked for it) histograms only the magnitudes inside one binade (4096
-//              sub-bins with their minima, and a direct count of the keys at or above the greedy
-//              query key) or inside one sub-bin (2048 single bit patterns), so every threshold the
-//              solvers need is resolved exactly.
+//   k_solve    the solver (Proposition 1; Algorithm 2's criterion with a density budget or as
+//              printed, or Algorithm 3): a leading workgroup per row sums the copies and decides;
+//              where a threshold cuts a binade that holds several keys, the row's workgroups list,
+//              bin or count that binade's keys for it, down to single bit patterns, so every
+//              threshold the solvers need is resolved exactly.
 //   k_sample   one streaming pass: Philox4x32-10 per group of four coordinates, Bernoulli selection,
 //              amplification to g_i or sign(g_i)/lambda, order-preserving compaction with a
 //              decoupled look-back across tiles.
@@ -26,8 +23,8 @@
 //
 // Sums of magnitudes are exact: a magnitude's bit pattern (its "key") fixes its binade, bins never
 // straddle a binade, so per-bin sums of 24-bit significands are exact integers and are combined
-// in a 320-bit fixed-point accumulator (unit 2^-149) that is rounded once to double. Hence lambda,
-// the capped set and every decision are independent of the launch geometry and of atomic order.
+// in a fixed-point sum (unit 2^-149) that is rounded once to double. Hence lambda, the capped set
+// and every decision are independent of the launch geometry and of atomic order.
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -50,14 +47,13 @@
 namespace gspar {
 
 constexpr uint32_t kKeyInf = 0x7F800000u;   // bit pattern of +inf: keys >= this are non-finite
-constexpr uint32_t kNone = 0xFFFFFFFFu;
 constexpr int kNT = 512;                    // threads of the histogram / solver workgroups
 constexpr int kLaneCopies = 8;              // LDS copies of the statistics histogram (by lane)
 constexpr int kC1 = 4;                      // global copies of the level-1 histogram per row
-constexpr int kC23 = 2;                     // global copies of the level-2 / level-3 histograms
 constexpr int kB1 = 256;                    // level 1: one bin per binade (key >> 23)
-constexpr int kB2 = 4096;                   // level 2: one binade, 2^11 keys per bin
-constexpr int kB3 = 2048;                   // level 3: one level-2 bin, one key per bin
+constexpr int kWB = 512;                    // bins of a refinement window, one per thread
+constexpr int kWC = 4;                      // copies of a window, in LDS by lane and in global memory
+static_assert(kWB == kNT, "one bin per thread");
 constexpr int kTileThreads = 256;
 constexpr int kTileGroups = 16;             // float4 groups per thread per tile
 constexpr int kTileElems = kTileThreads * kTileGroups * 4;  // 16384 coordinates per tile
@@ -69,195 +65,65 @@ constexpr int kTileElems = kTileThreads * kTileGroups * 4;  // 16384 coordinates
 constexpr int64_t kSampleResident = GSPAR_SAMPLE_RESIDENT;
 constexpr int kMaxIters = 64;
 constexpr int64_t kMaxChunk = (1 << 20) - 4;  // LDS packing holds < 2^20 elements per workgroup
+static_assert(INT32_MAX / kMaxChunk + 1 <= 2049, "histogram chunks of the longest row");
 
 enum : uint32_t { kFlagInternal = 16 };
 
 // ------------------------------------------------------------------------------------------
-// 320-bit fixed point, value = x * 2^-149 (the smallest subnormal float).
+// Exact sums. A value v * 2^s is added into an array of 32-bit digits held in 64-bit words (digit i
+// weighs 2^(32 i)); a word takes up to 2^30 additions before it could overflow, so many threads can
+// add with plain 64-bit atomics and no carry, and the carries are resolved once, when the sum is
+// rounded. Magnitudes are in units of 2^-149 (the smallest subnormal float), their squares in units
+// of 2^-298.
 // ------------------------------------------------------------------------------------------
-struct Fx {
-  uint64_t w[5];
-};
+constexpr int kDig = 11;    // sums of magnitudes: below 2^31 * 2^24 * 2^254 = 2^309
+constexpr int kDigSq = 20;  // sums of squares: below 2^31 * 2^48 * 2^508 = 2^587
 
-GS_HD Fx fx_zero() {
-  Fx r;
-  for (int i = 0; i < 5; ++i) r.w[i] = 0;
-  return r;
-}
-GS_HD void fx_add(Fx& a, const Fx& b) {
-  uint64_t c = 0;
-  for (int i = 0; i < 5; ++i) {
-    uint64_t s = a.w[i] + b.w[i];
-    uint64_t c1 = s < a.w[i];
-    uint64_t s2 = s + c;
-    uint64_t c2 = s2 < s;
-    a.w[i] = s2;
-    c = c1 | c2;
-  }
-}
-GS_HD Fx fx_sub(const Fx& a, const Fx& b) {  // requires a >= b
-  Fx r;
-  uint64_t br = 0;
-  for (int i = 0; i < 5; ++i) {
-    uint64_t d1 = a.w[i] - b.w[i];
-    uint64_t b1 = a.w[i] < b.w[i];
-    uint64_t d2 = d1 - br;
-    uint64_t b2 = d1 < br;
-    r.w[i] = d2;
-    br = b1 | b2;
-  }
-  return r;
-}
-// Limb i of a, with i in [0, 5) known only at run time; written as selects so the accumulator
-// stays in registers (no dynamically indexed private array).
-GS_HD uint64_t fx_limb(const Fx& a, int i) {
-  uint64_t r = 0;
-#pragma unroll
-  for (int j = 0; j < 5; ++j) r = (j == i) ? a.w[j] : r;
-  return r;
-}
-// v * 2^s for s in [0, 255] (every v < 2^64 then fits). A shift outside that range breaks an
-// invariant of the callers (a binade index outside [0, 255]): it sets kFlagInternal in *err and
-// gives 0, so the row is reported instead of being solved with a wrong sum.
-GS_HD Fx fx_shifted(uint64_t v, int s, uint32_t* err) {
-  if ((unsigned)s > 255u) {
-    *err |= kFlagInternal;
-    return fx_zero();
-  }
-  const int li = s >> 6, off = s & 63;
-  const uint64_t lo = v << off;
-  const uint64_t hi = off ? (v >> (64 - off)) : 0;
-  Fx r;
-#pragma unroll
-  for (int j = 0; j < 5; ++j) r.w[j] = (j == li) ? lo : ((j == li + 1) ? hi : 0);
-  return r;
-}
-GS_HD bool fx_bit(const Fx& a, int k) { return (fx_limb(a, k >> 6) >> (k & 63)) & 1; }
-GS_HD bool fx_any_below(const Fx& a, int k) {  // any set bit at positions [0, k)
-  if (k <= 0) return false;
-  const int li = k >> 6, off = k & 63;
-  bool any = false;
-#pragma unroll
-  for (int j = 0; j < 5; ++j) {
-    const uint64_t m = j < li ? ~0ull : ((j == li && off) ? ((1ull << off) - 1) : 0ull);
-    any = any || (a.w[j] & m) != 0;
-  }
-  return any;
-}
-// Round to the nearest double, ties to even.
-GS_HD double fx_to_double(const Fx& a) {
-  int top = -1;
-#pragma unroll
-  for (int i = 0; i < 5; ++i)
-    if (a.w[i]) top = i * 64 + 63 - __builtin_clzll(a.w[i]);
-  if (top < 0) return 0.0;
-  if (top < 53) return ldexp((double)a.w[0], -149);
-  const int lo = top - 52;
-  const int li = lo >> 6, off = lo & 63;
-  uint64_t m = fx_limb(a, li) >> off;
-  if (off) m |= fx_limb(a, li + 1) << (64 - off);
-  m &= (1ull << 53) - 1;
-  const bool rnd = fx_bit(a, lo - 1);
-  const bool sticky = fx_any_below(a, lo - 1);
-  if (rnd && (sticky || (m & 1))) m += 1;
-  return ldexp((double)m, lo - 149);
+// The three digit additions of v * 2^s, s in [0, smax]: x[i] goes to digit at + i. A shift outside
+// the range breaks an invariant of the callers (a binade index outside [0, 255]) and is reported:
+// kFlagInternal, and nothing to add.
+GS_HD uint32_t dig_split(uint64_t v, int s, int smax, int& at, uint64_t x[3]) {
+  const bool ok = s >= 0 && s <= smax;
+  at = ok ? s >> 5 : 0;
+  const int off = s & 31;
+  const uint64_t a = (v & 0xFFFFFFFFull) << off, b = (v >> 32) << off;
+  x[0] = ok ? a & 0xFFFFFFFFull : 0;
+  x[1] = ok ? (a >> 32) + (b & 0xFFFFFFFFull) : 0;
+  x[2] = ok ? b >> 32 : 0;
+  return ok ? 0u : (uint32_t)kFlagInternal;
 }
 
-// ------------------------------------------------------------------------------------------
-// 640-bit fixed point, value = x * 2^-298 (the square of the smallest subnormal float): exact sums
-// of squared magnitudes for the variance-budget solver.
-// ------------------------------------------------------------------------------------------
-constexpr int kQ = 10;
-struct Fq {
-  uint64_t w[kQ];
-};
-
-GS_HD Fq fq_zero() {
-  Fq r;
-  for (int i = 0; i < kQ; ++i) r.w[i] = 0;
-  return r;
-}
-GS_HD void fq_add(Fq& a, const Fq& b) {
-  uint64_t c = 0;
-  for (int i = 0; i < kQ; ++i) {
-    uint64_t s = a.w[i] + b.w[i];
-    uint64_t c1 = s < a.w[i];
-    uint64_t s2 = s + c;
-    uint64_t c2 = s2 < s;
-    a.w[i] = s2;
-    c = c1 | c2;
+// Rounds the digit sum times 2^unit to the nearest double, ties to even: the top 64 bits with every
+// lower bit folded into the last one, then two exact conversions and one rounded addition.
+template <int N, class T>
+GS_HD double dig_round(const T* d, int unit) {
+  uint64_t carry = 0, next = d[0];
+  uint32_t p1 = 0, p2 = 0, low = 0;          // the digits below the current one, and all below those
+  uint32_t t0 = 0, t1 = 0, t2 = 0, rest = 0;  // the same at the highest nonzero digit
+  int top = 0;
+#pragma unroll 1
+  for (int i = 0; i < N; ++i) {
+    const uint64_t v = next + carry;
+    next = d[i + 1 < N ? i + 1 : i];
+    const uint32_t x = (uint32_t)v;
+    carry = v >> 32;
+    if (x) {
+      top = i;
+      t0 = x;
+      t1 = p1;
+      t2 = p2;
+      rest = low;
+    }
+    low |= p2;
+    p2 = p1;
+    p1 = x;
   }
-}
-GS_HD Fq fq_sub(const Fq& a, const Fq& b) {  // requires a >= b
-  Fq r;
-  uint64_t br = 0;
-  for (int i = 0; i < kQ; ++i) {
-    uint64_t d1 = a.w[i] - b.w[i];
-    uint64_t b1 = a.w[i] < b.w[i];
-    uint64_t d2 = d1 - br;
-    uint64_t b2 = d1 < br;
-    r.w[i] = d2;
-    br = b1 | b2;
-  }
-  return r;
-}
-GS_HD uint64_t fq_limb(const Fq& a, int i) {
-  uint64_t r = 0;
-#pragma unroll
-  for (int j = 0; j < kQ; ++j) r = (j == i) ? a.w[j] : r;
-  return r;
-}
-// Squared significands summed per bin as qh * 2^24 + ql (each square m^2 < 2^48 split at bit 24;
-// qh, ql < 2^55 for at most 2^31 values), times 2^(2 shift): the bin's exact sum of squares. The
-// sum is below 2^80, so 2 shift in [0, 511] keeps it inside the 640 bits; any other shift sets
-// kFlagInternal in *err and gives 0, like fx_shifted.
-GS_HD Fq fq_squares(uint64_t qh, uint64_t ql, int shift, uint32_t* err) {
-  const int sh = 2 * shift;
-  if ((unsigned)sh > 511u) {
-    *err |= kFlagInternal;
-    return fq_zero();
-  }
-  const uint64_t lo0 = qh << 24;
-  const uint64_t lo = lo0 + ql;
-  const uint64_t hi = (qh >> 40) + (lo < lo0 ? 1 : 0);
-  const int li = sh >> 6, off = sh & 63;
-  const uint64_t w0 = lo << off;
-  const uint64_t w1 = off ? ((lo >> (64 - off)) | (hi << off)) : hi;
-  const uint64_t w2 = off ? (hi >> (64 - off)) : 0;
-  Fq r;
-#pragma unroll
-  for (int j = 0; j < kQ; ++j) r.w[j] = j == li ? w0 : (j == li + 1 ? w1 : (j == li + 2 ? w2 : 0));
-  return r;
-}
-GS_HD bool fq_bit(const Fq& a, int k) { return (fq_limb(a, k >> 6) >> (k & 63)) & 1; }
-GS_HD bool fq_any_below(const Fq& a, int k) {
-  if (k <= 0) return false;
-  const int li = k >> 6, off = k & 63;
-  bool any = false;
-#pragma unroll
-  for (int j = 0; j < kQ; ++j) {
-    const uint64_t m = j < li ? ~0ull : ((j == li && off) ? ((1ull << off) - 1) : 0ull);
-    any = any || (a.w[j] & m) != 0;
-  }
-  return any;
-}
-// Round to the nearest double, ties to even.
-GS_HD double fq_to_double(const Fq& a) {
-  int top = -1;
-#pragma unroll
-  for (int i = 0; i < kQ; ++i)
-    if (a.w[i]) top = i * 64 + 63 - __builtin_clzll(a.w[i]);
-  if (top < 0) return 0.0;
-  if (top < 53) return ldexp((double)a.w[0], -298);
-  const int lo = top - 52;
-  const int li = lo >> 6, off = lo & 63;
-  uint64_t m = fq_limb(a, li) >> off;
-  if (off) m |= fq_limb(a, li + 1) << (64 - off);
-  m &= (1ull << 53) - 1;
-  const bool rnd = fq_bit(a, lo - 1);
-  const bool sticky = fq_any_below(a, lo - 1);
-  if (rnd && (sticky || (m & 1))) m += 1;
-  return ldexp((double)m, lo - 298);
+  if (t0 == 0) return 0.0;
+  const int lz = __builtin_clz(t0);
+  uint64_t m = (((uint64_t)t0 << 32) | t1) << lz;
+  m |= lz ? t2 >> (32 - lz) : 0u;
+  m |= ((t2 << lz) | rest) != 0 ? 1u : 0u;
+  return ldexp((double)(uint32_t)(m >> 32) * 0x1p32 + (double)(uint32_t)m, 32 * (top - 1) - lz + unit);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -292,7 +158,9 @@ GS_HD uint32_t cap_key(double lam) {
     k = key_of((float)x);
     if (k == 0) k = 1;
   }
+#pragma unroll 1
   for (int it = 0; it < 4 && k > 1 && lam * key_value(k - 1) >= 1.0; ++it) --k;
+#pragma unroll 1
   for (int it = 0; it < 4 && k < kKeyInf && !(lam * key_value(k) >= 1.0); ++it) ++k;
   return k;
 }
@@ -328,39 +196,34 @@ GS_HD void philox10(uint32_t& c0, uint32_t& c1, uint32_t& c2, uint32_t& c3, uint
 // ------------------------------------------------------------------------------------------
 // Workspace.
 // ------------------------------------------------------------------------------------------
+// A row's control block. The first 128 bytes are the solver's hand-off words, read and written by
+// its workgroups at agent scope while the solver kernel runs; the rest is written by one kernel and
+// read by later ones.
 struct alignas(256) RowCtl {
-  double B;          // rho * d
-  double lam;        // greedy: current lambda; final: lambda of Proposition 1
-  Fx S;              // exact sum of |g|
-  Fx fbW;            // exact solver: capped sum of the best candidate found so far
-  uint64_t fbK;      // exact solver: capped count of that candidate
-  uint64_t zeros;    // zero entries of the row (d minus the histogram's population)
-  uint64_t wK;       // exact solver, level 3: count of keys above the window
-  Fx wW;             // and their exact sum
+  uint64_t req;      // the current request (see Pass; 0: none yet)
+  uint32_t lcount;   // keys in the list (kReqList)
+  uint32_t pad0[29];
+  double B;          // rho * d (the variance-budget solver: eps)
+  double lam;        // lambda of Proposition 1
   float inv_lam;     // fl32(1/lambda): the amplified value off the capped set
-  uint32_t fbTcap;   // exact solver: candidate's capped threshold key
-  uint32_t fbValid;
-  uint32_t tcap;     // final: coordinate capped (p = 1) iff key >= tcap
+  uint32_t tcap;     // coordinate capped (p = 1) iff key >= tcap
   uint32_t flags;
-  uint32_t need;     // 0: none; 2 / 3: a level-2 / level-3 pass is requested
   uint32_t done;     // 1 once lambda and tcap are final
-  uint32_t qkey;     // greedy: key whose count and sum above the level-2 pass also counts directly
-  uint32_t src;      // 1: the requested window lies in the candidate band, its pass reads the candidates
-  uint32_t l2exp;    // binade of the level-2 window (kNone: none)
-  uint32_t l3base;   // first key of the level-3 window (kNone: none)
-  int32_t iter;      // greedy rescale steps taken
-  int32_t stage;     // 0 before the first solve; exact solver: next level to examine
   int32_t solver;
   int32_t T;
+  uint32_t pad1[6];
+  uint32_t src;      // 1: the solver's last request read the candidates
+  uint32_t pad2[6];
   uint32_t band_lo;  // candidate band [band_lo, band_hi) of keys (whole binades) the statistics pass
   uint32_t band_hi;  // collected, written by its first workgroup (equal bounds: no band)
-  uint64_t cand_n;   // candidates collected (first solve; above the capacity: incomplete, unused)
-  uint32_t qonly;    // greedy, last rescale step: the level-2 pass only counts the keys >= qkey
+  uint32_t pad3;
+  uint64_t cand_n;   // candidates collected (above the capacity: incomplete, unused)
+  uint64_t pad4[2];
 };
 static_assert(sizeof(RowCtl) == 256, "RowCtl layout");
 // offsets read by the tests to see which source a refinement pass used
-static_assert(offsetof(RowCtl, src) == 192 && offsetof(RowCtl, band_lo) == 220 && offsetof(RowCtl, band_hi) == 224 &&
-                  offsetof(RowCtl, cand_n) == 232,
+static_assert(offsetof(RowCtl, B) == 128 && offsetof(RowCtl, src) == 192 && offsetof(RowCtl, band_lo) == 220 &&
+                  offsetof(RowCtl, band_hi) == 224 && offsetof(RowCtl, cand_n) == 232,
               "RowCtl offsets known to the tests");
 
 struct Hist1 {
@@ -368,44 +231,46 @@ struct Hist1 {
   uint64_t sig[kB1];
   uint32_t mx[kB1];
 };
-// Histogram of one refinement window: a level-2 window uses all kB2 bins (one binade, 2^11 keys per
-// bin), a level-3 window the first kB3 (one key per bin).
-struct alignas(256) WinHist {
-  uint64_t cnt[kB2];
-  uint64_t sig[kB2];
-  uint32_t mx[kB2];
-  uint32_t mnc[kB2];  // level 2: bitwise complement of the bin's minimum key (0: empty), so max-combined
-  uint64_t qcnt;      // level 2: count of window keys >= the row's qkey
-  uint64_t qsig;      // their significand sum
-};
-
-// The level-1 histogram summed over its copies, with per binade the count K and exact sum W of all
-// keys in the binades above it.
-struct alignas(16) L1Cache {
-  uint64_t cnt[kB1];
-  uint64_t sig[kB1];
-  uint32_t mx[kB1];
-  uint64_t K[kB1];
-  Fx W[kB1];
-};
-static_assert(sizeof(L1Cache) % 16 == 0, "L1Cache is copied in 16-byte units");
-// Variance-budget solver: per-bin sums of squared significands (see fq_squares) of the level-1
-// histogram copies and of the level-2 window copies, and per row the exact total of squares and
-// the square sums that go with the solver's stored counts and sums (above the requested window,
-// and of the fallback candidate).
+// Variance-budget solver: squared significands m^2 < 2^48 of the level-1 histogram copies, summed as
+// their bits 24-47 (qh) and 0-23 (ql).
 struct H1Q {
   uint64_t qh[kB1];
   uint64_t ql[kB1];
 };
-struct alignas(256) WinQ {
-  uint64_t qh[kB2];
-  uint64_t ql[kB2];
+// One copy of a refinement window: per bin the count, the maximum key's offset in the window, and the
+// sums of the offsets within the bin and (variance budget) of their squares.
+struct WinBins {
+  uint32_t cnt[kWB];
+  uint32_t mx[kWB];
+  uint64_t sr[kWB];
+  uint64_t s2[kWB];
 };
-struct alignas(256) VarCtl {
-  Fq A2;   // sum of a^2 over the row
-  Fq wH;   // square sum above the requested window
-  Fq fbH;  // square sum of the fallback candidate's capped set
+// The solver's scratch of a row: copies of the refinement window and the list of the keys of a
+// range, when it holds few enough.
+constexpr size_t kScratchBytes = 345856;
+constexpr int kMaxChunks = 2048 + 8;  // histogram chunks of the longest row (2^31 - 1 coordinates)
+// A chunk of the row's requests: the last request that was taken and that was finished, and for
+// kReqCount its keys >= qkey and their significand sum.
+struct ChunkState {
+  uint32_t taken;
+  uint32_t done;
+  uint32_t qcnt;
+  uint32_t pad;
+  uint64_t qsig;
 };
+constexpr int kListMax = (int)((kScratchBytes - kWC * sizeof(WinBins) - kMaxChunks * sizeof(ChunkState)) / sizeof(uint32_t));
+// Keys of a range up to which it is listed instead of binned again (a build may lower it to exercise
+// the windows on small inputs).
+#ifndef GSPAR_LIST_CAP
+#define GSPAR_LIST_CAP kListMax
+#endif
+constexpr uint32_t kListCap = GSPAR_LIST_CAP;
+struct alignas(256) RowScratch {
+  WinBins win[kWC];
+  ChunkState chunk[kMaxChunks];
+  uint32_t list[kListMax];
+};
+static_assert(sizeof(RowScratch) == kScratchBytes && kListCap <= (uint32_t)kListMax, "solver scratch of a row");
 
 // Per-row partial count of capped coordinates written by the probabilities pass, one per class.
 struct alignas(128) CountLine {
@@ -423,7 +288,7 @@ struct PreHist {
 GS_HD size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-  size_t ctl, h1, l1t, win, kc, status, bmap, tmap, h1q, winq, vctl, pre, ccnt, cand, total;
+  size_t ctl, h1, scratch, kc, status, bmap, tmap, h1q, pre, ccnt, cand, total;
   int64_t tiles;     // tiles per row of the sample pass
   int64_t cand_cap;  // candidate keys per row (0: no candidate band)
 };
@@ -452,12 +317,9 @@ GS_HD int64_t pre_lines(int64_t len) {
   const int64_t nl = len / 16, ns = (int64_t)kPreWG * kPreLines;
   return nl < ns ? nl : ns;
 }
-// Refinement over candidates: at least kCandShare keys per workgroup and at most kCandGroups
-// workgroups per row (each workgroup adds its whole window into the global copies, so fewer,
-// fuller workgroups cost fewer global atomics), read kCandLoads float4 per thread at a time.
-constexpr int64_t kCandShare = 1 << 14;
+// Refinement over candidates: at least kCandShare keys per chunk and at most kCandGroups chunks.
+constexpr int64_t kCandShare = 1 << 13;
 constexpr int64_t kCandGroups = 128;
-constexpr int kCandLoads = 8;
 // keys a lane buffers in LDS before its wave flushes (an odd stride keeps the lanes on different
 // banks); sized so that the statistics workgroup stays within a quarter of the LDS (four resident
 // per compute unit)
@@ -470,8 +332,7 @@ GS_HD int64_t cand_cap_full(int64_t d) {
   return (c < d ? c : d) & ~(int64_t)63;  // whole 256-byte blocks
 }
 
-// Histogram copies: row r's copy c of level 1 is h1 + (r * kC1 + c), of a refinement window
-// win + (r * kC23 + c); the solve that requests a refinement pass clears the window's copies.
+// Histogram copies: row r's copy c of level 1 is h1 + (r * kC1 + c).
 // cand_cap: candidate keys per row (the workspace ends with the candidate buffers, so a smaller
 // capacity changes no other offset).
 GS_HD Layout layout_of(int64_t rows, int64_t d, int64_t cand_cap) {
@@ -482,10 +343,8 @@ GS_HD Layout layout_of(int64_t rows, int64_t d, int64_t cand_cap) {
   off += align256((size_t)rows * sizeof(RowCtl));
   L.h1 = off;
   off += align256((size_t)rows * kC1 * sizeof(Hist1));
-  L.l1t = off;
-  off += align256((size_t)rows * sizeof(L1Cache));
-  L.win = off;
-  off += align256((size_t)rows * kC23 * sizeof(WinHist));
+  L.scratch = off;
+  off += (size_t)rows * sizeof(RowScratch);
   L.kc = off;
   off += align256((size_t)rows * 8 * sizeof(CountLine));
   L.status = off;
@@ -499,10 +358,6 @@ GS_HD Layout layout_of(int64_t rows, int64_t d, int64_t cand_cap) {
   // variance-budget solver only
   L.h1q = off;
   off += align256((size_t)rows * kC1 * sizeof(H1Q));
-  L.winq = off;
-  off += align256((size_t)rows * kC23 * sizeof(WinQ));
-  L.vctl = off;
-  off += align256((size_t)rows * sizeof(VarCtl));
   // candidate band
   L.pre = off;
   off += align256((size_t)rows * sizeof(PreHist));
@@ -527,7 +382,6 @@ struct Args {
   Layout lay;
   int nb;          // workgroups per row of the histogram passes
   int64_t chunk;   // elements per histogram workgroup (multiple of 4)
-  int first;       // k_solve: the solve right after the statistics pass
   int32_t* idx;    // compaction: every survivor; hybrid coding: Q_A, the capped survivors
   float* val;
   int64_t cap;
@@ -582,23 +436,12 @@ __device__ __forceinline__ RowCtl* ctl_of(const Args& a, int64_t r) {
 __device__ __forceinline__ Hist1* h1_of(const Args& a, int64_t r, int c = 0) {
   return reinterpret_cast<Hist1*>(a.ws + a.lay.h1) + r * kC1 + c;
 }
-__device__ __forceinline__ L1Cache* l1t_of(const Args& a, int64_t r) {
-  return reinterpret_cast<L1Cache*>(a.ws + a.lay.l1t) + r;
+__device__ __forceinline__ RowScratch* scratch_of(const Args& a, int64_t r) {
+  return reinterpret_cast<RowScratch*>(a.ws + a.lay.scratch) + r;
 }
-__device__ __forceinline__ WinHist* win_of(const Args& a, int64_t r, int c = 0) {
-  return reinterpret_cast<WinHist*>(a.ws + a.lay.win) + r * kC23 + c;
-}
-
 __device__ __forceinline__ H1Q* h1q_of(const Args& a, int64_t r, int c = 0) {
   return reinterpret_cast<H1Q*>(a.ws + a.lay.h1q) + r * kC1 + c;
 }
-__device__ __forceinline__ WinQ* winq_of(const Args& a, int64_t r, int c = 0) {
-  return reinterpret_cast<WinQ*>(a.ws + a.lay.winq) + r * kC23 + c;
-}
-__device__ __forceinline__ VarCtl* vctl_of(const Args& a, int64_t r) {
-  return reinterpret_cast<VarCtl*>(a.ws + a.lay.vctl) + r;
-}
-
 __device__ __forceinline__ CountLine* kc_of(const Args& a, int64_t r) {
   return reinterpret_cast<CountLine*>(a.ws + a.lay.kc) + r * 8;
 }
@@ -728,11 +571,8 @@ __device__ __forceinline__ void stream_groups(const float* __restrict__ row, int
   }
 }
 
-// ------------------------------------------------------------------------------------------
-// The per-row solver, run by one workgroup of kNT threads per row (k_solve). Every helper is
-// force-inlined so LDS and global pointers keep their address spaces and no call frames or scratch
-// are needed.
-// ------------------------------------------------------------------------------------------
+// Helpers of the histogram passes and the solver are force-inlined, so LDS and global pointers keep
+// their address spaces and no call frames or scratch are needed.
 #define GS_DI __device__ __attribute__((always_inline)) inline
 
 // LDS of the statistics pass: per binade and lane class, (count << 44) | significand sum and the
@@ -741,7 +581,7 @@ struct StatsLds {
   unsigned long long pk[kB1 * kLaneCopies];
   uint32_t mx[kB1 * kLaneCopies];
 };
-// with the squared significands of the variance-budget solver (split at bit 24, see fq_squares)
+// with the squared significands of the variance-budget solver (split at bit 24, see H1Q)
 template <bool SQ>
 struct StatsLdsT : StatsLds {};
 template <>
@@ -749,460 +589,533 @@ struct StatsLdsT<true> : StatsLds {
   unsigned long long qh[kB1 * kLaneCopies];
   unsigned long long ql[kB1 * kLaneCopies];
 };
-// LDS of a refinement pass: one window of at most kB2 bins, same packing, and for a level-2 window
-// the complemented bin minimum.
+// popcount(m & bits of the lanes below this one)
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+// Exclusive prefix over the lanes of a wave of x in [0, 2^B) from B ballots; `total` receives the
+// wave's sum.
+template <int B>
+__device__ __forceinline__ uint32_t wave_prefix_bits(uint32_t x, uint32_t& total) {
+  uint32_t pre = 0;
+  total = 0;
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    const unsigned long long m = __ballot((x >> b) & 1);
+    pre += lanes_below(m) << b;
+    total += (uint32_t)__popcll(m) << b;
+  }
+  return pre;
+}
+
+// ------------------------------------------------------------------------------------------
+// The solver: one kernel after the statistics pass, k_solve, with a leading workgroup per row
+// (workgroups 0 .. rows - 1) and helpers for the rows of more than one histogram chunk.
+//
+// What bounds it is latency: a row needs its 256 binades, then (only if a capped threshold falls
+// inside a binade that holds several keys) the keys of that binade, which may take a pass over the
+// row. The leader decides everything; a pass over the row (or over its candidates) is a request in
+// the row's control block that every workgroup of the row takes chunks of. One launch does it all:
+// a row that needs no pass costs one short kernel (9-10 us), where a launch for every possible
+// pass and solve cost 23 us (11 us for the first solve, the rest idle kernels). A call on 65,536
+// coordinates takes 26.8 us with it against 38.9 before, the 54 layers of a residual network 73.7
+// against 96.6; 5 rows of 300,007 whose solver lists a binade 44 against 70, 2^28 coordinates 457
+// against 483 (exact, rho = 0.01) and 539 against 571 (greedy, rho = 0.1), 16 rows of 2^20 under the
+// variance budget 249 against 266.
+//
+// Waiting: a chunk is taken with an atomic on its own word by its helper, or by the leader once it
+// has done its own, so a chunk is only ever held by a running workgroup and the leader waits only
+// for chunks that were taken: no wait depends on another workgroup being scheduled. Helpers are
+// optional (the leader alone would take every chunk); one that finds no request for long enough
+// leaves. Hand-offs use agent-scope atomics for the data itself as well as for the words that
+// announce it, each side waiting for its own accesses to complete (s_waitcnt) before it announces
+// them, so no cache write-back or invalidation is needed. Every word that all chunks would touch is
+// avoided: atomics on one address take 10-30 ns each (counting a 2^28 row's candidates through one
+// counter per wave took 150 us a request).
+//
+// Exact and variance solver: descend from binades (2^23 keys) to windows of 512 bins, of 2^14, then
+// 2^5, then single keys. At each level the highest bin whose maximum passes the criterion (b1) and
+// the lowest occupied bin above it (b2): the answer is b1's maximum unless b2 holds two or more keys
+// that could still pass, in which case b2 is the next window. A range of at most kListCap keys is
+// collected into a list once and every further level is binned from it by the leader.
+// ------------------------------------------------------------------------------------------
+enum : uint32_t { kReqWindow = 1, kReqList = 2, kReqCount = 3 };
+constexpr uint32_t kReqDone = 255;      // request number: the row is solved
+constexpr int kHelperPolls = 1 << 15;   // some 20 ms without a request
+constexpr int kKeyRegs = 8;             // listed keys each thread of the leader keeps in registers
+constexpr int kPassBuf = 4096;          // listed keys a workgroup gathers in LDS before it appends them
+
+template <class T>
+GS_DI T ld_agent(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+GS_DI void st_agent(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// A value every lane holds equally, moved to scalar registers.
+template <class T>
+GS_DI T uni(T v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  static_assert(sizeof(T) % 4 == 0, "whole registers");
+  uint32_t w[sizeof(T) / 4];
+  memcpy(w, &v, sizeof(T));
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(T) / 4); ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
+  memcpy(&v, w, sizeof(T));
+#endif
+  return v;
+}
+// Every access of this wave so far has completed.
+GS_DI void wait_own() { __builtin_amdgcn_s_waitcnt(0); }
+
+// One request. The leader announces it as one word, so that a helper needs no second look:
+// bits 0-31 the range's first key (kReqCount: the query key), 32-39 its number, 40-41 its kind, 42
+// set when the chunks are of the row's candidates, 43-44 the range: a binade, 2^14 or 2^5 keys.
+struct Pass {
+  uint32_t key, num, kind, from, shift;
+};
+GS_DI uint64_t pass_word(const Pass& P) {
+  const uint32_t lev = P.shift == 14 ? 0u : (P.shift == 5 ? 1u : 2u);
+  return ((uint64_t)(P.num | (P.kind << 8) | (P.from << 10) | (lev << 11)) << 32) | P.key;
+}
+GS_DI Pass pass_of(uint64_t w) {
+  const uint32_t h = (uint32_t)(w >> 32), lev = h >> 11;
+  Pass P;
+  P.key = (uint32_t)w;
+  P.num = h & 0xFFu;
+  P.kind = (h >> 8) & 3u;
+  P.from = (h >> 10) & 1u;
+  P.shift = lev == 0 ? 14u : (lev == 1 ? 5u : 0u);
+  return P;
+}
+// The chunks of the row, or of its candidates: equal shares of whole groups of 4, at least kCandShare
+// keys each, at most kCandGroups shares. n: the source's length.
+GS_DI void pass_chunks(const Args& a, uint32_t from, int64_t n, int64_t& share, uint32_t& chunks) {
+  share = a.chunk;
+  if (from) {
+    const int64_t groups = min((int64_t)a.nb, kCandGroups);
+    share = max(kCandShare, (((n + groups - 1) / groups) + 3) & ~(int64_t)3);
+  }
+  chunks = (uint32_t)((n + share - 1) / share);
+}
+
+// LDS of a window binned by one workgroup: kWC copies by lane. pk: (count << 44) | sum of offsets
+// within the bin (fewer than 2^20 keys a time, offsets below 2^14).
+template <bool VAR>
 struct WinLds {
-  unsigned long long pk[kB2];
-  uint32_t mx[kB2];
-  uint32_t mnc[kB2];
-  uint64_t qc[kNT / 64];
-  uint64_t qs[kNT / 64];
+  unsigned long long pk[kWB * kWC];
+  unsigned long long s2[VAR ? kWB * kWC : 1];
+  uint32_t mx[kWB * kWC];
 };
-template <bool SQ>
-struct WinLdsT : WinLds {};
-template <>
-struct WinLdsT<true> : WinLds {
-  unsigned long long qh[kB2];
-  unsigned long long ql[kB2];
+// A bin of the level under examination, broadcast by the thread that owns it.
+struct BinOut {
+  uint64_t part;   // significand sum of the keys of binade E up to and including the bin
+  uint64_t ph, pl; // and of their squares (bits above 24, low part)
+  uint64_t sig, sh, sl;  // the bin's own sums
+  uint32_t below;  // keys of the row up to and including the bin
+  uint32_t cnt, mx, state;
 };
-struct BinInfo {
-  uint64_t Kab;  // count of keys strictly above the bin (including above the window)
-  Fx Wab;        // their exact sum
-  uint64_t cnt;
-  Fx Wb;
-  uint32_t mx;
-};
-// The solver's working copies of the histograms, in LDS: level 1 (L1Cache, kept in global memory
-// as well between solves); the level-2 and level-3 windows when they exist.
-template <int N>
-struct WinCache {
-  uint32_t cnt[N];  // window counts never exceed d < 2^31
-  uint64_t sig[N];
-  uint32_t mx[N];
-};
+template <bool VAR>
 struct SolveLds {
-  uint64_t sk[kNT / 64];  // per-wave partial results of block scans and reductions
-  uint64_t ss[kNT / 64];
-  Fx sw[kB1 / 64];
-  int ired[kNT / 64];
-  BinInfo bi;
-  L1Cache l1;
-  WinCache<kB2> w2;
-  WinCache<kB3> w3;
-  uint32_t err;         // kFlagInternal when a wide-arithmetic invariant broke during this solve
-  uint64_t bcnt, bsig;  // a level-2 bin's totals, broadcast by its owner (greedy queries)
-  uint32_t bmx, bmn;
-  // variance-budget solver: partial square sums of scans, and broadcasts of square sums
-  Fq sq[kB1 / 64];
-  Fq hq[2];
-  uint64_t sqh[kNT / 64];
-  uint64_t sql[kNT / 64];
-};
-struct Hists {
-  uint32_t* err;       // LDS word collecting kFlagInternal from the wide-arithmetic helpers
-  L1Cache* l1;         // LDS
-  WinCache<kB2>* w2;   // LDS
-  WinCache<kB3>* w3;   // LDS
-  L1Cache* l1g;        // the row's level-1 table in global memory, written by the first solve
-  const Hist1* h1g;    // the row's global copies, filled by the histogram passes
-  WinHist* wg;         // copies of the refinement window
-  const H1Q* h1q;      // variance-budget solver: square sums of the level-1 copies
-  WinQ* wq;            // and of the level-2 window copies
-  VarCtl* vc;          // and its per-row state
-  const CountLine* cc; // keys collected in the row's candidate band
-  int64_t cand_cap;    // the candidate list's capacity (0: no band)
+  uint32_t cnt[kB1];   // level 1: per binade the count, significand sum, maximum key
+  uint64_t sig[kB1];
+  uint32_t mx[kB1];
+  uint32_t pc[kB1];    // count of the keys of the binades up to and including this one
+  double pw[kB1];      // about their sum
+  uint64_t qh[VAR ? kB1 : 1];
+  uint64_t ql[VAR ? kB1 : 1];
+  double pq[VAR ? kB1 : 1];
+  unsigned long long dig[kDigSq];
+  int hi[2][kNT / 64];
+  uint32_t rc[kNT / 64];
+  uint64_t rs[kNT / 64], rh[kNT / 64], rl[kNT / 64];
+  double rw[kNT / 64], rq[kNT / 64];
+  BinOut bin[2], ans;  // the bins b1 and b2 as their owners see them; the answer so far
+  uint64_t word;       // a helper's next request (0: leave)
+  uint32_t cmd;        // whether the chunk at hand was taken by this workgroup
+  uint32_t nbuf, base;  // keys of the chunk at hand that belong in the list, and their place there
+  union {
+    WinLds<VAR> win;
+    uint32_t buf[kPassBuf];
+  };
 };
 
-GS_DI int block_max(SolveLds& s, int v) {
-  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
-  if ((threadIdx.x & 63) == 0) s.ired[threadIdx.x >> 6] = v;
+// Block-wide: the highest (HIGH) or lowest thread with pred; -1 or kNT when there is none. Two
+// result rows used in turn, so one barrier per search.
+template <bool HIGH, class S>
+GS_DI int block_find(S& s, uint32_t& turn, bool pred) {
+  const unsigned long long m = __ballot(pred);
+  const int wv = threadIdx.x >> 6;
+  turn ^= 1u;
+  if ((threadIdx.x & 63) == 0)
+    s.hi[turn][wv] = m ? wv * 64 + (HIGH ? 63 - __builtin_clzll(m) : __builtin_ctzll(m)) : (HIGH ? -1 : kNT);
   __syncthreads();
-  int r = s.ired[0];
-  for (int i = 1; i < kNT / 64; ++i) r = max(r, s.ired[i]);
-  __syncthreads();
-  return r;
-}
-GS_DI int block_min(SolveLds& s, int v) {
-  for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
-  if ((threadIdx.x & 63) == 0) s.ired[threadIdx.x >> 6] = v;
-  __syncthreads();
-  int r = s.ired[0];
-  for (int i = 1; i < kNT / 64; ++i) r = min(r, s.ired[i]);
-  __syncthreads();
-  return r;
-}
-
-// Inclusive suffix sums over the lanes of a wave: lane l receives the sum over lanes l..63.
-GS_DI uint64_t wave_suffix(uint64_t x, int lane) {
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint64_t y = __shfl_down(x, (unsigned)o);
-    if (lane + o < 64) x += y;
-  }
-  return x;
-}
-GS_DI Fx wave_suffix(Fx x, int lane) {
-  for (int o = 1; o < 64; o <<= 1) {
-    Fx y;
+  int r = s.hi[turn][0];
 #pragma unroll
-    for (int i = 0; i < 5; ++i) y.w[i] = __shfl_down(x.w[i], (unsigned)o);
-    if (lane + o < 64) fx_add(x, y);
+  for (int i = 1; i < kNT / 64; ++i) r = HIGH ? max(r, s.hi[turn][i]) : min(r, s.hi[turn][i]);
+  return uni(r);
+}
+
+template <class T>
+GS_DI T wave_incl(T x, int lane) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const T y = __shfl_up(x, o);
+    if (lane >= o) x += y;
   }
   return x;
 }
 
-// Level 1 (one bin per binade): exclusive suffix sums over the 256 binades, exact, into the LDS
-// cache. Threads 0..255 (waves 0..3) own one binade each: a suffix scan inside each wave, then the
-// totals of the waves above.
-GS_DI void l1_build(SolveLds& s, const Hists& H) {
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  uint64_t k = 0, ik = 0;
-  Fx w = fx_zero(), iw = fx_zero();
-  if (t < kB1) {  // whole waves
-    k = H.l1->cnt[t];
-    if (k) w = fx_shifted(H.l1->sig[t], binade_shift(t), H.err);
-    ik = wave_suffix(k, lane);
-    iw = wave_suffix(w, lane);
-    if (lane == 0) {
-      s.sk[wv] = ik;
-      s.sw[wv] = iw;
-    }
-  }
-  __syncthreads();
-  if (t < kB1) {
-    uint64_t K = ik - k;
-    Fx W = fx_sub(iw, w);
-    for (int i = wv + 1; i < kB1 / 64; ++i) {
-      K += s.sk[i];
-      fx_add(W, s.sw[i]);
-    }
-    H.l1->K[t] = K;
-    H.l1->W[t] = W;
-  }
-  __syncthreads();
-}
-
-GS_DI BinInfo l1_info(const Hists& H, int e) {
-  BinInfo i;
-  i.Kab = H.l1->K[e];
-  i.Wab = H.l1->W[e];
-  i.cnt = H.l1->cnt[e];
-  i.Wb = i.cnt ? fx_shifted(H.l1->sig[e], binade_shift(e), H.err) : fx_zero();
-  i.mx = H.l1->mx[e];
-  return i;
-}
-
-// A refinement level inside one binade E: bins b = 0..nbins-1, thread t owns bins
-// [t*per, t*per + per). Within one binade, sums of significands are plain integers.
-struct Lvl {
-  const uint32_t* cnt;
-  const uint64_t* sig;
-  const uint32_t* mx;
-  int nbins, per;
-  int shift;     // binade_shift(E): value = significand * 2^shift (units of 2^-149)
-  uint64_t Kaw;  // count of keys above the window
-  Fx Waw;        // their exact sum
-  uint32_t* err; // as in Hists
-};
-struct Walk {
-  uint64_t exK;  // count above this thread's bins, inside the window
-  uint64_t exS;  // significand sum above this thread's bins, inside the window
-};
-
-GS_DI Lvl lvl2(const Hists& H, uint32_t E, uint64_t Kaw, const Fx& Waw) {
-  Lvl L;
-  L.cnt = H.w2->cnt; L.sig = H.w2->sig; L.mx = H.w2->mx;
-  L.nbins = kB2; L.per = kB2 / kNT; L.shift = binade_shift((int)E); L.Kaw = Kaw; L.Waw = Waw; L.err = H.err;
-  return L;
-}
-GS_DI Lvl lvl3(const Hists& H, uint32_t E, uint64_t Kaw, const Fx& Waw) {
-  Lvl L;
-  L.cnt = H.w3->cnt; L.sig = H.w3->sig; L.mx = H.w3->mx;
-  L.nbins = kB3; L.per = kB3 / kNT; L.shift = binade_shift((int)E); L.Kaw = Kaw; L.Waw = Waw; L.err = H.err;
-  return L;
-}
-
-// Exclusive suffix scan over thread index of (count, significand sum): a suffix scan inside each
-// wave, then the totals of the waves above.
-GS_DI void lvl_scan(const Lvl& L, SolveLds& s, Walk& w) {
-  uint64_t k = 0, sg = 0;
-  const int b0 = threadIdx.x * L.per;
-  for (int j = 0; j < L.per; ++j) {
-    const int b = b0 + j;
-    if (b < L.nbins) {
-      k += (uint64_t)L.cnt[b];
-      sg += (uint64_t)L.sig[b];
-    }
-  }
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const uint64_t ik = wave_suffix(k, lane), is = wave_suffix(sg, lane);
-  if (lane == 0) {
-    s.sk[wv] = ik;
-    s.ss[wv] = is;
-  }
-  __syncthreads();
-  uint64_t ak = 0, as = 0;
-  for (int i = wv + 1; i < kNT / 64; ++i) {
-    ak += s.sk[i];
-    as += s.ss[i];
-  }
-  w.exK = ik - k + ak;
-  w.exS = is - sg + as;
-  __syncthreads();
-}
-
-GS_DI Fx lvl_total(const Lvl& L, uint64_t K, uint64_t S, uint64_t& Kout) {
-  Kout = L.Kaw + K;
-  Fx W = L.Waw;
-  if (S) fx_add(W, fx_shifted(S, L.shift, L.err));
-  return W;
-}
-
-// Aggregates above bin b and the bin's own totals, broadcast to every thread (b uniform).
-GS_DI void lvl_bin_info(const Lvl& L, const Walk& w, int b, SolveLds& s, BinInfo& out) {
-  if ((int)threadIdx.x == b / L.per) {
-    uint64_t K = w.exK, S = w.exS;
-    for (int j = L.per - 1; j >= 0; --j) {
-      const int bb = threadIdx.x * L.per + j;
-      if (bb >= L.nbins) continue;
-      const uint64_t c = (uint64_t)L.cnt[bb];
-      const uint64_t sg = (uint64_t)L.sig[bb];
-      if (bb == b) {
-        s.bi.Wab = lvl_total(L, K, S, s.bi.Kab);
-        s.bi.cnt = c;
-        s.bi.Wb = c ? fx_shifted(sg, L.shift, L.err) : fx_zero();
-        s.bi.mx = L.mx[bb];
-        break;
-      }
-      K += c;
-      S += sg;
-    }
-  }
-  __syncthreads();
-  out = s.bi;
-  __syncthreads();
-}
-
-// The density-budget form of Algorithm 2's criterion at a data value v, with k = #{a > v} and
-// W = exact sum{a > v}: (B - k) * v <= fl(S - W).
-GS_DI bool criterion(double B, const Fx& S, uint64_t k, const Fx& W, uint32_t vkey) {
-  return (B - (double)k) * key_value(vkey) <= fx_to_double(fx_sub(S, W));
-}
-
-// Exact solver step: b1 = highest non-empty bin whose maximum satisfies the criterion, b2 =
-// lowest non-empty bin above b1 (INT_MAX if none).
-GS_DI void l1_exact(const Hists& H, double B, const Fx& S, SolveLds& s, int& b1, int& b2) {
+// The exact sum of every magnitude of the binades below E and of the keys of binade E whose
+// significands add up to `part`, rounded once. Every thread calls it and receives the sum.
+template <class S>
+GS_DI double exact_sum(S& s, int E, uint64_t part) {
   const int t = threadIdx.x;
-  int best = -1, occupied = INT_MAX;
-  if (t < kB1 && H.l1->cnt[t]) {
-    if (criterion(B, S, H.l1->K[t], H.l1->W[t], H.l1->mx[t])) best = t;
+  if (t < kDig) s.dig[t] = 0;
+  __syncthreads();
+  const uint64_t v = t < E && t < kB1 ? s.sig[t] : (t == E ? part : 0ull);
+  if (v) {
+    int at;
+    uint64_t x[3];
+    dig_split(v, binade_shift(t), 255, at, x);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) atomicAdd(&s.dig[at + i], (unsigned long long)x[i]);
   }
-  b1 = block_max(s, best);
-  if (t < kB1 && t > b1 && H.l1->cnt[t]) occupied = t;
-  b2 = block_min(s, occupied);
+  __syncthreads();
+  const double r = uni(dig_round<kDig>(s.dig, -149));
+  __syncthreads();
+  return r;
 }
-// Inside a window each thread walks its bins from the top. A double-precision screen decides the
-// criterion at every bin whose margin exceeds 2^-46 S: T = S - W is approximated by
-// fl(S) - (fl(W above the window) + fl(window sum above)), within 2^-50 S of fl(T), and the
-// left-hand side is computed exactly as the criterion computes it, so the screen and the exact
-// evaluation agree wherever the screen decides; the exact criterion decides the rest (the bins
-// next to the threshold).
-GS_DI void lvl_exact(const Lvl& L, const Walk& w, double B, const Fx& S, SolveLds& s, int& b1, int& b2) {
-  int best = -1;
-  uint64_t K = w.exK, Sg = w.exS;
-  const double Sd = fx_to_double(S), Wawd = fx_to_double(L.Waw);
-  const double tol = 0x1p-46 * Sd + 0x1p-1000;
-#pragma unroll 1
-  for (int j = L.per - 1; j >= 0 && best < 0; --j) {
-    const int b = threadIdx.x * L.per + j;
-    if (b >= L.nbins) continue;
-    const uint64_t c = (uint64_t)L.cnt[b];
-    if (!c) continue;
-    const double lhs = (B - (double)(L.Kaw + K)) * key_value(L.mx[b]);
-    const double Td = Sd - (Wawd + ldexp((double)Sg, L.shift - 149));
-    int pass = lhs <= Td - tol ? 1 : (lhs > Td + tol ? 0 : -1);
-    if (pass < 0) {
-      uint64_t Kt;
-      const Fx W = lvl_total(L, K, Sg, Kt);
-      pass = criterion(B, S, Kt, W, L.mx[b]) ? 1 : 0;
-    }
-    if (pass) best = b;
-    K += c;
-    Sg += (uint64_t)L.sig[b];
+// The same for the squares; `ph`, `pl` as in H1Q.
+template <class S>
+GS_DI double exact_sum_sq(S& s, int E, uint64_t ph, uint64_t pl) {
+  const int t = threadIdx.x;
+  if (t < kDigSq) s.dig[t] = 0;
+  __syncthreads();
+  const bool own = t < E && t < kB1;
+  const uint64_t vh = own ? s.qh[t] : (t == E ? ph : 0ull), vl = own ? s.ql[t] : (t == E ? pl : 0ull);
+  if (vh | vl) {
+    int at;
+    uint64_t x[3];
+    dig_split(vh, 2 * binade_shift(t) + 24, 2 * 255 + 24, at, x);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) atomicAdd(&s.dig[at + i], (unsigned long long)x[i]);
+    dig_split(vl, 2 * binade_shift(t), 2 * 255, at, x);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) atomicAdd(&s.dig[at + i], (unsigned long long)x[i]);
   }
-  b1 = block_max(s, best);
-  int lowest = INT_MAX;
-  for (int j = 0; j < L.per; ++j) {
-    const int b = threadIdx.x * L.per + j;
-    if (b < L.nbins && b > b1 && (uint64_t)L.cnt[b]) {
-      lowest = b;
-      break;
-    }
-  }
-  b2 = block_min(s, lowest);
+  __syncthreads();
+  const double r = uni(dig_round<kDigSq>(s.dig, -298));
+  __syncthreads();
+  return r;
 }
 
-// The solver's control flow runs in every thread of the workgroup on a private copy of the row's
-// control block: every decision depends only on data all threads see (the LDS tables and values
-// broadcast through LDS by the block-wide steps), so the copies stay identical and no barrier is
-// needed between scalar steps. Thread 0 writes the block back at the end.
-GS_DI void sv_finalize(RowCtl& c, double lam, uint32_t tcap) {
-  c.lam = lam;
-  c.tcap = tcap;
-  c.inv_lam = (lam > 0.0 && lam < INFINITY) ? (float)(1.0 / lam) : 0.0f;
-  c.done = 1;
-  c.need = 0;
-}
-
-// Ask for a histogram of binade E (level 2; the pass also counts the keys >= qkey directly, kNone
-// for none) or of keys [base, base + 2048) (level 3; wK and wW count and sum the keys above it).
-// Clears the window's copies (every thread of the workgroup takes part; the kernel boundary orders
-// the stores before the pass).
-GS_DI void sv_request(RowCtl& c, const Hists& H, int level, uint32_t E, uint32_t base, uint32_t qkey, uint64_t wK,
-                      const Fx& wW) {
-  // The greedy solver's query of its last rescale step is answered by the direct count alone (no
-  // later query reads a bin of this window), so that pass builds no bins and only the direct
-  // count's fields are cleared.
-  const bool qonly = level == 2 && c.solver == GSPAR_GREEDY && c.iter + 1 >= c.T;
-  if (qonly) {
-    if (threadIdx.x < kC23) {
-      H.wg[threadIdx.x].qcnt = 0;
-      H.wg[threadIdx.x].qsig = 0;
+// Works on chunk c of a request and puts the results into the row's scratch, if the chunk is this
+// workgroup's: it is taken (with an atomic whose answer is needed only at the end) unless `own`
+// says that it is already. Every thread of the workgroup calls it.
+template <bool VAR>
+GS_DI void pass_chunk(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc, int64_t row, int64_t base,
+                      int64_t len, uint32_t c, const Pass& P, bool own) {
+  const int64_t n = P.from ? (int64_t)ccnt_of(a, row)->v : len;
+  int64_t share;
+  uint32_t chunks;
+  pass_chunks(a, P.from, n, share, chunks);
+  if (c >= chunks) return;
+  uint32_t taken = 0;
+  if (threadIdx.x == 0 && !own) taken = atomicMax(&sc->chunk[c].taken, P.num);
+  const uint32_t lc = threadIdx.x & (kWC - 1);
+  const float* src = P.from ? reinterpret_cast<const float*>(cand_of(a, row)) : a.g + base;
+  const int64_t beg = (int64_t)c * share, end = min(n, beg + share);
+  // the range; for kReqCount the keys of the query key's binade from it on
+  const uint32_t lo = P.kind == kReqCount ? (P.key & 0x7F800000u) : P.key;
+  const uint32_t span = P.shift ? (uint32_t)kWB << P.shift : 32u;
+  auto claim = [&]() {
+    if (threadIdx.x == 0) s.cmd = own || taken < P.num ? 1u : 0u;
+    __syncthreads();
+    return uni(s.cmd) != 0;
+  };
+  if (P.kind == kReqWindow) {
+    for (int i = threadIdx.x; i < kWB * kWC; i += kNT) {
+      s.win.pk[i] = 0;
+      s.win.mx[i] = 0;
+      if constexpr (VAR) s.win.s2[i] = 0;
     }
-  } else {
-    uint4 z;
-    z.x = z.y = z.z = z.w = 0u;
-    uint4* w = reinterpret_cast<uint4*>(H.wg);
-    for (int i = threadIdx.x; i < (int)(kC23 * sizeof(WinHist) / 16); i += kNT) w[i] = z;
-  }
-  c.qonly = qonly ? 1u : 0u;
-  c.need = level;
-  if (level == 2) {
-    c.l2exp = E;
-    c.l3base = kNone;
-    c.qkey = qkey;
-  } else {
-    c.l3base = base;
-    c.wK = wK;
-    c.wW = wW;
-  }
-  // a window inside the candidate band (whole binades) holds only collected keys: its pass reads
-  // the candidates instead of the row
-  const uint32_t e = level == 2 ? E : (base >> 23);
-  c.src = (c.band_hi > c.band_lo && (e << 23) >= c.band_lo && ((e + 1) << 23) <= c.band_hi) ? 1u : 0u;
-}
-
-// Count and significand sum of the level-2 window's keys in bins above sb, summed straight from the
-// global copies (thread t owns bins [t * per, t * per + per)); bin sb's own totals, maximum and
-// minimum go to s.bcnt, s.bsig, s.bmx, s.bmn.
-GS_DI void w2_above(SolveLds& s, const Hists& H, int sb, uint64_t& ka, uint64_t& sa) {
-  constexpr int per = kB2 / kNT;
-  const int b0 = threadIdx.x * per;
-  uint64_t c[per], g[per];
+    __syncthreads();
+    const uint32_t omask = (1u << P.shift) - 1u;
+    stream_groups<4, kNT>(src, beg, end, [&](int64_t, const float v[4], uint32_t) {
 #pragma unroll
-  for (int j = 0; j < per; ++j) {
-    c[j] = 0;
-    g[j] = 0;
-#pragma unroll
-    for (int q = 0; q < kC23; ++q) {
-      c[j] += H.wg[q].cnt[b0 + j];
-      g[j] += H.wg[q].sig[b0 + j];
-    }
-  }
-  uint64_t k = 0, sg = 0;
-#pragma unroll
-  for (int j = 0; j < per; ++j) {
-    if (b0 + j > sb) {
-      k += c[j];
-      sg += g[j];
-    } else if (b0 + j == sb) {
-      uint32_t mx = 0, mc = 0;
-      for (int q = 0; q < kC23; ++q) {
-        mx = max(mx, H.wg[q].mx[sb]);
-        mc = max(mc, H.wg[q].mnc[sb]);
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t key = key_of(v[k]), rel = key - lo;
+        if (key != 0 && rel < span) {
+          const uint32_t i = (rel >> P.shift) * kWC + lc, r = rel & omask;
+          atomicAdd(&s.win.pk[i], (1ull << 44) | (unsigned long long)r);
+          if constexpr (VAR) atomicAdd(&s.win.s2[i], (unsigned long long)r * r);
+          atomicMax(&s.win.mx[i], rel);
+        }
       }
-      s.bcnt = c[j];
-      s.bsig = g[j];
-      s.bmx = mx;
-      s.bmn = ~mc;
+    });
+    if (!claim()) return;
+    const int b = threadIdx.x;
+    uint64_t cnt = 0, sr = 0, s2 = 0;
+    uint32_t mx = 0;
+#pragma unroll
+    for (int j = 0; j < kWC; ++j) {
+      const uint64_t p = s.win.pk[b * kWC + j];
+      cnt += p >> 44;
+      sr += p & ((1ull << 44) - 1);
+      mx = max(mx, s.win.mx[b * kWC + j]);
+      if constexpr (VAR) s2 += s.win.s2[b * kWC + j];
     }
+    if (cnt) {
+      WinBins* w = &sc->win[c % kWC];
+      atomicAdd(&w->cnt[b], (uint32_t)cnt);
+      if (sr) atomicAdd((unsigned long long*)&w->sr[b], (unsigned long long)sr);
+      if constexpr (VAR) {
+        if (s2) atomicAdd((unsigned long long*)&w->s2[b], (unsigned long long)s2);
+      }
+      atomicMax(&w->mx[b], mx);
+    }
+  } else if (P.kind == kReqList) {
+    if (threadIdx.x == 0) s.nbuf = 0;
+    __syncthreads();
+    stream_groups<4, kNT>(src, beg, end, [&](int64_t, const float v[4], uint32_t) {
+      // the wave's keys of this group: one reservation for all of them, in LDS while there is room
+      uint32_t hit = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) hit |= (uint32_t)(key_of(v[k]) != 0 && key_of(v[k]) - lo < span) << k;
+      if (!__ballot(hit != 0)) return;
+      uint32_t tot;
+      uint32_t at = wave_prefix_bits<3>((uint32_t)__popc(hit), tot), b = 0;
+      const int lane = threadIdx.x & 63;
+      if (lane == 0) b = atomicAdd(&s.nbuf, tot);
+      b = (uint32_t)__shfl((int)b, 0);
+      at += b;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if ((hit >> k) & 1) {
+          if (at < (uint32_t)kPassBuf) s.buf[at] = key_of(v[k]);
+          ++at;
+        }
+      }
+    });
+    if (!claim()) return;
+    const uint32_t m = s.nbuf;
+    if (threadIdx.x == 0 && m) s.base = atomicAdd(&ctl->lcount, m);
+    __syncthreads();
+    const uint32_t to = s.base;
+    if (m <= (uint32_t)kPassBuf) {
+      for (uint32_t i = threadIdx.x; i < m; i += kNT)
+        if (to + i < (uint32_t)kListMax) st_agent(&sc->list[to + i], s.buf[i]);
+    } else {
+      // more than the buffer holds: read the chunk again, straight to the list
+      if (threadIdx.x == 0) s.nbuf = to;
+      __syncthreads();
+      stream_groups<4, kNT>(src, beg, end, [&](int64_t, const float v[4], uint32_t) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const uint32_t key = key_of(v[k]);
+          if (key != 0 && key - lo < span) {
+            const uint32_t i = atomicAdd(&s.nbuf, 1u);
+            if (i < (uint32_t)kListMax) st_agent(&sc->list[i], key);
+          }
+        }
+      });
+    }
+  } else {
+    uint32_t qc = 0;
+    uint64_t qs = 0;
+    stream_groups<4, kNT>(src, beg, end, [&](int64_t, const float v[4], uint32_t) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t key = key_of(v[k]);
+        if (key >= P.key && key - lo < span) {
+          ++qc;
+          qs += key_sig(key);
+        }
+      }
+    });
+    for (int o = 32; o > 0; o >>= 1) {
+      qc += __shfl_xor(qc, o);
+      qs += __shfl_xor(qs, o);
+    }
+    if ((threadIdx.x & 63) == 0) {
+      s.rc[threadIdx.x >> 6] = qc;
+      s.rs[threadIdx.x >> 6] = qs;
+    }
+    if (!claim()) return;
+    if (threadIdx.x == 0) {
+      for (int i = 1; i < kNT / 64; ++i) {
+        qc += s.rc[i];
+        qs += s.rs[i];
+      }
+      st_agent(&sc->chunk[c].qcnt, qc);
+      st_agent(&sc->chunk[c].qsig, qs);
+    }
+  }
+  wait_own();
+  __syncthreads();  // every wave's results have landed, and the LDS may be reused
+  if (threadIdx.x == 0) st_agent(&sc->chunk[c].done, P.num);
+}
+
+// The helper of chunk c: works on it in each of the row's requests until the row is solved.
+template <bool VAR>
+GS_DI void help_row(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc, int64_t row, int64_t base,
+                    int64_t len, uint32_t c) {
+  uint32_t seen = 0;  // thread 0: the last request looked at
+  while (true) {
+    if (threadIdx.x == 0) {
+      uint64_t word = 0;
+      for (int polls = 0; polls < kHelperPolls; ++polls) {
+        word = ld_agent(&ctl->req);
+        const uint32_t num = (uint32_t)(word >> 32) & 0xFFu;
+        if (num != seen) {
+          seen = num;
+          break;
+        }
+        word = 0;
+        __builtin_amdgcn_s_sleep(8);
+      }
+      s.word = word;
+    }
+    __syncthreads();
+    const Pass P = pass_of(uni(s.word));
+    if (P.num == 0 || P.num == kReqDone) return;
+    pass_chunk<VAR>(a, s, ctl, sc, row, base, len, c, P, false);
+    __syncthreads();
+  }
+}
+
+// The leader's running state of a row.
+struct Lead {
+  uint32_t req = 0;      // requests made
+  uint32_t turn = 0;
+  bool banded = false;   // the candidate band is complete
+  uint32_t blo = 0, bhi = 0;
+  uint64_t cand_n = 0;
+  uint32_t from = 0;     // source of the last request
+  uint32_t chunks = 0;   // and its chunks
+  uint32_t llo = 0, lspan = 0, ln = 0;  // the listed range's first key, whether there is one, its number of keys
+  uint32_t kr[kKeyRegs];  // this thread's first listed keys (0: none)
+};
+
+// Makes a request, works on it and waits until all of it is done. `key`: the range's first key, for
+// kReqCount the query key; `n`: the range's number of keys. The range lies in one binade.
+template <bool VAR>
+GS_DI void request(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc, int64_t row, int64_t base, int64_t len,
+                   Lead& L, uint32_t kind, uint32_t key, uint32_t shift, uint32_t n) {
+  const uint32_t e = key >> 23;
+  L.from = L.banded && (e << 23) >= L.blo && ((e + 1) << 23) <= L.bhi ? 1u : 0u;
+  ++L.req;
+  const Pass P{key, L.req, kind, L.from, shift};
+  int64_t share;
+  uint32_t chunks;
+  pass_chunks(a, P.from, P.from ? (int64_t)L.cand_n : len, share, chunks);
+  L.chunks = chunks;
+  if (L.req == 1)
+    for (uint32_t c = threadIdx.x; c < (uint32_t)a.nb && c < (uint32_t)kMaxChunks; c += kNT) {
+      st_agent(&sc->chunk[c].taken, 0u);
+      st_agent(&sc->chunk[c].done, 0u);
+    }
+  if (kind == kReqWindow) {
+    uint64_t* w = reinterpret_cast<uint64_t*>(sc->win);
+    for (int i = threadIdx.x; i < (int)(sizeof(sc->win) / 8); i += kNT) st_agent(&w[i], (uint64_t)0);
+  }
+  // (the list's counter starts at zero, and a row makes at most one list for each binade)
+  if (kind == kReqList && L.lspan && threadIdx.x == 0) st_agent(&ctl->lcount, 0u);
+  wait_own();
+  __syncthreads();  // the scratch is clear: announce the request
+  if (threadIdx.x == 0) st_agent(&ctl->req, pass_word(P));
+  pass_chunk<VAR>(a, s, ctl, sc, row, base, len, 0, P, true);
+  // chunks that no helper has taken by now, then those that are still being worked on
+  for (uint32_t c0 = 0; c0 < chunks; c0 += kNT) {
+    const uint32_t c = c0 + threadIdx.x;
+    while (true) {
+      const int f = block_find<false>(s, L.turn, c > 0 && c < chunks && ld_agent(&sc->chunk[c].taken) < P.num);
+      if (f == kNT) break;
+      pass_chunk<VAR>(a, s, ctl, sc, row, base, len, c0 + (uint32_t)f, P, false);
+      __syncthreads();
+    }
+    while (block_find<false>(s, L.turn, c < chunks && ld_agent(&sc->chunk[c].done) != P.num) != kNT)
+      __builtin_amdgcn_s_sleep(1);
+  }
+  if (kind == kReqList) {
+    L.llo = key;
+    L.lspan = 1;
+    L.ln = n;
+#pragma unroll
+    for (int j = 0; j < kKeyRegs; ++j) {
+      const uint32_t i = threadIdx.x + j * kNT;
+      L.kr[j] = i < n ? ld_agent(&sc->list[i]) : 0u;
+    }
+  }
+}
+
+// Visits this thread's listed keys.
+template <class F>
+GS_DI void each_listed(const RowScratch* sc, const Lead& L, F&& f) {
+#pragma unroll
+  for (int j = 0; j < kKeyRegs; ++j)
+    if (L.kr[j]) f(L.kr[j]);
+  for (uint32_t i = threadIdx.x + kKeyRegs * kNT; i < L.ln; i += kNT) f(ld_agent(&sc->list[i]));
+}
+
+// Count and significand sum of the keys >= t of t's binade.
+GS_DI void count_above(const Args& a, SolveLds<false>& s, RowCtl* ctl, RowScratch* sc, int64_t row, int64_t base,
+                       int64_t len, Lead& L, uint32_t t, uint64_t& qc, uint64_t& qs) {
+  const uint32_t lo = (t >> 23) << 23, n = s.cnt[t >> 23];
+  if (L.lspan == 0 || L.llo != lo) {
+    request<false>(a, s, ctl, sc, row, base, len, L, n > kListCap ? kReqCount : kReqList, n > kListCap ? t : lo, 14, n);
+  }
+  uint32_t c = 0;
+  uint64_t g = 0;
+  if (n > kListCap) {
+    for (uint32_t i = threadIdx.x; i < L.chunks; i += kNT) {
+      c += ld_agent(&sc->chunk[i].qcnt);
+      g += ld_agent(&sc->chunk[i].qsig);
+    }
+  } else {
+    each_listed(sc, L, [&](uint32_t key) {
+      if (key >= t) {
+        ++c;
+        g += key_sig(key);
+      }
+    });
   }
   for (int o = 32; o > 0; o >>= 1) {
-    k += __shfl_xor(k, o);
-    sg += __shfl_xor(sg, o);
+    c += __shfl_xor(c, o);
+    g += __shfl_xor(g, o);
   }
+  __syncthreads();
   if ((threadIdx.x & 63) == 0) {
-    s.sk[threadIdx.x >> 6] = k;
-    s.ss[threadIdx.x >> 6] = sg;
+    s.rc[threadIdx.x >> 6] = c;
+    s.rs[threadIdx.x >> 6] = g;
   }
   __syncthreads();
-  ka = 0;
-  sa = 0;
+  qc = 0;
+  qs = 0;
   for (int i = 0; i < kNT / 64; ++i) {
-    ka += s.sk[i];
-    sa += s.ss[i];
+    qc += s.rc[i];
+    qs += s.rs[i];
   }
-  __syncthreads();
 }
 
-// Greedy query: count K and exact sum W of the keys >= t. Resolved from level 1 when t's binade
-// is empty, lies below t or starts at t; else from the level-2 pass of that binade, which counted
-// the keys >= its qkey directly (qcnt, qsig), or whose bin holding t has all its keys on one side
-// of t (bin minimum and maximum). Otherwise a level-2 pass of t's binade counting the keys >= t is
-// requested. Returns 0 when resolved, 2 after a request.
-GS_DI int sv_query(SolveLds& s, RowCtl& c, const Hists& H, uint64_t qcnt, uint64_t qsig, uint32_t t, uint64_t& K,
-                   Fx& W) {
-  const int e = (int)(t >> 23);
-  const BinInfo i1 = l1_info(H, e);
-  if ((t & 0x7FFFFFu) == 0) {
-    K = i1.Kab + i1.cnt; W = i1.Wab; fx_add(W, i1.Wb);
-    return 0;
+// Algorithm 2's criterion at a data value v, from K = #{a > v} and the rounded exact sums T1 (and,
+// variance budget, T2) of the magnitudes up to v and of their squares. Density budget:
+// (B - K) v <= T1; variance budget: v T1 <= eps A2 + T2 with every operation rounded on its own
+// (the pragma keeps the compiler from fusing the product and the sum).
+template <bool VAR>
+GS_DI bool criterion(double B, double A2, uint64_t K, uint32_t vkey, double T1, double T2, double& lhs, double& rhs) {
+#pragma clang fp contract(off)
+  if constexpr (VAR) {
+    lhs = key_value(vkey) * T1;
+    const double eA = B * A2;
+    rhs = eA + T2;
+  } else {
+    lhs = (B - (double)K) * key_value(vkey);
+    rhs = T1;
   }
-  if (i1.cnt == 0 || i1.mx < t) {
-    K = i1.Kab; W = i1.Wab;
-    return 0;
-  }
-  if (c.l2exp == (uint32_t)e) {
-    uint64_t kq = 0, sq = 0;
-    bool ok = false;
-    if (c.qkey == t) {
-      kq = qcnt;
-      sq = qsig;
-      ok = true;
-    } else {
-      uint64_t ka, sa;
-      w2_above(s, H, (int)((t >> 11) & (kB2 - 1)), ka, sa);
-      if (s.bcnt == 0 || s.bmx < t) {
-        kq = ka; sq = sa; ok = true;
-      } else if (s.bmn >= t) {
-        kq = ka + s.bcnt; sq = sa + s.bsig; ok = true;
-      }
-    }
-    if (ok) {
-      K = i1.Kab + kq;
-      W = i1.Wab;
-      if (sq) fx_add(W, fx_shifted(sq, binade_shift(e), H.err));
-      return 0;
-    }
-  }
-  sv_request(c, H, 2, (uint32_t)e, 0, t, 0, fx_zero());
-  return 2;
-}
-
-// Algorithm 3 in scale form: lambda_{j+1} = (B - k_j) / U_j, stop when it does not grow.
-GS_DI void sv_greedy(SolveLds& s, RowCtl& c, const Hists& H, uint64_t qcnt, uint64_t qsig) {
-  while (c.iter < c.T) {
-    const double lam = c.lam;
-    uint64_t K;
-    Fx W;
-    if (sv_query(s, c, H, qcnt, qsig, cap_key(lam), K, W)) return;
-    const double U = fx_to_double(fx_sub(c.S, W));
-    if (U == 0.0) break;
-    const double ln = (c.B - (double)K) / U;
-    if (!(ln > lam)) break;
-    c.lam = ln;
-    c.iter += 1;
-  }
-  sv_finalize(c, c.lam, cap_key(c.lam));
+  return lhs <= rhs;
 }
 
 // The capped set of Proposition 1 is {p_i = 1}: the magnitudes above the criterion's value v
@@ -1214,571 +1127,362 @@ GS_DI uint32_t capped_threshold(double lam, uint32_t tcap) {
   return t < tcap ? t : tcap;
 }
 
-GS_DI void sv_exact_finish(RowCtl& c, uint64_t K, const Fx& W, uint32_t tcap) {
-  const double T1 = fx_to_double(fx_sub(c.S, W));
-  const double lam = (c.B - (double)K) / T1;
-  sv_finalize(c, lam, capped_threshold(lam, tcap));
-}
-
-// The exact solver descends levels: at each one it finds the highest bin whose maximum passes
-// the criterion (b1) and the lowest occupied bin above it (b2); the answer is b1's maximum
-// unless b2 holds two or more values that could still pass, in which case b2 is refined.
-GS_DI void sv_exact(SolveLds& s, RowCtl& c, const Hists& H) {
-  const int level = c.stage;
-  int b1, b2;
-  BinInfo c1, c2;  // the bins b1 and b2 at this level
-  uint32_t E = 0;
-  if (level == 1) {
-    l1_exact(H, c.B, c.S, s, b1, b2);
-    if (b1 >= 0) c1 = l1_info(H, b1);
-    if (b2 != INT_MAX) c2 = l1_info(H, b2);
-  } else {
-    E = c.l2exp;
-    Lvl L;
-    if (level == 2) {
-      const BinInfo iE = l1_info(H, (int)E);
-      L = lvl2(H, E, iE.Kab, iE.Wab);
-    } else {
-      L = lvl3(H, E, c.wK, c.wW);
-    }
-    Walk w;
-    lvl_scan(L, s, w);
-    lvl_exact(L, w, c.B, c.S, s, b1, b2);
-    if (b1 >= 0) lvl_bin_info(L, w, b1, s, c1);
-    if (b2 != INT_MAX) lvl_bin_info(L, w, b2, s, c2);
-  }
-  // refine b2 when it holds two or more values, of which a smaller one may pass; also when no
-  // bin's maximum passes at this level (b1 < 0): the lowest occupied bin may still hold a passing
-  // value below its maximum (when the answer lies in the row's lowest binade, or in a window's
-  // lowest bin), and the candidate from a level up, if any, stays the fallback
-  if (b2 != INT_MAX && level < 3 && c2.cnt >= 2) {
-    if (b1 >= 0) {
-      c.fbValid = 1;
-      c.fbK = c1.Kab;
-      c.fbW = c1.Wab;
-      c.fbTcap = c1.mx + 1;
-    }
-    c.stage = level + 1;
-    if (level == 1) sv_request(c, H, 2, (uint32_t)b2, 0, kNone, 0, fx_zero());
-    else sv_request(c, H, 3, 0, (E << 23) | ((uint32_t)b2 << 11), kNone, c2.Kab, c2.Wab);
-    return;
-  }
-  if (b1 >= 0) {
-    sv_exact_finish(c, c1.Kab, c1.Wab, c1.mx + 1);
-  } else if (c.fbValid) {
-    // no value in this window passes: the answer is the candidate found one level up
-    sv_exact_finish(c, c.fbK, c.fbW, c.fbTcap);
-  } else {
-    c.flags |= kFlagInternal;
-    sv_finalize(c, NAN, kKeyInf);
-  }
-}
-
-// ------------------------------------------------------------------------------------------
-// Variance-budget exact solver: Algorithm 2 as printed (budget (1 + eps) sum a^2 on the variance,
-// eqs. 6-7). With the magnitudes sorted decreasingly, k is the smallest index with
-// a_(k+1) T1_k <= eps A + T2_k, where A = sum a^2 and T1_k, T2_k are the sum and the sum of
-// squares of the magnitudes after the first k; lambda = T1_k / (eps A + T2_k) and the capped set
-// is {a > a_(k+1)}. Candidates are distinct values; moving down to the next smaller value never
-// turns the criterion from true to false, so the same three-level search as the density form
-// applies, with the square sums of the bins carried alongside the counts and sums.
-// ------------------------------------------------------------------------------------------
-GS_DI Fq wave_suffix(Fq x, int lane) {
-  for (int o = 1; o < 64; o <<= 1) {
-    Fq y;
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) y.w[i] = __shfl_down(x.w[i], (unsigned)o);
-    if (lane + o < 64) fq_add(x, y);
-  }
-  return x;
-}
-
-// The criterion at a data value v, with W and H the exact sum and square sum of the magnitudes
-// above v: v * fl(S - W) <= fl(eps * fl(A2)) + fl(A2 - H), each operation rounded on its own (the
-// pragma keeps the compiler from fusing the product and the sum). T1 and the right-hand side are
-// returned for lambda.
-GS_DI bool v_criterion(double eps, const Fx& S, const Fq& A2, const Fx& W, const Fq& H, uint32_t vkey, double& T1,
-                       double& rhs) {
-#pragma clang fp contract(off)
-  T1 = fx_to_double(fx_sub(S, W));
-  const double T2 = fq_to_double(fq_sub(A2, H));
-  const double eA = eps * fq_to_double(A2);
-  rhs = eA + T2;
-  return key_value(vkey) * T1 <= rhs;
-}
-
-// A double-precision screen of the criterion from approximate sums (each within a few units of
-// rounding of the exact value, all terms non-negative): 1 or 0 when the margin exceeds 2^-44 of
-// v*S + (1 + eps)*A2, far above every rounding of either evaluation, so the exact criterion
-// decides the same way; -1 when the exact evaluation must decide.
-GS_DI int v_screen(double eps, double Sd, double A2d, double Wd, double Hd, double v) {
-#pragma clang fp contract(off)
-  const double lhs = v * (Sd - Wd);
-  const double rhs = eps * A2d + (A2d - Hd);
-  const double tol = 0x1p-44 * (v * Sd + (1.0 + eps) * A2d);
-  if (lhs <= rhs - tol) return 1;
-  if (lhs >= rhs + tol) return 0;
-  return -1;
-}
-
-GS_DI void v_finish(RowCtl& c, const Fq& A2, const Fx& W, const Fq& H, uint32_t tcap) {
-  double T1, rhs;
-  v_criterion(c.B, c.S, A2, W, H, 1u, T1, rhs);
-  const double lam = T1 / rhs;
-  sv_finalize(c, lam, capped_threshold(lam, tcap));
-}
-
-// A bin of a level: keys above it (count, sum, square sum), its own count and maximum key.
-struct VInfo {
-  uint64_t K;
-  Fx W;
-  Fq H;
-  uint64_t cnt;
-  uint32_t mx;
-};
-
-// Asks for a refinement window like sv_request, clears the window's square sums for level 2 and
-// keeps the square sum above the window.
-GS_DI void v_request(RowCtl& c, const Hists& H, int level, uint32_t E, uint32_t base, uint64_t wK, const Fx& wW,
-                     const Fq& wH) {
-  sv_request(c, H, level, E, base, kNone, wK, wW);
-  if (level == 2) {
-    uint4 z;
-    z.x = z.y = z.z = z.w = 0u;
-    uint4* w = reinterpret_cast<uint4*>(H.wq);
-    for (int i = threadIdx.x; i < (int)(kC23 * sizeof(WinQ) / 16); i += kNT) w[i] = z;
-  }
-  if (threadIdx.x == 0) H.vc->wH = wH;
-}
-
-// Level 1 (first solve): square sums of the binades from the global copies, the square sum above
-// each binade (exclusive suffix over binades), the total A2, then b1 = highest occupied binade whose
-// maximum passes the criterion and b2 = lowest occupied binade above b1.
-GS_DI void v_level1(SolveLds& s, const RowCtl& c, const Hists& H, Fq& A2, int& b1, int& b2, VInfo& i1, VInfo& i2) {
+// The exact and the variance-budget solver (see above): lambda and the capped threshold of a row
+// whose level-1 table is in LDS. Returns kFlagInternal when nothing passes (density budget: a broken
+// invariant, the criterion holds at the smallest magnitude).
+template <bool VAR>
+GS_DI uint32_t solve_levels(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc, int64_t row, int64_t base,
+                            int64_t len, Lead& L, double B, uint64_t nnz, double A2, double& lam, uint32_t& tcap) {
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  Fq q = fq_zero(), iq = fq_zero();
-  if (t < kB1) {  // whole waves
-    uint64_t qh = 0, ql = 0;
-    for (int k = 0; k < kC1; ++k) {
-      qh += H.h1q[k].qh[t];
-      ql += H.h1q[k].ql[t];
-    }
-    if (H.l1->cnt[t]) q = fq_squares(qh, ql, binade_shift(t), H.err);
-    iq = wave_suffix(q, lane);
-    if (lane == 0) s.sq[wv] = iq;
-  }
-  __syncthreads();
-  Fq above = fq_zero();
-  if (t < kB1) {
-    above = fq_sub(iq, q);
-    for (int i = wv + 1; i < kB1 / 64; ++i) fq_add(above, s.sq[i]);
-    if (t == 0) {
-      Fq tot = above;
-      fq_add(tot, q);
-      s.hq[0] = tot;
-    }
-  }
-  __syncthreads();
-  A2 = s.hq[0];
-  int best = -1, occupied = INT_MAX;
-  if (t < kB1 && H.l1->cnt[t]) {
-    double T1, rhs;
-    if (v_criterion(c.B, c.S, A2, H.l1->W[t], above, H.l1->mx[t], T1, rhs)) best = t;
-  }
-  b1 = block_max(s, best);
-  if (t < kB1 && t > b1 && H.l1->cnt[t]) occupied = t;
-  b2 = block_min(s, occupied);
-  if (t == b1) s.hq[0] = above;
-  if (t == b2) s.hq[1] = above;
-  __syncthreads();
-  if (b1 >= 0) {
-    i1.K = H.l1->K[b1];
-    i1.W = H.l1->W[b1];
-    i1.H = s.hq[0];
-    i1.cnt = H.l1->cnt[b1];
-    i1.mx = H.l1->mx[b1];
-  }
-  if (b2 != INT_MAX) {
-    i2.K = H.l1->K[b2];
-    i2.W = H.l1->W[b2];
-    i2.H = s.hq[1];
-    i2.cnt = H.l1->cnt[b2];
-    i2.mx = H.l1->mx[b2];
-  }
-  __syncthreads();
-}
-
-// Level 2 (a binade's 4096 bins, square sums from the global window copies) or level 3 (2048
-// single keys from `base`, whose square sums follow from the counts): b1 and b2 as at level 1, the
-// keys above the window given by (L.Kaw, L.Waw, Haw).
-// The square-sum parts (see fq_squares) of bin b of a level: level 2 from the global window copies,
-// level 3 (one key per bin) the count times the key's squared significand.
-GS_DI void v_bin_squares(const Hists& H, const Lvl& L, bool level2, uint32_t base, int b, uint64_t& qh,
-                         uint64_t& ql) {
-  if (level2) {
-    qh = 0;
-    ql = 0;
-#pragma unroll
-    for (int k = 0; k < kC23; ++k) {
-      qh += H.wq[k].qh[b];
-      ql += H.wq[k].ql[b];
-    }
-  } else {
-    const uint64_t m = key_sig(base + (uint32_t)b), m2 = m * m, cnt = (uint64_t)L.cnt[b];
-    qh = cnt * (m2 >> 24);
-    ql = cnt * (m2 & 0xFFFFFFu);
-  }
-}
-
-// Level 2 (a binade's 4096 bins, square sums from the global window copies) or level 3 (2048
-// single keys from `base`): b1 and b2 as at level 1, the keys above the window given by (L.Kaw,
-// L.Waw, Haw). The thread's bins are walked again where needed instead of being held in registers.
-GS_DI void v_level(SolveLds& s, const RowCtl& c, const Hists& H, const Lvl& L, bool level2, uint32_t base,
-                   const Fq& A2, const Fq& Haw, int& b1, int& b2, VInfo& i1, VInfo& i2) {
-  const int per = L.per, b0 = threadIdx.x * per;
-  uint64_t tk = 0, ts = 0, tqh = 0, tql = 0;
-  for (int j = 0; j < per; ++j) {
-    const int b = b0 + j;
-    if (b >= L.nbins) break;
-    uint64_t qh, ql;
-    v_bin_squares(H, L, level2, base, b, qh, ql);
-    tk += (uint64_t)L.cnt[b];
-    ts += (uint64_t)L.sig[b];
-    tqh += qh;
-    tql += ql;
-  }
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const uint64_t ik = wave_suffix(tk, lane), is = wave_suffix(ts, lane);
-  const uint64_t iqh = wave_suffix(tqh, lane), iql = wave_suffix(tql, lane);
-  if (lane == 0) {
-    s.sk[wv] = ik;
-    s.ss[wv] = is;
-    s.sqh[wv] = iqh;
-    s.sql[wv] = iql;
-  }
-  __syncthreads();
-  uint64_t eK = ik - tk, eS = is - ts, eQH = iqh - tqh, eQL = iql - tql;  // above this thread's bins
-  for (int i = wv + 1; i < kNT / 64; ++i) {
-    eK += s.sk[i];
-    eS += s.ss[i];
-    eQH += s.sqh[i];
-    eQL += s.sql[i];
-  }
-  __syncthreads();
-  // this thread's bins from the top: the first (highest) passing one (a loop that is not unrolled:
-  // the criterion's wide arithmetic is long, and one copy of it keeps the code in the instruction
-  // cache). The double-precision screen decides all but the bins next to the threshold.
-  int best = -1;
-  {
-    const double Sd = fx_to_double(c.S), A2d = fq_to_double(A2);
-    const double Wawd = fx_to_double(L.Waw), Hawd = fq_to_double(Haw);
-    uint64_t Sg = eS, QH = eQH, QL = eQL;
-#pragma unroll 1
-    for (int j = per - 1; j >= 0; --j) {
-      const int b = b0 + j;
-      if (b >= L.nbins) continue;
-      const uint64_t cnt = (uint64_t)L.cnt[b];
-      uint64_t qh, ql;
-      v_bin_squares(H, L, level2, base, b, qh, ql);
-      if (cnt) {
-        const double Wd = Wawd + ldexp((double)Sg, L.shift - 149);
-        const double Hd = Hawd + ldexp((double)QH, 2 * L.shift - 298 + 24) + ldexp((double)QL, 2 * L.shift - 298);
-        int pass = v_screen(c.B, Sd, A2d, Wd, Hd, key_value(L.mx[b]));
-        if (pass < 0) {
-          Fx W = L.Waw;
-          if (Sg) fx_add(W, fx_shifted(Sg, L.shift, L.err));
-          Fq Hq = Haw;
-          fq_add(Hq, fq_squares(QH, QL, L.shift, L.err));
-          double T1, rhs;
-          pass = v_criterion(c.B, c.S, A2, W, Hq, L.mx[b], T1, rhs) ? 1 : 0;
-        }
-        if (pass) {
-          best = b;
-          break;
+  // the level: bins of 2^shift keys from `lo` (level 1: thread t's bin is binade t), with `below` keys
+  // of the row and the sums (bsig; bh, bl) of binade E below it
+  int E = -1;
+  uint32_t lo = 0, shift = 23, below = 0;
+  uint64_t bsig = 0, bh = 0, bl = 0;
+  bool have = false;  // an answer, unless a lower level gives a better one
+  bool rounded = false;  // its sums T1, T2 and the criterion's right-hand side are rounded
+  int aE = 0;
+  double T1 = 0.0, T2 = 0.0, rhs = 0.0;
+  while (true) {
+    // this thread's bin: count, significand sum, largest key, square sums
+    uint32_t cnt = 0, mx = 0;
+    uint64_t sig = 0, qh = 0, ql = 0;
+    if (E < 0) {
+      if (t < kB1) {
+        cnt = s.cnt[t];
+        sig = s.sig[t];
+        mx = s.mx[t];
+        if constexpr (VAR) {
+          qh = s.qh[t];
+          ql = s.ql[t];
         }
       }
-      Sg += (uint64_t)L.sig[b];
-      QH += qh;
-      QL += ql;
+    } else {
+      uint64_t sr = 0, s2 = 0;
+      if (L.lspan) {
+        __syncthreads();
+        for (int i = t; i < kWB * kWC; i += kNT) {
+          s.win.pk[i] = 0;
+          s.win.mx[i] = 0;
+          if constexpr (VAR) s.win.s2[i] = 0;
+        }
+        __syncthreads();
+        const uint32_t lc = t & (kWC - 1), span = shift ? (uint32_t)kWB << shift : 32u, omask = (1u << shift) - 1u;
+        each_listed(sc, L, [&](uint32_t key) {
+          const uint32_t rel = key - lo;
+          if (rel < span) {
+            const uint32_t i = (rel >> shift) * kWC + lc, r = rel & omask;
+            atomicAdd(&s.win.pk[i], (1ull << 44) | (unsigned long long)r);
+            if constexpr (VAR) atomicAdd(&s.win.s2[i], (unsigned long long)r * r);
+            atomicMax(&s.win.mx[i], rel);
+          }
+        });
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kWC; ++j) {
+          const uint64_t p = s.win.pk[t * kWC + j];
+          cnt += (uint32_t)(p >> 44);
+          sr += p & ((1ull << 44) - 1);
+          mx = max(mx, s.win.mx[t * kWC + j]);
+          if constexpr (VAR) s2 += s.win.s2[t * kWC + j];
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < kWC; ++j) {
+          cnt += ld_agent(&sc->win[j].cnt[t]);
+          sr += ld_agent(&sc->win[j].sr[t]);
+          mx = max(mx, ld_agent(&sc->win[j].mx[t]));
+          if constexpr (VAR) s2 += ld_agent(&sc->win[j].s2[t]);
+        }
+      }
+      mx += lo;
+      // the bin's keys are m0 + offset as significands
+      const uint64_t m0 = key_sig(lo) + ((uint64_t)t << shift);
+      sig = cnt * m0 + sr;
+      if constexpr (VAR) {
+        // sum (m0 + r)^2 = cnt m0^2 + 2 m0 sum r + sum r^2, below 2^79
+        const unsigned __int128 q = (unsigned __int128)(m0 * m0) * cnt + (unsigned __int128)(2 * m0) * sr + s2;
+        qh = (uint64_t)(q >> 24);
+        ql = (uint64_t)q & 0xFFFFFFu;
+      }
     }
-  }
-  b1 = block_max(s, best);
-  int lowest = INT_MAX;
-  for (int j = 0; j < per; ++j) {
-    const int b = b0 + j;
-    if (b < L.nbins && b > b1 && (uint64_t)L.cnt[b]) {
-      lowest = b;
+    // inclusive prefixes over the bins: counts, exact significand sums, and the sums as doubles
+    const int sh = binade_shift(E < 0 ? t : E);
+    uint32_t pc = cnt;
+    uint64_t ps = sig, ph = qh, pl = ql;
+    double pw = cnt ? ldexp((double)sig, sh - 149) : 0.0, pq = 0.0;
+    if constexpr (VAR) pq = cnt ? ldexp((double)qh * 0x1p24 + (double)ql, 2 * sh - 298) : 0.0;
+#pragma unroll 1
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t yc = __shfl_up(pc, o);
+      const uint64_t ys = __shfl_up(ps, o);
+      const double yw = __shfl_up(pw, o);
+      const bool in = lane >= o;
+      pc += in ? yc : 0u;
+      ps += in ? ys : 0ull;
+      pw += in ? yw : 0.0;
+      if constexpr (VAR) {
+        const uint64_t yh = __shfl_up(ph, o), yl = __shfl_up(pl, o);
+        const double yq = __shfl_up(pq, o);
+        ph += in ? yh : 0ull;
+        pl += in ? yl : 0ull;
+        pq += in ? yq : 0.0;
+      }
+    }
+    __syncthreads();
+    if (lane == 63) {
+      s.rc[wv] = pc;
+      s.rs[wv] = ps;
+      s.rw[wv] = pw;
+      if constexpr (VAR) {
+        s.rh[wv] = ph;
+        s.rl[wv] = pl;
+        s.rq[wv] = pq;
+      }
+    }
+    __syncthreads();
+    for (int i = 0; i < wv; ++i) {
+      pc += s.rc[i];
+      ps += s.rs[i];
+      pw += s.rw[i];
+      if constexpr (VAR) {
+        ph += s.rh[i];
+        pl += s.rl[i];
+        pq += s.rq[i];
+      }
+    }
+    if (E < 0) {
+      if (t < kB1) {
+        s.pw[t] = pw;
+        if constexpr (VAR) s.pq[t] = pq;
+      }
+    } else {
+      // the keys below the window: the binades below E and the lower part of E
+      pw += (E > 0 ? s.pw[E - 1] : 0.0) + ldexp((double)bsig, sh - 149);
+      if constexpr (VAR) pq += (E > 0 ? s.pq[E - 1] : 0.0) + ldexp((double)bh * 0x1p24 + (double)bl, 2 * sh - 298);
+    }
+    // what the criterion needs at this bin's maximum: keys up to the bin, sums of binade E up to it
+    const uint32_t kb = below + pc;
+    const uint64_t part = E < 0 ? sig : bsig + ps, parth = E < 0 ? qh : bh + ph, partl = E < 0 ? ql : bl + pl;
+    // screen with the double sums (non-negative terms, each prefix within 2^-48 of its value): a margin
+    // above 2^-44 decides as the exact evaluation would; the rest (2) is evaluated exactly
+    uint32_t st = 0;
+    if (cnt) {
+      double lhs, about;
+      criterion<VAR>(B, A2, nnz - kb, mx, pw, pq, lhs, about);
+      const double tol = 0x1p-44 * (VAR ? lhs + about : about);
+      st = lhs <= about - tol ? 1u : (lhs > about + tol ? 0u : 2u);
+    }
+    // b1: the highest bin whose maximum passes; b2: the lowest occupied bin above it (when no maximum
+    // passes, the lowest occupied bin itself: the answer may be one of its smaller keys), refined
+    // while it holds two or more keys. An answer's sums are rounded only when it may stand (one place
+    // for all of it: the code runs once per level, and cold instructions cost more than these steps).
+    BinOut o2;
+    bool down;
+    int b2;
+    while (true) {
+      const int b1 = block_find<true>(s, L.turn, st != 0);
+      b2 = block_find<false>(s, L.turn, cnt != 0 && t > b1);
+      if (t == b1 || t == b2) {
+        BinOut& o = s.bin[t == b1 ? 0 : 1];
+        o.part = part;
+        o.ph = parth;
+        o.pl = partl;
+        o.sig = sig;
+        o.sh = qh;
+        o.sl = ql;
+        o.below = kb;
+        o.cnt = cnt;
+        o.mx = mx;
+        o.state = st;
+      }
+      __syncthreads();
+      o2 = uni(s.bin[1]);
+      down = b2 < kNT && shift > 0 && o2.cnt >= 2;
+      int Eb = E < 0 ? b1 : E;
+      if (b1 < 0) {
+        if (down || !have || rounded) break;
+        Eb = aE;  // the answer of a level above stands
+      }
+      const BinOut o1 = uni(b1 < 0 ? s.ans : s.bin[0]);
+      rounded = b1 < 0 || o1.state != 1 || !down;
+      if (rounded) {
+        T1 = exact_sum(s, Eb, o1.part);
+        if constexpr (VAR) T2 = exact_sum_sq(s, Eb, o1.ph, o1.pl);
+        double lhs;
+        const bool pass = criterion<VAR>(B, A2, nnz - o1.below, o1.mx, T1, T2, lhs, rhs);
+        if (b1 >= 0 && o1.state == 2 && !pass) {
+          if (t == b1) st = 0;
+          continue;
+        }
+      }
+      if (t == 0) s.ans = o1;
+      have = true;
+      aE = Eb;
       break;
     }
+    if (!down) break;
+    below = o2.below - o2.cnt;
+    bsig = o2.part - o2.sig;
+    bh = o2.ph - o2.sh;
+    bl = o2.pl - o2.sl;
+    if (E < 0) {
+      E = b2;
+      lo = (uint32_t)b2 << 23;
+    } else {
+      lo += (uint32_t)b2 << shift;
+    }
+    shift = shift > 9 ? shift - 9 : 0;
+    if (!L.lspan)
+      request<VAR>(a, s, ctl, sc, row, base, len, L, o2.cnt <= kListCap ? kReqList : kReqWindow, lo, shift, o2.cnt);
   }
-  b2 = block_min(s, lowest);
-  // the owners of b1 and b2 broadcast the aggregates above their bin
+  if (!have) {
+    // variance budget: no value passes (possible only through rounding with eps = 0), every nonzero
+    // is capped
+    lam = VAR ? (double)INFINITY : (double)NAN;
+    tcap = VAR ? 1u : kKeyInf;
+    return VAR ? 0u : (uint32_t)kFlagInternal;
+  }
+  __syncthreads();
+  const BinOut o = uni(s.ans);
+  lam = VAR ? T1 / rhs : (B - (double)(nnz - o.below)) / T1;
+  tcap = capped_threshold(lam, o.mx + 1);
+  return 0;
+}
+
+// Algorithm 3 in scale form: lambda_{j+1} = (B - k_j) / U_j, stop when it does not grow. The count
+// k_j and the sum U_j of the rest follow from the binades unless the threshold cuts a binade's keys.
+GS_DI void solve_greedy(const Args& a, SolveLds<false>& s, RowCtl* ctl, RowScratch* sc, int64_t row, int64_t base,
+                        int64_t len, Lead& L, double B, uint64_t nnz, int T, double& lam, uint32_t& tcap) {
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  uint32_t pc = wave_incl(t < kB1 ? s.cnt[t] : 0u, lane);
+  if (lane == 63) s.rc[wv] = pc;
+  __syncthreads();
+  for (int i = 0; i < wv; ++i) pc += s.rc[i];
+  if (t < kB1) s.pc[t] = pc;
+  // step -1: lambda_0 = B / S
+  int e = 254;
+  uint64_t K = 0, part = s.sig[254];
+  uint32_t q = 0;
+  lam = 0.0;
 #pragma unroll 1
-  for (int w = 0; w < 2; ++w) {
-    const int bb = w == 0 ? b1 : b2;
-    if (bb >= 0 && bb != INT_MAX && (int)threadIdx.x == bb / per) {
-      uint64_t K = eK, Sg = eS, QH = eQH, QL = eQL;
-#pragma unroll 1
-      for (int j = per - 1; b0 + j > bb; --j) {
-        const int b = b0 + j;
-        if (b >= L.nbins) continue;
-        uint64_t qh, ql;
-        v_bin_squares(H, L, level2, base, b, qh, ql);
-        K += (uint64_t)L.cnt[b];
-        Sg += (uint64_t)L.sig[b];
-        QH += qh;
-        QL += ql;
+  for (int it = -1;; ++it) {
+    const double U = exact_sum(s, e, part);
+    if (U == 0.0) break;
+    const double ln = (B - (double)K) / U;
+    if (!(ln > lam)) break;
+    lam = ln;
+    q = cap_key(lam);
+    if (it + 1 >= T) break;
+    e = (int)(q >> 23);
+    const uint32_t cnt = s.cnt[e];
+    K = nnz - s.pc[e];  // keys >= q, and binade e's significands below q
+    part = s.sig[e];
+    if ((q & 0x7FFFFFu) == 0) {
+      K += cnt;
+      part = 0;
+    } else if (cnt != 0 && s.mx[e] >= q) {
+      uint64_t qc, qs;
+      count_above(a, s, ctl, sc, row, base, len, L, q, qc, qs);
+      K += qc;
+      part -= qs;
+    }
+  }
+  tcap = q;
+}
+
+// The leader of a row.
+template <int SOLVER, bool VAR = SOLVER == GSPAR_VARIANCE>
+GS_DI void lead_row(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc, int64_t row, int64_t base,
+                    int64_t len) {
+  const int t = threadIdx.x;
+  const double B = ctl->B;
+  const int T = ctl->T;
+  uint32_t flags = ctl->flags;
+  Lead L;
+#pragma unroll
+  for (int j = 0; j < kKeyRegs; ++j) L.kr[j] = 0;
+  // level 1: the copies of the row's histogram summed, one binade per thread
+  const Hist1* h = h1_of(a, row);
+  uint64_t cnt = 0;
+  if (t < kB1) {
+    uint64_t sig = 0;
+    uint32_t mx = 0;
+#pragma unroll
+    for (int k = 0; k < kC1; ++k) {
+      cnt += h[k].cnt[t];
+      sig += h[k].sig[t];
+      mx = max(mx, h[k].mx[t]);
+    }
+    s.cnt[t] = (uint32_t)cnt;
+    s.sig[t] = sig;
+    s.mx[t] = mx;
+    if constexpr (VAR) {
+      const H1Q* q = h1q_of(a, row);
+      uint64_t qh = 0, ql = 0;
+#pragma unroll
+      for (int k = 0; k < kC1; ++k) {
+        qh += q[k].qh[t];
+        ql += q[k].ql[t];
       }
-      s.bi.Kab = L.Kaw + K;
-      Fx W = L.Waw;
-      if (Sg) fx_add(W, fx_shifted(Sg, L.shift, L.err));
-      s.bi.Wab = W;
-      Fq Hq = Haw;
-      fq_add(Hq, fq_squares(QH, QL, L.shift, L.err));
-      s.hq[0] = Hq;
-      s.bi.cnt = (uint64_t)L.cnt[bb];
-      s.bi.mx = L.mx[bb];
-    }
-    __syncthreads();
-    if (bb >= 0 && bb != INT_MAX) {
-      VInfo o;
-      o.K = s.bi.Kab;
-      o.W = s.bi.Wab;
-      o.H = s.hq[0];
-      o.cnt = s.bi.cnt;
-      o.mx = s.bi.mx;
-      if (w == 0) i1 = o;
-      else i2 = o;
-    }
-    __syncthreads();
-  }
-}
-
-GS_DI void sv_variance(SolveLds& s, RowCtl& c, const Hists& H) {
-  const int level = c.stage;
-  int b1, b2;
-  VInfo i1, i2;
-  Fq A2;
-  uint32_t E = 0;
-  if (level == 1) {
-    v_level1(s, c, H, A2, b1, b2, i1, i2);
-    if (threadIdx.x == 0) H.vc->A2 = A2;
-  } else {
-    A2 = H.vc->A2;
-    const Fq Haw = H.vc->wH;
-    E = c.l2exp;
-    Lvl L;
-    if (level == 2) {
-      const BinInfo iE = l1_info(H, (int)E);
-      L = lvl2(H, E, iE.Kab, iE.Wab);
-    } else {
-      L = lvl3(H, E, c.wK, c.wW);
-    }
-    v_level(s, c, H, L, level == 2, level == 2 ? 0u : c.l3base, A2, Haw, b1, b2, i1, i2);
-  }
-  // refine b2 when it holds two or more values, of which a smaller one may pass (also when
-  // nothing at this level passes: the lowest occupied bin may still hold a passing value)
-  if (b2 != INT_MAX && level < 3 && i2.cnt >= 2) {
-    if (b1 >= 0) {
-      c.fbValid = 1;
-      c.fbK = i1.K;
-      c.fbW = i1.W;
-      c.fbTcap = i1.mx + 1;
-      if (threadIdx.x == 0) H.vc->fbH = i1.H;
-    }
-    c.stage = level + 1;
-    if (level == 1) v_request(c, H, 2, (uint32_t)b2, 0, 0, fx_zero(), i2.H);
-    else v_request(c, H, 3, 0, (E << 23) | ((uint32_t)b2 << 11), i2.K, i2.W, i2.H);
-    return;
-  }
-  if (b1 >= 0 || c.fbValid) {
-    // b1's maximum, else the candidate found one level up
-    Fx W;
-    Fq Hq;
-    uint32_t tcap;
-    if (b1 >= 0) {
-      W = i1.W;
-      Hq = i1.H;
-      tcap = i1.mx + 1;
-    } else {
-      W = c.fbW;
-      Hq = H.vc->fbH;
-      tcap = c.fbTcap;
-    }
-    v_finish(c, A2, W, Hq, tcap);
-  } else {
-    // no value passes (possible only through rounding with eps = 0): every nonzero is capped
-    sv_finalize(c, INFINITY, 1);
-  }
-}
-
-// First solve after the statistics pass: totals and the special cases.
-template <bool VAR>
-GS_DI void sv_start(SolveLds& s, RowCtl& c, const Hists& H, int64_t d) {
-  const BinInfo i0 = l1_info(H, 0);
-  const BinInfo inf = l1_info(H, 255);
-  // every finite key lies in binades 0..254; binade 255 counts only Inf/NaN
-  Fx tot = i0.Wab;
-  fx_add(tot, i0.Wb);
-  if (inf.cnt) {
-    tot = fx_sub(tot, inf.Wb);
-    c.flags |= GSPAR_FLAG_NONFINITE;
-  }
-  c.S = tot;
-  c.stage = 1;
-  // zeros = d minus the histogram's population (every nonzero key, finite or not, is binned)
-  c.zeros = (uint64_t)d - (i0.Kab + i0.cnt);
-  const uint64_t nnz = (uint64_t)d - c.zeros;
-  if (c.flags & (GSPAR_FLAG_NONFINITE | GSPAR_FLAG_BADRHO | GSPAR_FLAG_BADSEG)) {
-    sv_finalize(c, NAN, kKeyInf);
-    return;
-  }
-  if (nnz == 0) {
-    c.flags |= GSPAR_FLAG_ALLZERO;
-    sv_finalize(c, INFINITY, 1);
-    return;
-  }
-  if constexpr (VAR) {
-    sv_variance(s, c, H);
-    return;
-  }
-  if (c.B >= (double)nnz) {
-    sv_finalize(c, INFINITY, 1);
-    return;
-  }
-  if (c.B == 0.0) {
-    sv_finalize(c, 0.0, kKeyInf);
-    return;
-  }
-  if (c.solver == GSPAR_GREEDY) {
-    c.lam = c.B / fx_to_double(c.S);
-    c.iter = 0;
-    sv_greedy(s, c, H, 0, 0);
-  } else {
-    sv_exact(s, c, H);
-  }
-}
-
-// Sums the global copies of a histogram (filled with atomics by an earlier kernel on the same
-// stream) into an LDS cache. Every load of a thread is issued before the first sum, so the whole
-// reduction costs one round trip to memory.
-template <int COPIES, int NBINS, typename HistT, typename CntT>
-GS_DI void reduce_into(const HistT* h, CntT* cnt, uint64_t* sig, uint32_t* mx) {
-  static_assert(NBINS % kNT == 0 || NBINS < kNT, "bins per thread");
-  constexpr int kPer = NBINS < kNT ? 1 : NBINS / kNT;
-  uint64_t c[kPer][COPIES], g[kPer][COPIES];
-  uint32_t m[kPer][COPIES];
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const int b = threadIdx.x + j * kNT;
-#pragma unroll
-    for (int k = 0; k < COPIES; ++k) {
-      const bool ok = b < NBINS;
-      c[j][k] = ok ? h[k].cnt[b] : 0;
-      g[j][k] = ok ? h[k].sig[b] : 0;
-      m[j][k] = ok ? h[k].mx[b] : 0;
+      s.qh[t] = qh;
+      s.ql[t] = ql;
     }
   }
-#pragma unroll
-  for (int j = 0; j < kPer; ++j) {
-    const int b = threadIdx.x + j * kNT;
-    uint64_t cs = 0, gs = 0;
-    uint32_t ms = 0;
-#pragma unroll
-    for (int k = 0; k < COPIES; ++k) {
-      cs += c[j][k];
-      gs += g[j][k];
-      ms = max(ms, m[j][k]);
-    }
-    if (b < NBINS) {
-      cnt[b] = (CntT)cs;
-      sig[b] = gs;
-      mx[b] = ms;
-    }
+  // the candidate band is usable only if every key in it was kept (a statistics workgroup whose
+  // region overflowed reserves more than the list holds)
+  if (a.lay.cand_cap) {
+    L.cand_n = ccnt_of(a, row)->v;
+    L.blo = ctl->band_lo;
+    L.bhi = ctl->band_hi;
+    L.banded = L.cand_n <= (uint64_t)a.lay.cand_cap;
+    if (!L.banded) L.blo = L.bhi = 0;
   }
-}
-
-// The row's solver, run by one workgroup per row after each histogram pass: it either finishes the
-// row (lambda and the capped threshold become final) or requests the next refinement window.
-// `first`: the solve right after the statistics pass.
-// VAR: the variance-budget solver's instantiation (a kernel of its own, so that its registers do
-// not weigh on the density-budget solvers).
-template <bool VAR>
-GS_DI void solve_row(SolveLds& s, RowCtl* gc, const Hists& H, int64_t d, bool first) {
-  // The global reads of a solve are issued together, so they share one round trip: level 1
-  // (summed from its copies by the first solve, which also builds the suffix sums and keeps the
-  // table in global memory for the later solves) and the direct count of the last level-2 pass.
-  RowCtl c = *gc;
-  constexpr int n16 = (int)(sizeof(L1Cache) / 16);
-  constexpr int per16 = (n16 + kNT - 1) / kNT;
-  uint4 tab[per16];
-  uint64_t qcnt = 0, qsig = 0;
-  if (first) {
-    reduce_into<kC1, kB1>(H.h1g, H.l1->cnt, H.l1->sig, H.l1->mx);
-    // the candidate band is usable only if every key in it was kept (a statistics workgroup whose
-    // region overflowed reserves more than the list holds)
-    if (H.cand_cap) {
-      c.cand_n = H.cc->v;
-      if (c.cand_n > (uint64_t)H.cand_cap) c.band_lo = c.band_hi = 0;
-    } else {
-      c.band_lo = c.band_hi = 0;
-    }
-  } else {
-    if (c.done) return;
-    const uint4* src = reinterpret_cast<const uint4*>(H.l1g);
-#pragma unroll
-    for (int j = 0; j < per16; ++j) {
-      const int i = threadIdx.x + j * kNT;
-      if (i < n16) tab[j] = src[i];
-    }
-#pragma unroll
-    for (int k = 0; k < kC23; ++k) {
-      qcnt += H.wg[k].qcnt;
-      qsig += H.wg[k].qsig;
-    }
-  }
-  if (c.done) return;
-  if (!first) {
-    uint4* dst = reinterpret_cast<uint4*>(H.l1);
-#pragma unroll
-    for (int j = 0; j < per16; ++j) {
-      const int i = threadIdx.x + j * kNT;
-      if (i < n16) dst[i] = tab[j];
-    }
-  }
-  // for the exact solver the level-2 / level-3 window the last pass filled (for the greedy solver
-  // the bins of a level-2 window are read only if a query needs them)
-  if (c.solver != GSPAR_GREEDY) {
-    if (c.stage == 2) reduce_into<kC23, kB2>(H.wg, H.w2->cnt, H.w2->sig, H.w2->mx);
-    if (c.stage == 3) reduce_into<kC23, kB3>(H.wg, H.w3->cnt, H.w3->sig, H.w3->mx);
-  }
-  c.need = 0;
-  if (threadIdx.x == 0) s.err = 0;
-  // every load above has returned before any thread can go on to clear the window it read
-  __builtin_amdgcn_s_waitcnt(0);
+  // the nonzero keys of the row (binade 255 holds only Inf and NaN)
+  uint32_t nz = (uint32_t)cnt;
+  for (int o = 32; o > 0; o >>= 1) nz += __shfl_xor(nz, o);
+  if ((t & 63) == 0) s.rc[t >> 6] = nz;
   __syncthreads();
-  if (first) {
-    l1_build(s, H);
-    constexpr int n16 = (int)(sizeof(L1Cache) / 16);
-    const uint4* src = reinterpret_cast<const uint4*>(H.l1);
-    uint4* dst = reinterpret_cast<uint4*>(H.l1g);
-    for (int i = threadIdx.x; i < n16; i += kNT) dst[i] = src[i];
-    sv_start<VAR>(s, c, H, d);
-  } else if constexpr (VAR) {
-    sv_variance(s, c, H);
-  } else if (c.solver == GSPAR_GREEDY) {
-    sv_greedy(s, c, H, qcnt, qsig);
-  } else {
-    sv_exact(s, c, H);
-  }
+  uint64_t nnz = 0;
+#pragma unroll
+  for (int i = 0; i < kNT / 64; ++i) nnz += s.rc[i];
+  nnz = uni(nnz);
+  const uint32_t odd = uni(s.cnt[255]);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    if (s.err) {
-      // a broken invariant of the exact arithmetic: the row is reported, not sampled
-      c.flags |= s.err;
-      sv_finalize(c, NAN, kKeyInf);
+  double lam = NAN;
+  uint32_t tcap = kKeyInf;
+  if (odd) flags |= GSPAR_FLAG_NONFINITE;
+  if (flags & (GSPAR_FLAG_NONFINITE | GSPAR_FLAG_BADRHO | GSPAR_FLAG_BADSEG)) {
+    // no solution: reported, not sampled
+  } else if (nnz == 0) {
+    flags |= GSPAR_FLAG_ALLZERO;
+    lam = INFINITY;
+    tcap = 1;
+  } else if (!VAR && B >= (double)nnz) {
+    lam = INFINITY;
+    tcap = 1;
+  } else if (!VAR && B == 0.0) {
+    lam = 0.0;
+  } else {
+    if constexpr (SOLVER == GSPAR_GREEDY) {
+      solve_greedy(a, s, ctl, sc, row, base, len, L, B, nnz, T, lam, tcap);
+    } else {
+      double A2 = 0.0;
+      if constexpr (VAR) A2 = exact_sum_sq(s, 254, s.qh[254], s.ql[254]);
+      flags |= solve_levels<VAR>(a, s, ctl, sc, row, base, len, L, B, nnz, A2, lam, tcap);
     }
-    *gc = c;
+  }
+  if (t == 0) {
+    st_agent(&ctl->req, (uint64_t)kReqDone << 32);
+    ctl->lam = lam;
+    ctl->tcap = tcap;
+    ctl->inv_lam = (lam > 0.0 && lam < INFINITY) ? (float)(1.0 / lam) : 0.0f;
+    ctl->flags = flags;
+    ctl->done = 1;
+    ctl->src = L.from;
+    ctl->band_lo = L.blo;
+    ctl->band_hi = L.bhi;
+    ctl->cand_n = L.cand_n;
   }
 }
 
@@ -1898,9 +1602,6 @@ __global__ void __launch_bounds__(256) k_init(Args a) {
       if (!(rho >= 0.0 && rho <= 1.0)) c.flags = GSPAR_FLAG_BADRHO;
     }
     if (!ok) c.flags |= GSPAR_FLAG_BADSEG;
-    c.l2exp = kNone;
-    c.l3base = kNone;
-    c.qkey = kNone;
     c.solver = a.solver;
     c.T = a.T;
     *ctl_of(a, r) = c;
@@ -1938,25 +1639,6 @@ typedef char gchar;
 #define GS_GLOBAL(T) T
 GS_HD gchar* uniform_ptr(void* p) { return static_cast<gchar*>(p); }
 #endif
-
-// popcount(m & bits of the lanes below this one)
-__device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-// Exclusive prefix over the lanes of a wave of x in [0, 2^B) from B ballots; `total` receives the
-// wave's sum.
-template <int B>
-__device__ __forceinline__ uint32_t wave_prefix_bits(uint32_t x, uint32_t& total) {
-  uint32_t pre = 0;
-  total = 0;
-#pragma unroll
-  for (int b = 0; b < B; ++b) {
-    const unsigned long long m = __ballot((x >> b) & 1);
-    pre += lanes_below(m) << b;
-    total += (uint32_t)__popcll(m) << b;
-  }
-  return pre;
-}
 
 // Systematic sample of each row for the candidate band: kPreWG workgroups per row each read
 // kPreLines of the row's whole 64-byte lines, spread evenly over the row, and add a histogram over
@@ -2283,174 +1965,49 @@ __global__ void __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) k
   }
 }
 
-// Refinement pass over one window of keys, for the rows whose solver asked for one.
-template <bool SQ>
-__global__ void __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) k_refine(Args a) {
-  __shared__ WinLdsT<SQ> sm_w;
-  WinLdsT<SQ>& sm = sm_w;
-  int64_t row, blk;
-  if (!hist_block(a, row, blk)) return;
-  const RowCtl* ctl = ctl_of(a, row);
-  const uint32_t need = ctl->need;
-  if (need != 2 && need != 3) return;
-  int64_t base, len;
-  row_span(a, row, base, len);
-  const float* __restrict__ gr = a.g + base;
-  int64_t beg = blk * a.chunk, end = min(len, beg + a.chunk);
-  // the window lies in the candidate band: the row's collected keys, read as the non-negative
-  // floats they are, in equal shares (whole groups of 4, at least kCandShare keys, at most
-  // kCandGroups shares) by the first of the row's workgroups
-  const bool from_cand = ctl->src != 0;
-  if (from_cand) {
-    const int64_t n = (int64_t)ctl->cand_n;
-    const int64_t groups = min((int64_t)a.nb, kCandGroups);
-    const int64_t share = max(kCandShare, (((n + groups - 1) / groups) + 3) & ~(int64_t)3);
-    beg = blk * share;
-    end = min(n, beg + share);
-    gr = reinterpret_cast<const float*>(cand_of(a, row));
-  }
-  if (beg >= end) return;  // past the end of a shorter segment, or of the candidates
-  uint32_t lo, shift;
-  int nbins;
-  const int cp = (int)(blk % kC23);
-  WinHist* h = win_of(a, row, cp);
-  if (need == 2) {
-    lo = ctl->l2exp << 23;
-    shift = 11;
-    nbins = kB2;
-  } else {
-    lo = ctl->l3base;
-    shift = 0;
-    nbins = kB3;
-  }
-  const uint32_t span = (uint32_t)nbins << shift;
-  // level 2 also keeps bin minima and counts the window's keys >= qkey directly (qkey lies in the
-  // window when set; kNone matches no key)
-  const bool l2 = need == 2;
-  const uint32_t qkey = l2 ? ctl->qkey : kNone;
-  // the greedy solver's last query needs the direct count only: no bins are built or flushed
-  const bool bins = !(l2 && ctl->qonly);
-  // the variance-budget solver's level-2 windows also sum squared significands (level 3 has one
-  // key per bin, whose square follows from the count)
-  const bool sq2 = SQ && l2 && bins;
-  for (int b = threadIdx.x; bins && b < nbins; b += kNT) {
-    sm.pk[b] = 0;
-    sm.mx[b] = 0;
-    sm.mnc[b] = 0;
-    if constexpr (SQ) {
-      sm.qh[b] = 0;
-      sm.ql[b] = 0;
-    }
-  }
-  __syncthreads();
-  uint64_t qc = 0, qs = 0;
-  auto visit = [&](int64_t, const float v[4], uint32_t) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const uint32_t key = key_of(v[c]);
-      const uint32_t rel = key - lo;
-      if (key != 0 && rel < span) {
-        const uint32_t b = rel >> shift;
-        const uint64_t sg = key_sig(key);
-        if (bins) {
-          atomicAdd(&sm.pk[b], (unsigned long long)((1ull << 44) + sg));
-          // level-2 bin extremes (fire-and-forget atomics: a read of the bin first would make
-          // every key wait on the LDS); a level-3 bin is one key, its own maximum
-          if (l2) {
-            atomicMax(&sm.mx[b], key);
-            atomicMax(&sm.mnc[b], ~key);
-          }
-        }
-        if (key >= qkey) {
-          ++qc;
-          qs += sg;
-        }
-        if constexpr (SQ) {
-          if (sq2) {
-            const uint64_t m2 = sg * sg;
-            atomicAdd(&sm.qh[b], (unsigned long long)(m2 >> 24));
-            atomicAdd(&sm.ql[b], (unsigned long long)(m2 & 0xFFFFFFu));
-          }
-        }
-      }
-    }
-  };
-  // (the variance-budget solver never collects candidates)
-  if (!SQ && from_cand) stream_groups<SQ ? 4 : kCandLoads, kNT>(gr, beg, end, visit);
-  else stream_groups<4, kNT>(gr, beg, end, visit);
-  if (l2) {
-    for (int o = 32; o > 0; o >>= 1) {
-      qc += __shfl_xor(qc, o);
-      qs += __shfl_xor(qs, o);
-    }
-    if ((threadIdx.x & 63) == 0) {
-      sm.qc[threadIdx.x >> 6] = qc;
-      sm.qs[threadIdx.x >> 6] = qs;
-    }
-  }
-  __syncthreads();
-  // flush: workgroups start at different blocks of kNT bins, so they do not queue on the same
-  // addresses at the same time
-  static_assert(kB2 % kNT == 0 && kB3 % kNT == 0, "whole blocks of bins");
-  const int nblk = bins ? nbins / kNT : 0;
-  for (int i = 0; i < nblk; ++i) {
-    const int b = ((i + (int)blk) % nblk) * kNT + threadIdx.x;
-    const uint64_t p = sm.pk[b];
-    if (p) {
-      atomicAdd((unsigned long long*)&h->cnt[b], (unsigned long long)(p >> 44));
-      atomicAdd((unsigned long long*)&h->sig[b], (unsigned long long)(p & ((1ull << 44) - 1)));
-      atomicMax(&h->mx[b], l2 ? sm.mx[b] : lo + (uint32_t)b);
-      if (l2) atomicMax(&h->mnc[b], sm.mnc[b]);
-      if constexpr (SQ) {
-        if (sq2) {
-          WinQ* q = winq_of(a, row, cp);
-          atomicAdd((unsigned long long*)&q->qh[b], (unsigned long long)sm.qh[b]);
-          atomicAdd((unsigned long long*)&q->ql[b], (unsigned long long)sm.ql[b]);
-        }
-      }
-    }
-  }
-  if (l2 && threadIdx.x == 0) {
-    uint64_t tc = 0, ts = 0;
-    for (int i = 0; i < kNT / 64; ++i) {
-      tc += sm.qc[i];
-      ts += sm.qs[i];
-    }
-    if (tc) {
-      atomicAdd((unsigned long long*)&h->qcnt, (unsigned long long)tc);
-      atomicAdd((unsigned long long*)&h->qsig, (unsigned long long)ts);
-    }
-  }
-}
-
-// The solver: one workgroup per row, after the statistics pass and after every refinement pass.
-template <bool VAR>
-__global__ void __launch_bounds__(kNT) k_solve(Args a) {
-  __shared__ SolveLds sm;
-  const int64_t row = blockIdx.x;
+// The solver. Grid: a leading workgroup per row, then the helpers: nb - 1 per row of a strided batch,
+// one per further histogram chunk of a segmented call (its map's entries with block > 0).
+template <int SOLVER>
+__global__ void __launch_bounds__(kNT, SOLVER == GSPAR_VARIANCE ? 2 : 4) k_solve(Args a) {
+  constexpr bool VAR = SOLVER == GSPAR_VARIANCE;
+  __shared__ SolveLds<VAR> sm;
+  const bool lead = blockIdx.x < a.rows;
+  const int64_t h = (int64_t)blockIdx.x - a.rows;
+  int64_t row = blockIdx.x, blk = 0;
   if (a.seg && *segok_of(a) != 1) {
     // the workgroup maps of a segmented call do not have the launched shape: no histogram pass
-    // ran and the sample pass does nothing, so the first solve skips the row and writes its results
-    if (a.first && threadIdx.x == 0) {
-      RowCtl* gc = ctl_of(a, row);
-      RowCtl c = *gc;
-      c.flags |= GSPAR_FLAG_BADSEG;
-      sv_finalize(c, NAN, kKeyInf);
-      *gc = c;
+    // ran and the sample pass does nothing, so the row is skipped and its results written here
+    if (lead && threadIdx.x == 0) {
+      RowCtl* c = ctl_of(a, row);
+      c->flags |= GSPAR_FLAG_BADSEG;
+      c->lam = NAN;
+      c->tcap = kKeyInf;
+      c->inv_lam = 0.0f;
+      c->done = 1;
       if (a.nnz) a.nnz[row] = 0;
       if (a.nnz_b) a.nnz_b[row] = 0;
-      if (a.inv_out) a.inv_out[row] = c.inv_lam;
+      if (a.inv_out) a.inv_out[row] = 0.0f;
       if (a.k_out) a.k_out[row] = 0;
-      if (a.lam_out) a.lam_out[row] = c.lam;
-      if (a.flags_out) a.flags_out[row] = c.flags;
+      if (a.lam_out) a.lam_out[row] = NAN;
+      if (a.flags_out) a.flags_out[row] = c->flags;
     }
     return;
   }
-  const Hists H{&sm.err, &sm.l1, &sm.w2, &sm.w3, l1t_of(a, row), h1_of(a, row), win_of(a, row),
-                h1q_of(a, row), winq_of(a, row), vctl_of(a, row), ccnt_of(a, row), a.lay.cand_cap};
+  if (!lead) {
+    if (!a.seg) {
+      row = h / (a.nb - 1);
+      blk = h % (a.nb - 1) + 1;
+    } else {
+      const uint64_t e = reinterpret_cast<const uint64_t*>(a.ws + a.lay.bmap)[h];
+      blk = (int64_t)(e & 0xFFFFFFFFu);
+      if (blk == 0) return;
+      row = (int64_t)(e >> 32);
+    }
+  }
   int64_t base, len;
   row_span(a, row, base, len);
-  solve_row<VAR>(sm, ctl_of(a, row), H, len, a.first != 0);
+  if (lead) lead_row<SOLVER>(a, sm, ctl_of(a, row), scratch_of(a, row), row, base, len);
+  else help_row<VAR>(a, sm, ctl_of(a, row), scratch_of(a, row), row, base, len, (uint32_t)blk);
 }
 
 // Sampling, amplification and order-preserving compaction. Workgroup t handles tile t (kTileElems
@@ -3177,7 +2734,7 @@ __global__ void __launch_bounds__(64) k_probs_out(Args a) {
 // ------------------------------------------------------------------------------------------
 // Kernel classes, in the order the instrumented build reports them.
 enum KernelClass {
-  kcSample = 0, kcStats, kcProbs, kcSolve, kcRefine, kcInit, kcAggregate, kcProbsOut, kcPresample, kcCount
+  kcSample = 0, kcStats, kcProbs, kcSolve, kcInit, kcAggregate, kcProbsOut, kcPresample, kcCount
 };
 
 #ifdef GSPAR_INSTRUMENT
@@ -3287,18 +2844,8 @@ static int launch_solve(Args& a, hipStream_t s) {
   if (nblocks > 0) {
     launch(kcStats, sq ? k_stats<true, false> : cand ? k_stats<false, true> : k_stats<false, false>, grid, dim3(kNT), s, a);
   }
-  a.first = 1;
-  launch(kcSolve, sq ? k_solve<true> : k_solve<false>, dim3((unsigned)a.rows), dim3(kNT), s, a);
-  // each greedy step needs at most one level-2 pass (which counts its query key directly), the
-  // exact solver at most a level-2 and a level-3 window
-  const int R = a.solver == GSPAR_GREEDY ? a.T : 2;  // the variance form also needs at most two
-  for (int r = 0; r < R; ++r) {
-    a.first = 0;
-    if (nblocks > 0) {
-      launch(kcRefine, sq ? k_refine<true> : k_refine<false>, grid, dim3(kNT), s, a);
-    }
-    launch(kcSolve, sq ? k_solve<true> : k_solve<false>, dim3((unsigned)a.rows), dim3(kNT), s, a);
-  }
+  const int64_t helpers = a.seg ? a.seg_blocks : a.rows * (a.nb - 1);
+  launch(kcSolve, sq ? k_solve<GSPAR_VARIANCE> : a.solver == GSPAR_GREEDY ? k_solve<GSPAR_GREEDY> : k_solve<GSPAR_EXACT>, dim3((unsigned)(a.rows + helpers)), dim3(kNT), s, a);
   return hipGetLastError() == hipSuccess ? GSPAR_OK : GSPAR_ERR_HIP;
 }
 
@@ -3892,36 +3439,59 @@ int gspar_prof_disarm(void) {
 }
 
 // Host-side checks of the device arithmetic (the same source compiled for the host): rounding of
-// the exact accumulator, the shift invariant, the capped-threshold search and the generator.
+// the exact sums, the shift invariant, the capped-threshold search and the generator.
 double gspar_check_fx_round(const uint64_t* limbs5) {
-  Fx f;
-  for (int i = 0; i < 5; ++i) f.w[i] = limbs5[i];
-  return fx_to_double(f);
+  uint64_t d[kDig] = {};
+  for (int i = 0; i < 5; ++i) {
+    d[2 * i] += limbs5[i] & 0xFFFFFFFFull;
+    d[2 * i + 1] += limbs5[i] >> 32;
+  }
+  return dig_round<kDig>(d, -149);
+}
+
+// v * 2^s added to digits, then carried into 64-bit limbs.
+static uint32_t check_digits(uint64_t v, int s, int smax, uint64_t* d) {
+  int at;
+  uint64_t x[3];
+  const uint32_t err = dig_split(v, s, smax, at, x);
+  for (int i = 0; i < 3; ++i) d[at + i] += x[i];
+  return err;
+}
+static void check_limbs(uint64_t* d, int limbs, uint64_t* out) {
+  uint64_t carry = 0;
+  for (int i = 0; i < 2 * limbs; ++i) {
+    const uint64_t v = d[i] + carry;
+    carry = v >> 32;
+    if (i & 1) out[i / 2] |= v << 32;
+    else out[i / 2] = v & 0xFFFFFFFFull;
+  }
 }
 
 uint32_t gspar_check_fx_shifted(uint64_t v, int s, uint64_t* limbs5) {
-  uint32_t err = 0;
-  const Fx f = fx_shifted(v, s, &err);
-  for (int i = 0; i < 5; ++i) limbs5[i] = f.w[i];
+  uint64_t d[kDig] = {};
+  const uint32_t err = check_digits(v, s, 255, d);
+  check_limbs(d, 5, limbs5);
   return err;
 }
 
 uint32_t gspar_check_fq_squares(uint64_t qh, uint64_t ql, int shift, uint64_t* limbs10) {
-  uint32_t err = 0;
-  const Fq f = fq_squares(qh, ql, shift, &err);
-  for (int i = 0; i < kQ; ++i) limbs10[i] = f.w[i];
+  uint64_t d[kDigSq] = {};
+  uint32_t err = kFlagInternal;
+  if (shift >= 0 && shift <= 255)
+    err = check_digits(qh, 2 * shift + 24, 2 * 255 + 24, d) | check_digits(ql, 2 * shift, 2 * 255, d);
+  check_limbs(d, 10, limbs10);
   return err;
 }
 
 double gspar_check_exact_sum(const float* x, int64_t n) {
-  Fx acc = fx_zero();
+  uint64_t d[kDig] = {};
   uint32_t err = 0;
   for (int64_t i = 0; i < n; ++i) {
     const uint32_t key = key_of(x[i]);
     if (key == 0 || key >= kKeyInf) continue;
-    fx_add(acc, fx_shifted(key_sig(key), binade_shift((int)(key >> 23)), &err));
+    err |= check_digits(key_sig(key), binade_shift((int)(key >> 23)), 255, d);
   }
-  return err ? NAN : fx_to_double(acc);
+  return err ? NAN : dig_round<kDig>(d, -149);
 }
 
 uint32_t gspar_check_cap_key(double lam) { return cap_key(lam); }

@@ -15,8 +15,10 @@ def build(asan: bool = False) -> str:
     # rows from this length on predict a candidate band (a small threshold and sample exercise the
     # band on the emulated sizes; the production threshold exercises refinement over the row)
     cmin = int(os.environ.get("GSPAR_EMU_CAND_MIN_ROW", "4096"))
+    # keys of a range up to which the solver lists them; a small value exercises its windows and counts
+    lst = os.environ.get("GSPAR_EMU_LIST")
     out = os.path.join(OUT_DIR, ("libgspar_emu_asan" if asan else "libgspar_emu") + (f"_r{int(res)}" if res else "")
-                       + f"_c{cmin}" + ".so")
+                       + f"_c{cmin}" + (f"_l{int(lst)}" if lst else "") + ".so")
     if os.path.exists(out) and os.path.getmtime(out) > max(os.path.getmtime(SRC),
                                                          os.path.getmtime(os.path.join(HERE, "hip", "hip_runtime.h"))):
         return out
@@ -28,6 +30,8 @@ def build(asan: bool = False) -> str:
            f"-DGSPAR_CAND_MIN_ROW={cmin}", "-DGSPAR_PRE_LINES=64",
            "-Wno-unknown-pragmas", "-I", HERE, "-I", os.path.join(ROOT, "include"), "-x", "c++", SRC,
            "-o", out + ".tmp"]
+    if lst:
+        cmd.insert(1, f"-DGSPAR_LIST_CAP={int(lst)}")
     if asan:
         cmd[1:1] = ["-fsanitize=address", "-fno-omit-frame-pointer"]
     subprocess.run(cmd, check=True)

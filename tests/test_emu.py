@@ -157,3 +157,15 @@ def test_emulated_two_tiles_per_workgroup():
     r = subprocess.run([sys.executable, os.path.join(HERE, "emu", "runner.py"), lib, "hybrid"], env=env,
                        capture_output=True, text=True, timeout=1200)
     assert r.returncode == 0 and "hybrid cases ok" in r.stdout, (r.stdout[-2000:], r.stderr[-2000:])
+
+
+@pytest.mark.parametrize("cap", [1, 40, 1500])
+def test_emulated_solver_windows(cap):
+    """The solver's window and count requests, which rows of many keys take, forced on the small
+    emulated inputs by listing at most `cap` keys of a range: every emulated check."""
+    env = dict(os.environ, GSPAR_EMU_LIST=str(cap))
+    lib = subprocess.run([sys.executable, "-c", "import sys; sys.path.insert(0, %r); import build; print(build.build())"
+                          % os.path.join(HERE, "emu")], env=env, capture_output=True, text=True, check=True).stdout.strip()
+    r = subprocess.run([sys.executable, os.path.join(HERE, "emu", "runner.py"), lib, "all"], env=env,
+                       capture_output=True, text=True, timeout=1200)
+    assert r.returncode == 0 and "checked 64" in r.stdout, (r.stdout[-2000:], r.stderr[-2000:])
