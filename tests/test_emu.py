@@ -92,6 +92,24 @@ def test_emulated_parity_subset(emu_lib):
                     assert lam == sol.lam and k == sol.k
 
 
+@pytest.mark.parametrize("scale", [1e-42, 1e-36, 1e-24, 1e20, 1e36])
+def test_emulated_selection_at_extreme_scales(emu_lib, scale):
+    """Whole tiles at scales where lambda * 2^32 lies inside, below and beyond the range in which fp32
+    decides a coordinate (and subnormal magnitudes), plus a ragged tail."""
+    L = runner.load(emu_lib)
+    import oracle
+    import workloads as W
+    from oracle.compare import compare_sample
+
+    g = np.ascontiguousarray(W.t_mixture(2 * 16384 + 37, 31).astype(np.float64) * scale)
+    g = np.clip(g, -3e38, 3e38).astype(np.float32)
+    for solver, rho in (("exact", 0.05), ("greedy", 0.2), ("exact", 1.0)):
+        sol = oracle.solve(g, rho, solver, 2)
+        idx, val, n, lam, k, fl = runner.sample_row(L, g, rho, solver, 78)
+        assert fl == 0
+        compare_sample(g, sol.p, 78, idx, val, n, lam, sol.lam)
+
+
 def test_emulated_full_sweep(emu_lib):
     assert runner.run_all(emu_lib, verbose=False) == 64
 

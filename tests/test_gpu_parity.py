@@ -515,6 +515,24 @@ def test_unaligned_scalar_path(gs):
         assert torch.equal(a.idx[:na], b.idx[:nb]) and torch.equal(a.val[:na], b.val[:nb])
 
 
+@pytest.mark.parametrize("scale", [1e-42, 1e-36, 1e-24, 1e20, 1e36])
+def test_selection_at_extreme_scales(gs, scale):
+    """Whole tiles at scales where lambda * 2^32 lies inside, below and beyond the range in which fp32
+    decides a coordinate (and subnormal magnitudes), plus a ragged tail, against the oracle."""
+    g = np.ascontiguousarray(W.t_mixture(20 * 16384 + 37, 31).astype(np.float64) * scale)
+    g = np.clip(g, -3e38, 3e38).astype(np.float32)
+    gd = torch.from_numpy(g).cuda()
+    _say(f"[scale] {scale}")
+    for solver, rho in (("exact", 0.05), ("greedy", 0.2), ("exact", 1.0)):
+        sol = oracle.solve(g, rho, solver, 2)
+        out = gs.sparsify_sample_compact(gd, rho, seed=78, solver=solver, capacity=g.size)
+        torch.cuda.synchronize()
+        n = int(out.nnz.item())
+        assert int(out.flags.item()) == 0
+        compare_sample(g, sol.p, 78, out.idx[:n].cpu().numpy(), out.val[:n].cpu().numpy(), n,
+                       float(out.lam.item()), sol.lam)
+
+
 @pytest.mark.parametrize("shift", [1, 2, 3])
 @pytest.mark.parametrize("d", [1, 5, 16384, 16387, 300007])
 def test_rows_at_any_float_boundary(gs, d, shift):
