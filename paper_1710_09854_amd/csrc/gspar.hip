@@ -571,6 +571,38 @@ __device__ __forceinline__ void stream_groups(const float* __restrict__ row, int
   }
 }
 
+// The same in blocks of U groups per thread, f(x) for each (coordinates outside [beg, end) read as 0),
+// for visitors with work to do once per block.
+template <int U, int NT, typename F>
+__device__ __forceinline__ void stream_blocks(const float* __restrict__ row, int64_t beg, int64_t end, F&& f) {
+  const int64_t qfull = end / 4;
+  int64_t qb = beg / 4;
+  float4 x[U];
+  for (; qb < qfull; qb += (int64_t)U * NT) {
+    const bool whole = qb + (int64_t)U * NT <= qfull;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t q = qb + threadIdx.x + u * NT;
+      x[u] = load_vec(row + 4 * (q < qfull ? q : qfull - 1));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (!whole) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (qb + threadIdx.x + u * NT >= qfull) x[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+    f(x);
+  }
+  if (4 * qfull < end && threadIdx.x < 64) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (threadIdx.x == 0) load4(row, qfull, end, v);
+    x[0] = make_float4(v[0], v[1], v[2], v[3]);
+    f(x);
+  }
+}
+
 // Helpers of the histogram passes and the solver are force-inlined, so LDS and global pointers keep
 // their address spaces and no call frames or scratch are needed.
 #define GS_DI __device__ __attribute__((always_inline)) inline
@@ -621,7 +653,7 @@ __device__ __forceinline__ uint32_t wave_prefix_bits(uint32_t x, uint32_t& total
 // coordinates takes 26.8 us with it against 38.9 before, the 54 layers of a residual network 73.7
 // against 96.6; 5 rows of 300,007 whose solver lists a binade 44 against 70, 2^28 coordinates 457
 // against 483 (exact, rho = 0.01) and 539 against 571 (greedy, rho = 0.1), 16 rows of 2^20 under the
-// variance budget 249 against 266.
+// variance budget 162 against 266.
 //
 // Waiting: a chunk is taken with an atomic on its own word by its helper, or by the leader once it
 // has done its own, so a chunk is only ever held by a running workgroup and the leader waits only
@@ -642,7 +674,7 @@ __device__ __forceinline__ uint32_t wave_prefix_bits(uint32_t x, uint32_t& total
 enum : uint32_t { kReqWindow = 1, kReqList = 2, kReqCount = 3 };
 constexpr uint32_t kReqDone = 255;      // request number: the row is solved
 constexpr int kHelperPolls = 1 << 15;   // some 20 ms without a request
-constexpr int kKeyRegs = 8;             // listed keys each thread of the leader keeps in registers
+constexpr int kListBatch = 8;           // listed keys in flight per thread of the leader
 constexpr int kPassBuf = 4096;          // listed keys a workgroup gathers in LDS before it appends them
 
 template <class T>
@@ -735,11 +767,13 @@ struct SolveLds {
   uint64_t word;       // a helper's next request (0: leave)
   uint32_t cmd;        // whether the chunk at hand was taken by this workgroup
   uint32_t nbuf, base;  // keys of the chunk at hand that belong in the list, and their place there
+  uint32_t keys[kPassBuf];  // the leader's first listed keys
   union {
     WinLds<VAR> win;
     uint32_t buf[kPassBuf];
   };
 };
+static_assert(kPassBuf == kListBatch * kNT, "one batch fills the leader's keys");
 
 // Block-wide: the highest (HIGH) or lowest thread with pred; -1 or kNT when there is none. Two
 // result rows used in turn, so one barrier per search.
@@ -879,26 +913,35 @@ GS_DI void pass_chunk(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* 
   } else if (P.kind == kReqList) {
     if (threadIdx.x == 0) s.nbuf = 0;
     __syncthreads();
-    stream_groups<4, kNT>(src, beg, end, [&](int64_t, const float v[4], uint32_t) {
-      // the wave's keys of this group: one reservation for all of them, in LDS while there is room
+    // the wave's keys of a block of groups: one reservation for all of them, in LDS while there is room
+    auto gather = [&](const auto& x) {
+      constexpr int U = (int)(sizeof(x) / sizeof(x[0]));
+      static_assert(4 * U < 32, "a 5-bit count per thread");
       uint32_t hit = 0;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) hit |= (uint32_t)(key_of(v[k]) != 0 && key_of(v[k]) - lo < span) << k;
+      for (int u = 0; u < U; ++u) {
+        const float v[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) hit |= (uint32_t)(key_of(v[k]) != 0 && key_of(v[k]) - lo < span) << (4 * u + k);
+      }
       if (!__ballot(hit != 0)) return;
       uint32_t tot;
-      uint32_t at = wave_prefix_bits<3>((uint32_t)__popc(hit), tot), b = 0;
-      const int lane = threadIdx.x & 63;
-      if (lane == 0) b = atomicAdd(&s.nbuf, tot);
-      b = (uint32_t)__shfl((int)b, 0);
-      at += b;
+      uint32_t at = wave_prefix_bits<5>((uint32_t)__popc(hit), tot), b = 0;
+      if ((threadIdx.x & 63) == 0) b = atomicAdd(&s.nbuf, tot);
+      at += (uint32_t)__shfl((int)b, 0);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if ((hit >> k) & 1) {
-          if (at < (uint32_t)kPassBuf) s.buf[at] = key_of(v[k]);
-          ++at;
+      for (int u = 0; u < U; ++u) {
+        const float v[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if ((hit >> (4 * u + k)) & 1) {
+            if (at < (uint32_t)kPassBuf) s.buf[at] = key_of(v[k]);
+            ++at;
+          }
         }
       }
-    });
+    };
+    stream_blocks<4, kNT>(src, beg, end, gather);
     if (!claim()) return;
     const uint32_t m = s.nbuf;
     if (threadIdx.x == 0 && m) s.base = atomicAdd(&ctl->lcount, m);
@@ -996,7 +1039,6 @@ struct Lead {
   uint32_t from = 0;     // source of the last request
   uint32_t chunks = 0;   // and its chunks
   uint32_t llo = 0, lspan = 0, ln = 0;  // the listed range's first key, whether there is one, its number of keys
-  uint32_t kr[kKeyRegs];  // this thread's first listed keys (0: none)
 };
 
 // Makes a request, works on it and waits until all of it is done. `key`: the range's first key, for
@@ -1026,15 +1068,17 @@ GS_DI void request(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc,
   wait_own();
   __syncthreads();  // the scratch is clear: announce the request
   if (threadIdx.x == 0) st_agent(&ctl->req, pass_word(P));
-  pass_chunk<VAR>(a, s, ctl, sc, row, base, len, 0, P, true);
-  // chunks that no helper has taken by now, then those that are still being worked on
+  // its own chunk, chunks that no helper has taken by now (one copy of the code for both: the kernel's
+  // instructions are mostly fetched once, from memory), then those that are still being worked on
+  int f = 0;
   for (uint32_t c0 = 0; c0 < chunks; c0 += kNT) {
     const uint32_t c = c0 + threadIdx.x;
     while (true) {
-      const int f = block_find<false>(s, L.turn, c > 0 && c < chunks && ld_agent(&sc->chunk[c].taken) < P.num);
+      if (f != 0 || c0 != 0) f = block_find<false>(s, L.turn, c > 0 && c < chunks && ld_agent(&sc->chunk[c].taken) < P.num);
       if (f == kNT) break;
-      pass_chunk<VAR>(a, s, ctl, sc, row, base, len, c0 + (uint32_t)f, P, false);
+      pass_chunk<VAR>(a, s, ctl, sc, row, base, len, c0 + (uint32_t)f, P, c0 + (uint32_t)f == 0);
       __syncthreads();
+      if (f == 0) f = kNT + 1;
     }
     while (block_find<false>(s, L.turn, c < chunks && ld_agent(&sc->chunk[c].done) != P.num) != kNT)
       __builtin_amdgcn_s_sleep(1);
@@ -1043,21 +1087,36 @@ GS_DI void request(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc,
     L.llo = key;
     L.lspan = 1;
     L.ln = n;
+    // the first kPassBuf keys stay in LDS, each read by the thread that put it there
+    uint32_t k[kListBatch];
 #pragma unroll
-    for (int j = 0; j < kKeyRegs; ++j) {
+    for (int j = 0; j < kListBatch; ++j) {
       const uint32_t i = threadIdx.x + j * kNT;
-      L.kr[j] = i < n ? ld_agent(&sc->list[i]) : 0u;
+      k[j] = i < n ? ld_agent(&sc->list[i]) : 0u;
     }
+#pragma unroll
+    for (int j = 0; j < kListBatch; ++j) s.keys[threadIdx.x + j * kNT] = k[j];
   }
 }
 
 // Visits this thread's listed keys.
-template <class F>
-GS_DI void each_listed(const RowScratch* sc, const Lead& L, F&& f) {
+template <class S, class F>
+GS_DI void each_listed(const S& s, const RowScratch* sc, const Lead& L, F&& f) {
+  for (uint32_t i = threadIdx.x; i < min(L.ln, (uint32_t)kPassBuf); i += kNT) f(s.keys[i]);
+  // the rest kListBatch at a time: one load after another took 0.4 us each, 7.6 us for 22,000 keys
+  for (uint32_t b = kListBatch * kNT; b < L.ln; b += kListBatch * kNT) {
+    uint32_t k[kListBatch];
 #pragma unroll
-  for (int j = 0; j < kKeyRegs; ++j)
-    if (L.kr[j]) f(L.kr[j]);
-  for (uint32_t i = threadIdx.x + kKeyRegs * kNT; i < L.ln; i += kNT) f(ld_agent(&sc->list[i]));
+    for (int j = 0; j < kListBatch; ++j) {
+      const uint32_t i = b + threadIdx.x + j * kNT;
+      k[j] = ld_agent(&sc->list[i < L.ln ? i : 0]);
+      if (i >= L.ln) k[j] = 0;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < kListBatch; ++j)
+      if (k[j]) f(k[j]);
+  }
 }
 
 // Count and significand sum of the keys >= t of t's binade.
@@ -1075,7 +1134,7 @@ GS_DI void count_above(const Args& a, SolveLds<false>& s, RowCtl* ctl, RowScratc
       g += ld_agent(&sc->chunk[i].qsig);
     }
   } else {
-    each_listed(sc, L, [&](uint32_t key) {
+    each_listed(s, sc, L, [&](uint32_t key) {
       if (key >= t) {
         ++c;
         g += key_sig(key);
@@ -1168,7 +1227,7 @@ GS_DI uint32_t solve_levels(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScr
         }
         __syncthreads();
         const uint32_t lc = t & (kWC - 1), span = shift ? (uint32_t)kWB << shift : 32u, omask = (1u << shift) - 1u;
-        each_listed(sc, L, [&](uint32_t key) {
+        each_listed(s, sc, L, [&](uint32_t key) {
           const uint32_t rel = key - lo;
           if (rel < span) {
             const uint32_t i = (rel >> shift) * kWC + lc, r = rel & omask;
@@ -1400,8 +1459,6 @@ GS_DI void lead_row(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc
   const int T = ctl->T;
   uint32_t flags = ctl->flags;
   Lead L;
-#pragma unroll
-  for (int j = 0; j < kKeyRegs; ++j) L.kr[j] = 0;
   // level 1: the copies of the row's histogram summed, one binade per thread
   const Hist1* h = h1_of(a, row);
   uint64_t cnt = 0;
@@ -1967,8 +2024,11 @@ __global__ void __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) k
 
 // The solver. Grid: a leading workgroup per row, then the helpers: nb - 1 per row of a strided batch,
 // one per further histogram chunk of a segmented call (its map's entries with block > 0).
+// Two workgroups of it fit a compute unit (128 registers), so that all 512 of 16 rows' are resident:
+// with one, under the variance budget, half of the rows had no helpers until the others were solved
+// (the kernel took 140 us on 16 rows of 2^20, and takes 66).
 template <int SOLVER>
-__global__ void __launch_bounds__(kNT, SOLVER == GSPAR_VARIANCE ? 2 : 4) k_solve(Args a) {
+__global__ void __launch_bounds__(kNT, 4) k_solve(Args a) {
   constexpr bool VAR = SOLVER == GSPAR_VARIANCE;
   __shared__ SolveLds<VAR> sm;
   const bool lead = blockIdx.x < a.rows;

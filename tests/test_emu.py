@@ -187,3 +187,24 @@ def test_emulated_solver_windows(cap):
     r = subprocess.run([sys.executable, os.path.join(HERE, "emu", "runner.py"), lib, "all"], env=env,
                        capture_output=True, text=True, timeout=1200)
     assert r.returncode == 0 and "checked 64" in r.stdout, (r.stdout[-2000:], r.stderr[-2000:])
+
+
+@pytest.mark.parametrize("d", [4095, 4096, 4097, 8193, 40003])
+def test_emulated_listed_binade(emu_lib, d):
+    """Rows whose keys all lie in one binade that a threshold cuts, so that one request lists all of
+    them: up to the keys that the solver's leader holds in LDS, past them, and past whole batches.
+    The exact solvers' lambda and capped count are the oracle's."""
+    L = runner.load(emu_lib)
+    import oracle
+    from oracle.compare import compare_sample
+
+    r = np.random.default_rng(d)
+    g = ((1.0 + r.random(d)) * r.choice([-1.0, 1.0], d)).astype(np.float32)
+    g = np.where(np.abs(g) >= 2.0, np.float32(1.5), g).astype(np.float32)
+    for solver, rho in (("exact", 0.9), ("greedy", 0.9), ("variance", 0.02)):
+        sol = oracle.solve(g, rho, solver, 2)
+        idx, val, n, lam, k, fl = runner.sample_row(L, g, rho, solver, 79, cap=d)
+        assert fl == 0
+        compare_sample(g, sol.p, 79, idx, val, n, lam, sol.lam)
+        if solver != "greedy":
+            assert lam == sol.lam and 0 < sol.k < d
