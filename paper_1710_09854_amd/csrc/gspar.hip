@@ -465,10 +465,10 @@ __device__ __forceinline__ uint32_t* creg_of(const Args& a, int64_t r) { return 
 
 
 // Streaming accesses: g is read once per pass and the outputs are written once, so those loads,
-// the probabilities' stores and the compaction's staged stores (whole runs of consecutive words)
+// the probabilities' stores and the sampling pass's staged stores (whole runs of consecutive words)
 // carry the non-temporal hint and do not displace what the caches keep (the level-1 copies,
 // windows and status words). Stores that lanes make one word at a time to scattered places (the
-// other emission paths, the hybrid coding's lists, the candidate band) keep the default policy:
+// other emission paths, the hybrid coding's Q_A list, the candidate band) keep the default policy:
 // there the hint made the hybrid coding's sampling pass a third slower at rho = 0.1. On 2^28
 // coordinates the hint takes the statistics pass from about 213 to 192 microseconds per call.
 //
@@ -2146,20 +2146,26 @@ __device__ uint64_t wave_tile_aggregate(const TileCtx& c, int64_t part, int lane
 // for the tile's prefix.
 // Phase 2: thread t owns the tile's groups [16t, 16t + 16), i.e. 64 consecutive coordinates
 // inside its own wave's quarter, so its survivors are contiguous in the output: one prefix over
-// the wave's lanes places it, and it writes only its own set bits (for up to kStageEmit survivors
-// per wave through an LDS staging area that the wave then stores with consecutive lanes on
-// consecutive slots). Phase 2 reads no global memory (a load would wait for every store issued
+// the wave's lanes places it, and it writes only its own set bits, through an LDS staging area of
+// kStageEmit survivors that the wave then stores with consecutive lanes on consecutive slots (up to
+// kDenseEmit survivors of its 4,096; rows of the variance budget that keep a quarter of 16 x 2^20
+// coordinates take 37 us this way against 62 with one store per lane and survivor). Phase 2 reads no global memory (a load would wait for every store issued
 // before it), except in a wave where some lane kept more capped values than its LDS row holds (a
 // separate instantiation).
 // Capped survivors' values are kept in LDS by the phase-1 lane that decided them, kLaneCap per
 // lane and tile (rows padded to kLaneStride floats so that lanes fall on different banks); a wave
 // with a lane past that reads its capped values from global memory in phase 2.
+// A group with one capped coordinate (nearly all that have any) keeps its largest magnitude, known
+// already, in one store: on 2^28 coordinates with one per cent of outliers the pass takes 242 us at
+// rho = 0.01 and 273 at 0.1 against 252 and 279 with a store for each of the four.
 constexpr int kLaneCap = 8;
 constexpr int kLaneStride = kLaneCap + 1;
 constexpr int kSampleBatch = 8;  // float4 loads in flight per lane in the sampling pass
-constexpr int kDenseEmit = 1024;  // survivors of a wave's quarter tile (of 4096) above which emission goes by groups
-// Survivors of a wave's quarter tile up to which emission is staged in LDS: 4-byte entries in the
-// quarter's 2 KB of code and capped-survivor bytes, free once every lane has read its own.
+// Survivors of a wave's quarter tile (of 4096) above which emission goes by groups: the staged loops take
+// as many steps as the fullest lane of each round, which grows with the square of the density.
+constexpr int kDenseEmit = 2048;
+// Survivors staged in LDS at a time: 4-byte entries in the quarter's 2 KB of code and capped-survivor
+// bytes, free once every lane has read its own.
 constexpr int kStageEmit = 512;
 static_assert(kTileGroups % kSampleBatch == 0 && kTileGroups == 16, "tile shape");
 static_assert(2 * kStageEmit <= kWaveElems / 4 && kTileElems <= 65536 && 64 * kLaneStride <= 1024,
@@ -2198,6 +2204,13 @@ __device__ __forceinline__ uint32_t sign_bytes(const float v[4], uint32_t mask) 
   return (s01 | s23) & mask;
 }
 constexpr uint32_t kSelBytes = 0x08040201u, kSignBytes = 0x80402010u;
+
+// |x| with bit 31 of `s` as its sign.
+__device__ __forceinline__ float signed_as(float x, uint32_t s) {
+  const uint32_t u = (__float_as_uint(x) & 0x7FFFFFFFu) | (s & 0x80000000u);
+  memcpy(&x, &u, 4);
+  return x;
+}
 
 // What a row's whole tiles are decided with (see decide_fast).
 struct FastCtx {
@@ -2271,9 +2284,9 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
   // them, and its last tile writes the row's results).
   int64_t row, part0;
   if (!a.seg) {
-    const int64_t wpr = (a.lay.tiles + K - 1) / K;  // workgroups per row
+    const uint32_t wpr = (uint32_t)((a.lay.tiles + K - 1) / K);  // workgroups per row (a row has at most 2^17 tiles)
     row = blockIdx.x / wpr;
-    part0 = (blockIdx.x % wpr) * K;
+    part0 = (int64_t)(blockIdx.x % wpr) * K;
   } else {
     // the map built by k_init holds only workgroups with tiles; a map that does not have the
     // launched shape leaves every row to the first solve
@@ -2304,8 +2317,10 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
   // passes its selection test: either fl(lambda a) >= 1, so t_i >= 2^32 > x_i, or it lies above the exact
   // criterion's value, where lambda a > 1 in exact arithmetic and the few roundings of lambda keep t_i
   // above 2^32 - 1 >= x_i
-  float capf;
+  float capf, uncapf;  // and the float below it
   memcpy(&capf, &c.tcap, 4);
+  const uint32_t below_cap = c.tcap - 1u;
+  memcpy(&uncapf, &below_cap, 4);
   uint64_t* st = status_of(a);
   // group j of this lane in a tile is tile group wv * (kWaveElems / 4) + 64 j + lane
   const int tg0 = wv * (kWaveElems / 4) + lane;
@@ -2332,14 +2347,33 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
           (uint8_t)__builtin_amdgcn_sad_u8(sign_bytes(v, kSignBytes), 0u, __builtin_amdgcn_sad_u8(sel, 0u, 0u));
       nsel += (uint32_t)__popc(sel);
     };
-    auto capture = [&](int j, const float v[4], uint32_t cz) {
+    // top: the group's largest magnitude, the value kept where only one is capped (the sign is in the
+    // group's code byte)
+    auto capture = [&](int j, const float v[4], float top, uint32_t cz) {
       s_capb[kk][tg0 + 64 * j] = (uint8_t)(cz | (min(run, 15u) << 4));
-      // every value goes to the next free slot (the row's pad slot once the row is full), and
-      // only a capped one takes it, so no lane branches per coordinate
+      if (__builtin_expect((cz & (cz - 1u)) == 0, 1)) {
+        capl[min(run, (uint32_t)kLaneCap)] = top;
+        ++run;
+      } else {
+        // every value goes to the next free slot (the row's pad slot once the row is full), and
+        // only a capped one takes it, so no lane branches per coordinate
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        capl[min(run, (uint32_t)kLaneCap)] = v[k];
-        run += (cz >> k) & 1u;
+        for (int k = 0; k < 4; ++k) {
+          capl[min(run, (uint32_t)kLaneCap)] = v[k];
+          run += (cz >> k) & 1u;
+        }
+      }
+    };
+    auto group = [&](int j, const float4& y) {
+      const float v[4] = {y.x, y.y, y.z, y.w};
+      record(j, v, decide_fast(q0 + 64 * j, v, fc, c.k0, c.k1));
+      // capped coordinates are rare: test the group's largest magnitude first
+      const float top = max_abs4(v);
+      if (top >= capf) {
+        float d[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) d[k] = uncapf - fabsf(v[k]);
+        capture(j, v, top, __builtin_amdgcn_sad_u8(sign_bytes(d, kSelBytes), 0u, 0u));
       }
     };
     if (fast && (part + 1) * (int64_t)kTileElems <= c.d) {
@@ -2348,23 +2382,45 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
       for (int jb = 0; jb < kTileGroups; jb += kSampleBatch) {
         float4 x[kSampleBatch];
 #pragma unroll
-        for (int u = 0; u < kSampleBatch; ++u)
-          x[u] = load_stream(c.row + 4 * (q0 + 64 * (jb + u)));
+        for (int u = 0; u < kSampleBatch; ++u) x[u] = load_stream(c.row + 4 * (q0 + 64 * (jb + u)));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < kSampleBatch; ++u) group(jb + u, x[u]);
+      }
+    } else if (fast && c.d >= 4) {
+      // a row's last tile: the same in two batches, coordinates past the row's end as zeros, which are
+      // never selected and never capped (16 loads one after another took 4 us more on short rows)
+      const int64_t qfull = c.d >> 2;
+#pragma unroll 1
+      for (int jb = 0; jb < kTileGroups; jb += kSampleBatch) {
+        const int64_t qb = q0 + 64 * jb;
+        float4 x[kSampleBatch];
+        if (4 * (qb - lane) >= c.d) {
+          // nothing of the row for this wave: its code bytes all the same
+#pragma unroll 1
+          for (int u = 0; u < kSampleBatch; ++u) s_code[kk][tg0 + 64 * (jb + u)] = 0;
+          continue;
+        }
+#pragma unroll
+        for (int u = 0; u < kSampleBatch; ++u) {
+          const int64_t q = qb + 64 * u;
+          x[u] = load_stream(c.row + 4 * (q < qfull ? q : qfull - 1));
+        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < kSampleBatch; ++u) {
-          const float v[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
-          record(jb + u, v, decide_fast(q0 + 64 * (jb + u), v, fc, c.k0, c.k1));
-          // capped coordinates are rare: test the group's largest magnitude first
-          if (max_abs4(v) >= capf) {
-            uint32_t cz = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) cz |= (uint32_t)(fabsf(v[k]) >= capf) << k;
-            capture(jb + u, v, cz);
+          const int64_t q = qb + 64 * u;
+          if (q >= qfull) {
+            float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (q == qfull) load4(c.row, q, c.d, v);
+            x[u] = make_float4(v[0], v[1], v[2], v[3]);
           }
         }
+#pragma unroll
+        for (int u = 0; u < kSampleBatch; ++u) group(jb + u, x[u]);
       }
     } else {
+#pragma unroll 1
       for (int j = 0; j < kTileGroups; ++j) {
         float v[4];
         uint32_t z = 0, cz = 0;
@@ -2373,7 +2429,7 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
         if (c.live && 4 * (q0 + 64 * j) < c.d) decide_group(c, q0 + 64 * j, v, z, cz);
         else v[0] = v[1] = v[2] = v[3] = 0.0f;
         record(j, v, (z | (z << 8) | (z << 16) | (z << 24)) & kSelBytes);
-        if (cz) capture(j, v, cz);
+        if (cz) capture(j, v, max_abs4(v), cz);
       }
     }
     const bool lane_over = run > (uint32_t)kLaneCap;
@@ -2506,7 +2562,46 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
         const int gi = b >> 2;
         const uint32_t cb = (cwd[gi >> 2] >> (8 * (gi & 3))) & 0xFFu;
         const uint32_t slot = (cb >> 4) + (uint32_t)__popc(cb & ((1u << (b & 3)) - 1u));
-        return s_capl[kk][wv][((16 * tid + gi) & 63) * kLaneStride + slot];
+        return signed_as(s_capl[kk][wv][((16 * tid + gi) & 63) * kLaneStride + slot], (uint32_t)(nm >> b) << 31);
+      };
+      // Staged emission of the wave's n survivors in `mask` (this lane's begin at rank j): kStageEmit at a
+      // time, each lane writes its survivors' entries (tile coordinate, 16 bits; value code: sign in bit
+      // 15; `more` adds bit 14 and a capped value's place in the LDS rows) at their ranks in
+      // the wave's quarter of the code and capped-survivor bytes, which every lane of the wave has read by
+      // now (LDS operations of a wave complete in order); then lane l puts out entries l, l + 64, ... so
+      // that each store covers consecutive addresses, instead of one address per lane far apart.
+      const int32_t t0c = (int32_t)(part * (int64_t)kTileElems);
+      // One round (most waves) needs no bound in its loop.
+      auto staged = [&](uint64_t mask, uint32_t j, uint32_t n, auto&& more, auto&& put) {
+        uint16_t* const si = reinterpret_cast<uint16_t*>(&s_code[kk][wv * (kWaveElems / 4)]);
+        uint16_t* const sc = reinterpret_cast<uint16_t*>(&s_capb[kk][wv * (kWaveElems / 4)]);
+        uint32_t m0 = (uint32_t)mask, m1 = (uint32_t)(mask >> 32);
+        // this lane's survivors of one half of its coordinates
+        auto enter = [&](auto bounded, uint32_t& m, uint32_t neg, uint32_t c0, uint32_t w0) {
+          while (m) {
+            if (decltype(bounded)::value && j - w0 >= (uint32_t)kStageEmit) break;
+            const int b = __builtin_ctz(m);
+            si[j - w0] = (uint16_t)(c0 + b);
+            sc[j - w0] = (uint16_t)(((neg >> b) & 1u) << 15);
+            ++j;
+            m &= m - 1u;
+          }
+        };
+        const uint32_t n0 = (uint32_t)nm, n1 = (uint32_t)(nm >> 32), c0 = (uint32_t)(64 * tid);
+        for (uint32_t w0 = 0; w0 < n; w0 += (uint32_t)kStageEmit) {
+          __builtin_amdgcn_wave_barrier();
+          if (n <= (uint32_t)kStageEmit) {
+            enter(std::false_type{}, m0, n0, c0, 0u);
+            enter(std::false_type{}, m1, n1, c0 + 32u, 0u);
+          } else {
+            enter(std::true_type{}, m0, n0, c0, w0);
+            if (!m0) enter(std::true_type{}, m1, n1, c0 + 32u, w0);
+          }
+          more(sc, w0);
+          __builtin_amdgcn_wave_barrier();
+          const uint32_t end = min(n - w0, (uint32_t)kStageEmit);
+          for (uint32_t i = (uint32_t)lane; i < end; i += 64u) put(w0 + i, si[i], sc[i]);
+        }
       };
       if constexpr (!HYB) {
         uint32_t wtot;
@@ -2532,88 +2627,37 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
           }
         };
         const uint64_t wave_end = (excl & 0x7FFFFFFFull) + wbase + s_wsel[kk][wv];
-        if (lds_values && s_wsel[kk][wv] <= (uint32_t)kStageEmit && wave_end <= (uint64_t)a.cap &&
+        const uint64_t wpos = (excl & 0x7FFFFFFFull) + wbase;  // the wave's first output slot
+        if (lds_values && s_wsel[kk][wv] <= (uint32_t)kDenseEmit && wave_end <= (uint64_t)a.cap &&
             wave_end <= ((uint64_t)1 << 30)) {
           // the common case, staged: every survivor of the wave within the capacity and its capped
-          // values in the lanes' LDS rows. Each lane writes its survivors' entries (tile coordinate,
-          // 16 bits; value code: sign in bit 15, or bit 14 and the capped value's place in the LDS
-          // rows) at its prefix in the wave's quarter of the code and capped-survivor bytes, which
-          // every lane of the wave has read by now (LDS operations of a wave complete in order);
-          // then lane l writes entries l, l + 64, ... so that each store covers consecutive
-          // addresses, instead of one address per lane far apart.
-          uint16_t* const si = reinterpret_cast<uint16_t*>(&s_code[kk][wv * (kWaveElems / 4)]);
-          uint16_t* const sc = reinterpret_cast<uint16_t*>(&s_capb[kk][wv * (kWaveElems / 4)]);
-          const uint64_t wpos = (excl & 0x7FFFFFFFull) + wbase;  // the wave's first output slot
+          // values in the lanes' LDS rows
           const uint32_t lpre = (uint32_t)(pos - wpos);
-          __builtin_amdgcn_wave_barrier();
-          uint32_t j = lpre;
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            uint32_t m = (uint32_t)(sm >> (32 * h));
-            const uint32_t neg = (uint32_t)(nm >> (32 * h));
-            const uint32_t c0 = (uint32_t)(64 * tid + 32 * h);
-            while (m) {
-              const int b = __builtin_ctz(m);
-              si[j] = (uint16_t)(c0 + b);
-              sc[j] = (uint16_t)(((neg >> b) & 1u) << 15);
-              ++j;
-              m &= m - 1u;
-            }
-          }
           uint64_t mc = cm;
-          while (mc) {
-            const int b = __ffsll((unsigned long long)mc) - 1;
-            const uint32_t below = (uint32_t)__popcll(sm & ((1ull << b) - 1ull));
-            const int gi = b >> 2;
-            const uint32_t cb = (cwd[gi >> 2] >> (8 * (gi & 3))) & 0xFFu;
-            const uint32_t slot = (cb >> 4) + (uint32_t)__popc(cb & ((1u << (b & 3)) - 1u));
-            sc[lpre + below] = (uint16_t)(0x4000u | (uint32_t)(((16 * tid + gi) & 63) * kLaneStride + slot));
-            mc &= mc - 1;
-          }
-          __builtin_amdgcn_wave_barrier();
-          const uint32_t wn = s_wsel[kk][wv];
           const float* const capw = &s_capl[kk][wv][0];
           gchar* __restrict__ bi = uniform_ptr(oi) + 4u * (uint32_t)wpos;
           gchar* __restrict__ bv = uniform_ptr(ov) + 4u * (uint32_t)wpos;
-          const int32_t t0c = (int32_t)(part * (int64_t)kTileElems);
-          for (uint32_t i = (uint32_t)lane; i < wn; i += 64u) {
-            const uint32_t x = si[i], cc = sc[i];
-            const float cv = capw[cc & 0x3FFu];
-            const float val = (cc & 0x4000u) ? cv : ((cc & 0x8000u) ? -inv : inv);
-            GS_STORE_STREAM((GS_GLOBAL(int32_t)*)(bi + 4u * i), t0c + (int32_t)x);
-            GS_STORE_STREAM((GS_GLOBAL(float)*)(bv + 4u * i), val);
-          }
-        } else if (lds_values && s_wsel[kk][wv] <= (uint32_t)kDenseEmit && wave_end <= (uint64_t)a.cap &&
-                   wave_end <= ((uint64_t)1 << 30)) {
-          // the same between kStageEmit and kDenseEmit survivors, unstaged (no store needs a bound
-          // check): a first loop writes every survivor with the sign's +-1/lambda, a second
-          // (capped survivors are few) overwrites the capped ones' values with g_i; both stores of
-          // a value come from this lane in program order. 32-bit byte offsets from the row's
-          // output arrays, masks in 32-bit halves.
-          gchar* __restrict__ bi = uniform_ptr(oi);
-          gchar* __restrict__ bv = uniform_ptr(ov);
-          const uint32_t off0 = (uint32_t)pos * 4u;
-          uint32_t off = off0;
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            uint32_t m = (uint32_t)(sm >> (32 * h));
-            const uint32_t neg = (uint32_t)(nm >> (32 * h));
-            const int32_t i0 = (int32_t)(e0 + 32 * h);
-            while (m) {
-              const int b = __builtin_ctz(m);
-              *(GS_GLOBAL(int32_t)*)(bi + off) = i0 + b;
-              *(GS_GLOBAL(float)*)(bv + off) = ((neg >> b) & 1u) ? -inv : inv;
-              off += 4u;
-              m &= m - 1u;
-            }
-          }
-          uint64_t m = cm;
-          while (m) {
-            const int b = __ffsll((unsigned long long)m) - 1;
-            const uint32_t below = (uint32_t)__popcll(sm & ((1ull << b) - 1ull));
-            *(GS_GLOBAL(float)*)(bv + off0 + 4u * below) = capval(b);
-            m &= m - 1;
-          }
+          staged(
+              sm, lpre, s_wsel[kk][wv],
+              [&](uint16_t* sc, uint32_t w0) {
+                while (mc) {
+                  const int b = __ffsll((unsigned long long)mc) - 1;
+                  const uint32_t at = lpre + (uint32_t)__popcll(sm & ((1ull << b) - 1ull)) - w0;
+                  if (at >= (uint32_t)kStageEmit) break;
+                  const int gi = b >> 2;
+                  const uint32_t cb = (cwd[gi >> 2] >> (8 * (gi & 3))) & 0xFFu;
+                  const uint32_t slot = (cb >> 4) + (uint32_t)__popc(cb & ((1u << (b & 3)) - 1u));
+                  sc[at] = (uint16_t)(0x4000u | ((uint32_t)(nm >> b) << 15) |
+                                      (uint32_t)(((16 * tid + gi) & 63) * kLaneStride + slot));
+                  mc &= mc - 1;
+                }
+              },
+              [&](uint32_t i, uint32_t x, uint32_t cc) {
+                const float cv = capw[cc & 0x3FFu];
+                const float val = signed_as((cc & 0x4000u) ? cv : inv, cc << 16);
+                GS_STORE_STREAM((GS_GLOBAL(int32_t)*)(bi + 4u * i), t0c + (int32_t)x);
+                GS_STORE_STREAM((GS_GLOBAL(float)*)(bv + 4u * i), val);
+              });
         } else if (s_wsel[kk][wv] > (uint32_t)kDenseEmit) {
           // many survivors: lane l takes the wave's groups 64 j + l (the order of phase 1 and of
           // this lane's capped-value row), one step j at a time, so the stores of a step fall on a
@@ -2634,7 +2678,8 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
               if ((sel >> k) & 1) {
                 float val = ((neg >> k) & 1) ? -inv : inv;
                 if ((cap >> k) & 1)
-                  val = lds_values ? s_capl[kk][wv][lane * kLaneStride + (cb >> 4) + __popc(cap & ((1u << k) - 1u))]
+                  val = lds_values ? signed_as(s_capl[kk][wv][lane * kLaneStride + (cb >> 4) +
+                                                              __popc(cap & ((1u << k) - 1u))], (neg >> k) << 31)
                                    : c.row[eq + k];
                 if ((int64_t)p < a.cap) {
                   oi[p] = (int32_t)(eq + k);
@@ -2694,7 +2739,8 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
             for (int k = 0; k < 4; ++k) {
               if ((cap >> k) & 1) {
                 const float val =
-                    lds_values ? s_capl[kk][wv][lane * kLaneStride + (cb >> 4) + __popc(cap & ((1u << k) - 1u))]
+                    lds_values ? signed_as(s_capl[kk][wv][lane * kLaneStride + (cb >> 4) +
+                                                          __popc(cap & ((1u << k) - 1u))], (neg >> k) << 31)
                                : c.row[eq + k];
                 if ((int64_t)qa < a.cap) {
                   oa[qa] = (int32_t)(eq + k);
@@ -2714,12 +2760,22 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
             if (lds_values) emit_a(std::true_type{});
             else emit_a(std::false_type{});
           }
-          uint64_t m = bm;
-          while (m) {
-            const int b = __ffsll((unsigned long long)m) - 1;
-            if ((int64_t)pb < a.cap_b) ob[pb] = (int32_t)((uint32_t)(e0 + b) | (uint32_t)(((nm >> b) & 1) << 31));
-            ++pb;
-            m &= m - 1;
+          const uint64_t wpos = (excl & 0x7FFFFFFFull) - excl_cap + (wbase - wbase_cap);
+          if (wpos + btot <= (uint64_t)a.cap_b && wpos + btot <= ((uint64_t)1 << 30)) {
+            gchar* __restrict__ bo = uniform_ptr(ob) + 4u * (uint32_t)wpos;
+            staged(
+                bm, (uint32_t)(pb - wpos), btot, [](uint16_t*, uint32_t) {},
+                [&](uint32_t i, uint32_t x, uint32_t cc) {
+                  GS_STORE_STREAM((GS_GLOBAL(int32_t)*)(bo + 4u * i), (int32_t)((uint32_t)t0c + x + (cc << 16)));
+                });
+          } else {
+            uint64_t m = bm;
+            while (m) {
+              const int b = __ffsll((unsigned long long)m) - 1;
+              if ((int64_t)pb < a.cap_b) ob[pb] = (int32_t)((uint32_t)(e0 + b) | (uint32_t)(((nm >> b) & 1) << 31));
+              ++pb;
+              m &= m - 1;
+            }
           }
         }
       }

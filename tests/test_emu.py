@@ -208,3 +208,34 @@ def test_emulated_listed_binade(emu_lib, d):
         compare_sample(g, sol.p, 79, idx, val, n, lam, sol.lam)
         if solver != "greedy":
             assert lam == sol.lam and 0 < sol.k < d
+
+
+@pytest.mark.parametrize("rho", [0.12, 0.126, 0.25, 0.49, 0.51])
+@pytest.mark.parametrize("tail", [0, 1, 4 * 64 * 8 + 3, 16383])
+def test_emulated_staged_emission(emu_lib, rho, tail):
+    """Survivor counts of a wave (of 4,096 coordinates) just below and above one staging round of 512,
+    several rounds, and on both sides of the limit of the staged path, with capped coordinates of both
+    signs alone in their group and two or more to a group, in whole tiles and in a row's last tile of 0,
+    1 or nearly all coordinates: the compaction is the oracle's sample and the hybrid coding the same
+    survivors."""
+    L = runner.load(emu_lib)
+    import oracle
+    from oracle.compare import compare_sample
+
+    d = 2 * 16384 + tail
+    r = np.random.default_rng(1000 + tail)
+    g = (r.choice([-1.0, 1.0], d) * (1.0 + 0.01 * r.random(d))).astype(np.float32)
+    g[r.integers(0, d, d // 300)] *= np.float32(50.0)
+    g[40:46] = [-300.0, 300.0, 200.0, -200.0, 100.0, -100.0]
+    sol = oracle.solve(g, rho, "exact", 2)
+    idx, val, n, lam, k, fl = runner.sample_row(L, g, rho, "exact", 80, cap=d)
+    assert fl == 0 and lam == sol.lam and k == sol.k and k > 0
+    compare_sample(g, sol.p, 80, idx, val, n, lam, sol.lam)
+    big = np.abs(g[idx]) > 40.0
+    assert np.array_equal(val[big], g[idx][big])
+    ia, va, na, cb, nb, inv, q, lam2, fl2 = runner.hybrid_batched(L, g[None, :], [rho], [80], "exact")
+    a, b = int(na[0]), int(nb[0])
+    bi = cb[0, :b] & 0x7FFFFFFF
+    assert not fl2.any() and a + b == n and a == k
+    assert np.array_equal(np.sort(np.concatenate([ia[0, :a], bi])), idx) and np.all(np.diff(bi) > 0)
+    assert np.array_equal(va[0, :a], g[ia[0, :a]]) and np.array_equal(cb[0, :b] < 0, g[bi] < 0)
