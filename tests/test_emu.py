@@ -239,3 +239,29 @@ def test_emulated_staged_emission(emu_lib, rho, tail):
     assert not fl2.any() and a + b == n and a == k
     assert np.array_equal(np.sort(np.concatenate([ia[0, :a], bi])), idx) and np.all(np.diff(bi) > 0)
     assert np.array_equal(va[0, :a], g[ia[0, :a]]) and np.array_equal(cb[0, :b] < 0, g[bi] < 0)
+
+
+@pytest.mark.parametrize("segs", [1, 255, 256, 257, 700])
+def test_emulated_many_segments(emu_lib, segs):
+    """Segment maps filled by several workgroups, of fewer and more rows than one scan holds, lengths
+    around a histogram chunk and a tile (and empty ones) among them: every segment's sample is that of
+    a row of its own."""
+    L = runner.load(emu_lib)
+    import workloads as W
+
+    r = np.random.default_rng(segs)
+    lens = r.integers(0, 40, segs)
+    for at, n in ((0, 16385), (segs // 2, 8193), (segs - 1, 40001)):
+        lens[at] = n
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    g = np.ascontiguousarray(W.t_mixture(int(off[-1]), 90 + segs), np.float32)
+    seeds = np.arange(segs) + 5
+    idx, val, nnz, lam, k, fl = runner.segmented(L, g, off, np.full(segs, 0.1), seeds, "exact")
+    for i in {0, 1 % segs, segs // 2, segs - 2 if segs > 1 else 0, segs - 1}:
+        row = g[off[i]:off[i + 1]]
+        if row.size == 0:
+            assert nnz[i] == 0
+            continue
+        ri, rv, n, rl, rk, rf = runner.sample_row(L, row, 0.1, "exact", int(seeds[i]))
+        assert nnz[i] == n and fl[i] == rf and k[i] == rk and lam[i] == rl
+        assert np.array_equal(idx[i][:n], ri) and np.array_equal(val[i][:n], rv)
