@@ -1199,9 +1199,9 @@ GS_DI uint32_t solve_levels(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScr
   uint32_t lo = 0, shift = 23, below = 0;
   uint64_t bsig = 0, bh = 0, bl = 0;
   bool have = false;  // an answer, unless a lower level gives a better one
-  bool rounded = false;  // its sums T1, T2 and the criterion's right-hand side are rounded
+  bool rounded = false;  // its sum T1 and the criterion's right-hand side are rounded
   int aE = 0;
-  double T1 = 0.0, T2 = 0.0, rhs = 0.0;
+  double T1 = 0.0, rhs = 0.0;
   while (true) {
     // this thread's bin: count, significand sum, largest key, square sums
     uint32_t cnt = 0, mx = 0;
@@ -1364,17 +1364,21 @@ GS_DI uint32_t solve_levels(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScr
         Eb = aE;  // the answer of a level above stands
       }
       const BinOut o1 = uni(b1 < 0 ? s.ans : s.bin[0]);
-      rounded = b1 < 0 || o1.state != 1 || !down;
-      if (rounded) {
-        T1 = exact_sum(s, Eb, o1.part);
-        if constexpr (VAR) T2 = exact_sum_sq(s, Eb, o1.ph, o1.pl);
-        double lhs;
-        const bool pass = criterion<VAR>(B, A2, nnz - o1.below, o1.mx, T1, T2, lhs, rhs);
+      const bool round = b1 < 0 || o1.state != 1 || !down;
+      if (round) {
+        const double S1 = exact_sum(s, Eb, o1.part);
+        double S2 = 0.0, lhs, right;
+        if constexpr (VAR) S2 = exact_sum_sq(s, Eb, o1.ph, o1.pl);
+        const bool pass = criterion<VAR>(B, A2, nnz - o1.below, o1.mx, S1, S2, lhs, right);
         if (b1 >= 0 && o1.state == 2 && !pass) {
+          // the answer so far and its sums stand
           if (t == b1) st = 0;
           continue;
         }
+        T1 = S1;
+        rhs = right;
       }
+      rounded = round;
       if (t == 0) s.ans = o1;
       have = true;
       aE = Eb;

@@ -265,3 +265,56 @@ def test_emulated_many_segments(emu_lib, segs):
         ri, rv, n, rl, rk, rf = runner.sample_row(L, row, 0.1, "exact", int(seeds[i]))
         assert nnz[i] == n and fl[i] == rf and k[i] == rk and lam[i] == rl
         assert np.array_equal(idx[i][:n], ri) and np.array_equal(val[i][:n], rv)
+
+
+def _exact_row(L, g, rho, solver, seed=5):
+    """The compaction of one row, with lambda and the capped count equal to the oracle's bit for bit."""
+    import oracle
+    from oracle.compare import compare_sample
+
+    g = np.ascontiguousarray(g, np.float32)
+    sol = oracle.solve(g, rho, solver, 2)
+    idx, val, n, lam, k, fl = runner.sample_row(L, g, rho, solver, seed, cap=g.size)
+    assert fl == sol.flags and lam == sol.lam and k == sol.k, (solver, rho, lam, sol.lam, k, sol.k, fl)
+    compare_sample(g, sol.p, seed, idx, val, n, lam, sol.lam)
+    return n, k
+
+
+_HALVES = np.concatenate([np.full(10, 0.5), [1.0, 1.5]])
+
+
+@pytest.mark.parametrize("g, rho, solver", [
+    (np.concatenate([np.ones(8), np.full(3, 2.0), np.zeros(89)]), 0.07, "exact"),
+    (np.concatenate([np.zeros(88), _HALVES]), 0.07, "exact"),
+    (_HALVES, 7 / 12 * (1 + 1e-14), "exact"),
+    (np.concatenate([[2.0 ** -40], np.full(100, 1.25), [1.5]]), 2.2e-16, "variance"),
+], ids=["ones_twos", "halves_zeros", "halves", "variance"])
+def test_emulated_failing_tie_above_the_answer(emu_lib, g, rho, solver):
+    """A value within rounding of Algorithm 2's criterion that fails it, alone in its window, above an
+    answer that a higher level gave: lambda comes from the answer's own sums."""
+    _exact_row(runner.load(emu_lib), g, rho, solver)
+
+
+@pytest.mark.parametrize("solver", ["exact", "variance"])
+def test_emulated_quantised_rows(emu_lib, solver):
+    """Integer and fixed-point rows, whose budgets lie on an integer or a few ulps off it (variance
+    budget: whose eps is about the rounding error of the sums), so that values meet the criterion with
+    equality up to rounding: lambda and k are the oracle's bit for bit."""
+    L = runner.load(emu_lib)
+    r = np.random.default_rng(7)
+    for _ in range(1500):
+        d = int(np.exp(r.uniform(0.0, np.log(160.0))))
+        top = int(r.choice([2, 3, 8]))
+        g = r.integers(-top, top + 1, d) / float(r.choice([1, 2, 128]))
+        if r.random() < 0.3:
+            g = np.full(d, 1.0 + r.random())
+            g[0] = 10.0 ** r.uniform(-14.0, 0.0)
+        if r.random() < 0.4:
+            g[r.random(d) < r.random()] = 0.0
+        if solver == "exact":
+            rho = int(r.integers(1, d + 1)) / d
+            for _ in range(int(r.integers(0, 3))):
+                rho = float(np.nextafter(rho, r.choice([0.0, 1.0])))
+        else:
+            rho = float(r.choice([10.0 ** r.uniform(-17.0, -15.0), 10.0 ** r.uniform(-15.0, 0.0), 0.25, 0.5, 1.0]))
+        _exact_row(L, g, rho, solver)

@@ -555,6 +555,26 @@ def test_rows_at_any_float_boundary(gs, d, shift):
         assert torch.equal(pa.p, pb.p) and int(pa.k.item()) == int(pb.k.item())
 
 
+_HALVES = np.concatenate([np.full(10, 0.5), [1.0, 1.5]])
+
+
+@pytest.mark.parametrize("g, rho, solver", [
+    (np.concatenate([np.ones(8), np.full(3, 2.0), np.zeros(89)]), 0.07, "exact"),
+    (np.concatenate([np.zeros(88), _HALVES]), 0.07, "exact"),
+    (_HALVES, 7 / 12 * (1 + 1e-14), "exact"),
+    (np.concatenate([[2.0 ** -40], np.full(100, 1.25), [1.5]]), 2.2e-16, "variance"),
+], ids=["ones_twos", "halves_zeros", "halves", "variance"])
+def test_failing_tie_above_the_answer(gs, g, rho, solver):
+    """A value within rounding of Algorithm 2's criterion that fails it, alone in its window, above an
+    answer that a higher level gave: lambda and the capped count are the oracle's bit for bit."""
+    g = g.astype(np.float32)
+    _say(f"[failing tie] d={g.size} rho={rho} {solver}")
+    sol = oracle.solve(g, rho, solver, 2)
+    idx, val, n, lam, k, fl = _run_row(gs, g, rho, solver, 5, cap=g.size)
+    assert fl == 0 and lam == sol.lam and k == sol.k
+    compare_sample(g, sol.p, 5, idx, val, n, lam, sol.lam)
+
+
 def test_batched_equals_rows_and_oracle(gs):
     rows, d = 12, 50003
     rng = np.random.default_rng(71)
