@@ -2321,10 +2321,10 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
   const float inv = ctl->inv_lam;
   const bool fast = c.live && (c.lam == 0.0 || c.lam >= kLamScaledMin);
   const FastCtx fc = fast_ctx(c.lam);
-  // a coordinate is capped (p_i = 1) iff |g_i| >= capf, the float with bit pattern tcap; it always
-  // passes its selection test: either fl(lambda a) >= 1, so t_i >= 2^32 > x_i, or it lies above the exact
-  // criterion's value, where lambda a > 1 in exact arithmetic and the few roundings of lambda keep t_i
-  // above 2^32 - 1 >= x_i
+  // a coordinate is capped (p_i = 1) iff |g_i| >= capf, the float with bit pattern tcap, and is then
+  // kept whatever its selection test says: nearly always t_i >= 2^32 > x_i, but where the exact
+  // criterion was decided by its roundings (a variance budget with eps of about 1e-16) lambda |g_i| may
+  // lie anywhere below 1
   float capf, uncapf;  // and the float below it
   memcpy(&capf, &c.tcap, 4);
   const uint32_t below_cap = c.tcap - 1u;
@@ -2374,15 +2374,18 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
     };
     auto group = [&](int j, const float4& y) {
       const float v[4] = {y.x, y.y, y.z, y.w};
-      record(j, v, decide_fast(q0 + 64 * j, v, fc, c.k0, c.k1));
+      uint32_t sel = decide_fast(q0 + 64 * j, v, fc, c.k0, c.k1);
       // capped coordinates are rare: test the group's largest magnitude first
       const float top = max_abs4(v);
       if (top >= capf) {
         float d[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) d[k] = uncapf - fabsf(v[k]);
-        capture(j, v, top, __builtin_amdgcn_sad_u8(sign_bytes(d, kSelBytes), 0u, 0u));
+        const uint32_t capped = sign_bytes(d, kSelBytes);
+        sel |= capped;
+        capture(j, v, top, __builtin_amdgcn_sad_u8(capped, 0u, 0u));
       }
+      record(j, v, sel);
     };
     if (fast && (part + 1) * (int64_t)kTileElems <= c.d) {
       // whole tile inside the row: kSampleBatch unconditional loads in flight per lane

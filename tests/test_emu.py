@@ -318,3 +318,34 @@ def test_emulated_quantised_rows(emu_lib, solver):
         else:
             rho = float(r.choice([10.0 ** r.uniform(-17.0, -15.0), 10.0 ** r.uniform(-15.0, 0.0), 0.25, 0.5, 1.0]))
         _exact_row(L, g, rho, solver)
+
+
+@pytest.mark.parametrize("d", [8000, 16384, 2 * 16384 + 100])
+def test_emulated_capped_below_one(emu_lib, d):
+    """The variance budget with an eps of about the sums' rounding error: the criterion makes the run of
+    equal magnitudes capped although fl(lambda |g_i|) lies well below 1. The capped set is kept whole, in
+    a row's whole tiles and in its last one, by the compaction, the probabilities and the hybrid coding."""
+    import oracle
+
+    L = runner.load(emu_lib)
+    r = np.random.default_rng(d)
+    capped = np.arange(339, d)
+    for _ in range(500):  # such a row: the rounding of the sums decides, so it is looked for
+        g = np.full(d, r.uniform(1.0, 2.0), np.float32)
+        g[0] = 0.55 * np.spacing(capped.size * float(g[1]))  # moves the sum of the rest by an ulp
+        g[1:339] = 0
+        eps = float(r.uniform(0.9e-16, 2.2e-16))
+        sol = oracle.solve(g, eps, "variance", 2)
+        if sol.k == capped.size and sol.lam * float(g[-1]) < 0.9:
+            break
+    else:
+        pytest.fail("no such row")
+    _, k = _exact_row(L, g, eps, "variance")
+    idx, val, n, _, _, _ = runner.sample_row(L, g, eps, "variance", 5, cap=d)
+    assert n == k == capped.size and np.array_equal(idx, capped) and np.array_equal(val, g[capped])
+    p, lam, kp, fl = runner.probs_row(L, g, eps, "variance")
+    assert kp == k and np.all(p[capped] == 1.0)
+    ia, va, na, cb, nb, inv, q, lam, fl = runner.hybrid_batched(L, g[None, :], [eps], [5], "variance")
+    assert na[0] == k and nb[0] == 0 and not fl.any()
+    assert np.array_equal(ia[0, :k], capped) and np.array_equal(va[0, :k], g[capped])
+    assert np.array_equal(np.flatnonzero(q[0]), capped) and np.all(q[0][capped] == 2)

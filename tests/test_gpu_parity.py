@@ -575,6 +575,32 @@ def test_failing_tie_above_the_answer(gs, g, rho, solver):
     compare_sample(g, sol.p, 5, idx, val, n, lam, sol.lam)
 
 
+@pytest.mark.parametrize("d", [8000, 16384, 2 * 16384 + 100])
+def test_capped_below_one(gs, d):
+    """The variance budget with an eps of about the sums' rounding error: equal magnitudes are capped by
+    the criterion although lambda |g_i| lies well below 1. All of them are kept, in whole tiles and in a
+    row's last one, by the compaction and the hybrid coding."""
+    r = np.random.default_rng(d)
+    capped = np.arange(339, d)
+    for _ in range(500):  # such a row: the rounding of the sums decides, so it is looked for
+        g = np.full(d, r.uniform(1.0, 2.0), np.float32)
+        g[0] = 0.55 * np.spacing(capped.size * float(g[1]))  # moves the sum of the rest by an ulp
+        g[1:339] = 0
+        eps = float(r.uniform(0.9e-16, 2.2e-16))
+        sol = oracle.solve(g, eps, "variance", 2)
+        if sol.k == capped.size and sol.lam * float(g[-1]) < 0.9:
+            break
+    else:
+        pytest.fail("no such row")
+    _say(f"[capped below one] d={d} eps={eps}")
+    idx, val, n, lam, k, fl = _run_row(gs, g, eps, "variance", 5, cap=d)
+    assert fl == 0 and lam == sol.lam and n == k == capped.size
+    assert np.array_equal(idx, capped) and np.array_equal(val, g[capped])
+    h = gs.sparsify_sample_hybrid(torch.from_numpy(g).cuda(), eps, seed=5, solver="variance")
+    torch.cuda.synchronize()
+    assert int(h.n_a.item()) == k and int(h.n_b.item()) == 0 and int(h.flags.item()) == 0
+
+
 def test_batched_equals_rows_and_oracle(gs):
     rows, d = 12, 50003
     rng = np.random.default_rng(71)
