@@ -1426,7 +1426,7 @@ GS_DI void solve_greedy(const Args& a, SolveLds<false>& s, RowCtl* ctl, RowScrat
   // step -1: lambda_0 = B / S
   int e = 254;
   uint64_t K = 0, part = s.sig[254];
-  uint32_t q = 0;
+  uint32_t q = kKeyInf;  // a first lambda that underflows to zero caps nothing
   lam = 0.0;
 #pragma unroll 1
   for (int it = -1;; ++it) {

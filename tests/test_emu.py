@@ -349,3 +349,19 @@ def test_emulated_capped_below_one(emu_lib, d):
     assert na[0] == k and nb[0] == 0 and not fl.any()
     assert np.array_equal(ia[0, :k], capped) and np.array_equal(va[0, :k], g[capped])
     assert np.array_equal(np.flatnonzero(q[0]), capped) and np.all(q[0][capped] == 2)
+
+
+@pytest.mark.parametrize("solver", ["greedy", "exact"])
+@pytest.mark.parametrize("d, scale, rho", [(1000, 1e30, 1e-300), (3, 100.0, 5e-324), (16384 + 7, 1e36, 1e-310)])
+def test_emulated_lambda_underflows(emu_lib, solver, d, scale, rho):
+    """A positive budget so small that lambda = B / sum |g_i| rounds to zero: nothing is capped and
+    nothing sampled, by the compaction, the hybrid coding and the probabilities."""
+    L = runner.load(emu_lib)
+    r = np.random.default_rng(d)
+    g = (r.choice([-1.0, 1.0], d) * (1.0 + r.random(d)) * scale).astype(np.float32)
+    idx, val, n, lam, k, fl = runner.sample_row(L, g, rho, solver, 5, cap=d)
+    assert (n, lam, k, fl) == (0, 0.0, 0, 0)
+    ia, va, na, cb, nb, inv, q, lam2, fl2 = runner.hybrid_batched(L, g[None, :], [rho], [5], solver)
+    assert na[0] == nb[0] == 0 and lam2[0] == 0.0 and not fl2.any() and not q.any()
+    p, lam3, k3, fl3 = runner.probs_row(L, g, rho, solver)
+    assert not p.any() and (lam3, k3, fl3) == (0.0, 0, 0)

@@ -601,6 +601,20 @@ def test_capped_below_one(gs, d):
     assert int(h.n_a.item()) == k and int(h.n_b.item()) == 0 and int(h.flags.item()) == 0
 
 
+@pytest.mark.parametrize("solver", ["greedy", "exact"])
+def test_lambda_underflows(gs, solver):
+    """A positive budget so small that lambda = B / sum |g_i| rounds to zero: nothing is capped and
+    nothing sampled, and every probability is zero."""
+    r = np.random.default_rng(1000)
+    g = (r.choice([-1.0, 1.0], 1000) * (1.0 + r.random(1000)) * 1e30).astype(np.float32)
+    _say(f"[lambda underflows] {solver}")
+    idx, val, n, lam, k, fl = _run_row(gs, g, 1e-300, solver, 5, cap=g.size)
+    assert (n, lam, k, fl) == (0, 0.0, 0, 0)
+    o = gs.sparsify_probs(torch.from_numpy(g).cuda(), 1e-300, solver=solver)
+    torch.cuda.synchronize()
+    assert float(o.lam.item()) == 0.0 and int(o.k.item()) == 0 and not bool(o.p.any())
+
+
 def test_batched_equals_rows_and_oracle(gs):
     rows, d = 12, 50003
     rng = np.random.default_rng(71)
