@@ -13,6 +13,13 @@
 // reads of shared state that no barrier separates from another lane's write. __shared__ variables
 // become static storage, shared by the fibers of the running workgroup. Because workgroups never
 // overlap, inter-workgroup waits (the look-back) always find their predecessors finished.
+//
+// Built with -DEMU_CONCURRENT, up to EMU_RESIDENT workgroups of a launch are resident at once and
+// the next one starts when one returns, as on a GPU. Each resident workgroup has a host thread (its
+// __shared__ variables and the scheduler state are thread_local), of which one at a time runs: it
+// may hand over to another at every s_sleep, and at random at barriers and at device-scope loads and
+// stores. Who runs next is drawn by weights that are drawn anew for each workgroup (1, 8 or 64, or
+// all alike with EMU_EVEN=1), so that some fall far behind; every draw follows from EMU_SHUFFLE_SEED.
 #pragma once
 #include <algorithm>
 #include <atomic>
@@ -38,7 +45,12 @@
 #define __global__
 #define __device__
 #define __host__
-#define __shared__ static
+#if defined(EMU_CONCURRENT)
+#define EMU_TLS thread_local
+#else
+#define EMU_TLS
+#endif
+#define __shared__ static EMU_TLS
 #define __forceinline__ inline
 #define __noinline__ __attribute__((noinline))
 #define __launch_bounds__(...)
@@ -96,8 +108,8 @@ struct Fiber {
   unsigned long nsync = 0;
 };
 inline constexpr size_t kFiberStack = size_t(1) << 20;
-inline Block* tl_block = nullptr;
-inline uint3e tl_tid, tl_bid, tl_bdim, tl_gdim;
+inline EMU_TLS Block* tl_block = nullptr;
+inline EMU_TLS uint3e tl_tid, tl_bid, tl_bdim, tl_gdim;
 // Stall diagnostics: each lane records the call site and count of its last block barrier.
 struct LaneTrace {
   std::atomic<const void*> site{nullptr};
@@ -109,19 +121,20 @@ inline bool g_shuffle = getenv("EMU_SHUFFLE") && atoi(getenv("EMU_SHUFFLE")) != 
 // EMU_SHUFFLE_SEED varies the random schedules between runs
 inline unsigned g_shuffle_seed = getenv("EMU_SHUFFLE_SEED") ? (unsigned)atoi(getenv("EMU_SHUFFLE_SEED")) : 0u;
 inline unsigned long g_launches = 0;
-inline std::minstd_rand g_rng;
+inline EMU_TLS std::minstd_rand g_rng;
 
-// scheduler state of the running launch (launches come from one host thread at a time)
-inline std::vector<Fiber> g_fibers;
-inline unsigned g_nfib = 0, g_cur = 0, g_live = 0;
-inline std::vector<unsigned> g_alive, g_slot;  // the fibers that have not returned, and where each sits
-inline void* g_main_sp = nullptr;
-inline void (*g_body)(void*) = nullptr;
-inline void* g_body_arg = nullptr;
+// scheduler state of the running launch (launches come from one host thread at a time), or with
+// EMU_CONCURRENT of the resident workgroup of this host thread
+inline EMU_TLS std::vector<Fiber> g_fibers;
+inline EMU_TLS unsigned g_nfib = 0, g_cur = 0, g_live = 0;
+inline EMU_TLS std::vector<unsigned> g_alive, g_slot;  // the fibers that have not returned, and where each sits
+inline EMU_TLS void* g_main_sp = nullptr;
+inline EMU_TLS void (*g_body)(void*) = nullptr;
+inline EMU_TLS void* g_body_arg = nullptr;
 #if defined(__SANITIZE_ADDRESS__)
-inline const void* g_main_bottom = nullptr;
-inline size_t g_main_size = 0;
-inline bool g_from_main = false;
+inline EMU_TLS const void* g_main_bottom = nullptr;
+inline EMU_TLS size_t g_main_size = 0;
+inline EMU_TLS bool g_from_main = false;
 #endif
 
 // Saves the callee-saved registers and the stack pointer of the running context in *save and
@@ -166,9 +179,61 @@ inline void release(Bar& b) {
   b.arrived = 0;
   ++b.gen;
 }
-inline unsigned long g_events = 0;  // barrier arrivals and returns from the kernel
+inline EMU_TLS unsigned long g_events = 0;  // barrier arrivals and returns from the kernel
 [[noreturn]] void deadlock();
+#if defined(EMU_CONCURRENT)
+// The resident workgroups of the running launch; the one whose index is `turn` runs.
+struct Resident {
+  std::mutex mu;
+  std::condition_variable cv;
+  std::vector<unsigned> weight;  // 0: its thread has ended
+  unsigned turn = 0;
+  std::minstd_rand rng;
+};
+inline Resident* g_res = nullptr;
+inline thread_local unsigned tl_slot = 0;
+inline unsigned env_u(const char* name, unsigned dflt) { return getenv(name) ? (unsigned)atoi(getenv(name)) : dflt; }
+inline unsigned draw_weight() {
+  if (env_u("EMU_EVEN", 0)) return 1;
+  return 1u << (3 * (g_res->rng() % 3));
+}
+// Lets a workgroup drawn by weight run, and waits for this one's turn (unless it has ended).
+inline void hand_over(bool ended = false) {
+  if (!g_res) return;
+  std::unique_lock<std::mutex> lk(g_res->mu);
+  unsigned total = 0;
+  for (unsigned w : g_res->weight) total += w;
+  if (!total) return;
+  unsigned at = g_res->rng() % total, next = 0;
+  while (at >= g_res->weight[next]) at -= g_res->weight[next++];
+  if (next == tl_slot) return;
+  g_res->turn = next;
+  g_res->cv.notify_all();
+  if (!ended) g_res->cv.wait(lk, [] { return g_res->turn == tl_slot; });
+}
+inline void maybe_hand_over(unsigned one_in) {
+  if (g_res && g_res->rng() % one_in == 0) hand_over();
+}
+// Waits for its own global accesses (s_waitcnt, by the first thread of a workgroup) per workgroup of
+// the last launches, from the last call of emu_waits on.
+inline std::vector<unsigned long> g_waits;
+inline void count_wait() {
+  if (tl_tid.x != 0) return;
+  if (g_waits.size() <= tl_bid.x) g_waits.resize(tl_bid.x + 1);
+  ++g_waits[tl_bid.x];
+}
+extern "C" __attribute__((visibility("default"))) unsigned long emu_waits(unsigned long* out, unsigned long n) {
+  const unsigned long m = g_waits.size();
+  for (unsigned long i = 0; i < n; ++i) out[i] = i < m ? g_waits[i] : 0;
+  g_waits.clear();
+  return m;
+}
+#else
+inline void maybe_hand_over(unsigned) {}
+inline void count_wait() {}
+#endif
 inline void bar_wait(Bar& b) {
+  maybe_hand_over(4096);
   const unsigned long gen = b.gen;
   ++g_events;
   if (++b.arrived == b.expected) {
@@ -295,9 +360,15 @@ struct uint4 {
 inline uint4 make_uint4(unsigned x, unsigned y, unsigned z, unsigned w) { return uint4{x, y, z, w}; }
 inline int __popc(unsigned v) { return __builtin_popcount(v); }
 inline int __popcll(unsigned long long v) { return __builtin_popcountll(v); }
-inline void __builtin_amdgcn_s_sleep(int) { emu::yield(); }
+inline void __builtin_amdgcn_s_sleep(int) {
+#if defined(EMU_CONCURRENT)
+  ++emu::g_events;  // the others may wait at a barrier for a lane that waits for another workgroup
+  emu::hand_over();
+#endif
+  emu::yield();
+}
 inline void __builtin_amdgcn_sched_barrier(int) {}
-inline void __builtin_amdgcn_s_waitcnt(int) {}
+inline void __builtin_amdgcn_s_waitcnt(int) { emu::count_wait(); }
 inline unsigned __float_as_uint(float f) {
   unsigned u;
   std::memcpy(&u, &f, 4);
@@ -323,6 +394,7 @@ namespace emu {
 inline bool g_hide_status = getenv("EMU_HIDE_STATUS") && atoi(getenv("EMU_HIDE_STATUS")) != 0;
 template <class T>
 inline T atomic_load_emu(T* p) {
+  maybe_hand_over(256);
   T v = __atomic_load_n(p, __ATOMIC_SEQ_CST);
   if constexpr (sizeof(T) == 8) {
     if (g_hide_status && ((uint64_t)v >> 62) != 0) return (T)0;
@@ -331,7 +403,7 @@ inline T atomic_load_emu(T* p) {
 }
 }  // namespace emu
 #define __hip_atomic_load(p, order, scope) emu::atomic_load_emu(p)
-#define __hip_atomic_store(p, v, order, scope) __atomic_store_n((p), (v), __ATOMIC_SEQ_CST)
+#define __hip_atomic_store(p, v, order, scope) (emu::maybe_hand_over(256), __atomic_store_n((p), (v), __ATOMIC_SEQ_CST))
 
 namespace emu {
 // No fiber of the running workgroup can proceed (a lane waits at a barrier its partners never
@@ -412,9 +484,7 @@ template <class K, class... A>
 void launch(K kernel, dim3 grid, dim3 block, A... args) {
   const unsigned nb = grid.x * grid.y * grid.z;
   const unsigned nt = block.x;
-  ensure_fibers(nt);
   ++g_launches;
-  Block blk;
   // EMU_STALL_SECONDS: a launch still running after that long reports each lane's last block
   // barrier and exits (a lane that loops without reaching a barrier)
   std::mutex mu;
@@ -439,10 +509,12 @@ void launch(K kernel, dim3 grid, dim3 block, A... args) {
     });
   }
   auto body = [&]() { kernel(args...); };
-  g_body = [](void* p) { (*static_cast<decltype(body)*>(p))(); };
-  g_body_arg = &body;
   bool divergent = false;
-  for (unsigned b = 0; b < nb && !divergent; ++b) {
+  // workgroup b on this host thread
+  auto run_block = [&](unsigned b) {
+    Block blk;
+    g_body = [](void* p) { (*static_cast<decltype(body)*>(p))(); };
+    g_body_arg = &body;
     blk.bar = Bar{nt, 0, 0};
     blk.waves.assign((nt + 63) / 64, Wave{});
     for (unsigned w = 0; w < blk.waves.size(); ++w) blk.waves[w].bar.expected = std::min(64u, nt - 64 * w);
@@ -489,7 +561,38 @@ void launch(K kernel, dim3 grid, dim3 block, A... args) {
         divergent = true;
         break;
       }
-  }
+  };
+#if defined(EMU_CONCURRENT)
+  Resident res;
+  g_res = &res;
+  res.rng.seed(987654u + 7919u * (unsigned)g_launches + 104729u * g_shuffle_seed);
+  unsigned next = 0;  // the first workgroup that has not started
+  const unsigned nres = std::min(nb, env_u("EMU_RESIDENT", 4));
+  for (unsigned w = 0; w < nres; ++w) res.weight.push_back(draw_weight());
+  std::vector<std::thread> workers;
+  for (unsigned w = 0; w < nres; ++w)
+    workers.emplace_back([&, w] {
+      tl_slot = w;
+      {
+        std::unique_lock<std::mutex> lk(res.mu);
+        res.cv.wait(lk, [&] { return res.turn == w; });
+      }
+      ensure_fibers(nt);
+      while (next < nb && !divergent) {
+        run_block(next++);
+        res.weight[w] = draw_weight();
+        hand_over();
+      }
+      for (Fiber& f : g_fibers) munmap(f.stack - 4096, kFiberStack + 4096);
+      res.weight[w] = 0;
+      hand_over(true);
+    });
+  for (auto& t : workers) t.join();
+  g_res = nullptr;
+#else
+  ensure_fibers(nt);
+  for (unsigned b = 0; b < nb && !divergent; ++b) run_block(b);
+#endif
   {
     std::lock_guard<std::mutex> lk(mu);
     finished = true;

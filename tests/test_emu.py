@@ -365,3 +365,73 @@ def test_emulated_lambda_underflows(emu_lib, solver, d, scale, rho):
     assert na[0] == nb[0] == 0 and lam2[0] == 0.0 and not fl2.any() and not q.any()
     p, lam3, k3, fl3 = runner.probs_row(L, g, rho, solver)
     assert not p.any() and (lam3, k3, fl3) == (0.0, 0, 0)
+
+
+def _build_emu(concurrent=False, **env):
+    """The emulation built with the given variables (see emu/build.py), in a process of its own."""
+    r = subprocess.run([sys.executable, "-c", "import sys; sys.path.insert(0, %r); import build; "
+                        "print(build.build(concurrent=%r))" % (os.path.join(HERE, "emu"), concurrent)],
+                       env=dict(os.environ, **env), capture_output=True, text=True, check=True)
+    return r.stdout.strip()
+
+
+_CONCURRENT = """
+import ctypes, sys
+sys.path.insert(0, sys.argv[3])
+import numpy as np
+import runner
+import workloads as W
+
+A, B = runner.load(sys.argv[1]), runner.load(sys.argv[2])
+same = lambda x, y: all(np.array_equal(np.asarray(u), np.asarray(v)) for u, v in zip(x, y))
+buf = (ctypes.c_ulong * 4096)()
+
+
+def helped(rows, call):
+    # whether a workgroup past the rows' leaders finished a chunk of a request
+    B.emu_waits(buf, ctypes.c_ulong(4096))
+    out = call(B)
+    B.emu_waits(buf, ctypes.c_ulong(4096))
+    return out, sum(buf[rows:4096])
+
+
+n = 0
+for d, seed in ((100003, 3), (65536, 4)):
+    g = np.ascontiguousarray(W.t_mixture(d, seed), np.float32)
+    for solver, rho in (("exact", 0.05), ("greedy", 0.1), ("variance", 1.0)):
+        f = lambda L: runner.sample_row(L, g, rho, solver, 5)
+        b, h = helped(1, f)
+        assert same(f(A), b), (d, solver)
+        n += h
+g2 = np.stack([W.t_mixture(40003, 30 + r) for r in range(3)])
+for solver, rho in (("exact", 0.05), ("greedy", 0.1), ("variance", 1.0)):
+    f = lambda L: runner.batched(L, g2, [rho] * 3, [1, 2, 3], solver)
+    b, h = helped(3, f)
+    assert same(f(A), b), solver
+    n += h
+off = np.cumsum([0, 30001, 5, 0, 70001]).astype(np.int64)
+g = np.ascontiguousarray(W.t_mixture(int(off[-1]), 8), np.float32)
+f = lambda L: runner.segmented(L, g, off, np.full(4, 0.1), [1, 2, 3, 4], "exact")
+b, h = helped(4, f)
+x, y = f(A), b
+assert same(x[2:], y[2:]) and all(same(u, v) for u, v in zip(x[:2], y[:2]))
+n += h
+print("helped", n)
+assert n > 0
+"""
+
+
+@pytest.mark.parametrize("resident, seed", [(2, 1), (4, 3), (8, 5)])
+@pytest.mark.parametrize("listed", [None, 40])
+def test_emulated_leader_and_helpers(emu_lib, listed, resident, seed):
+    """The solver's leader and helpers resident at once, at random speeds (helpers that take chunks,
+    lose them to the leader, hold an old request while the leader is at the next one, or start after
+    the row is solved), for list requests and, with at most 40 keys listed, windows and counts: all
+    results are those of the leader working alone, bit for bit."""
+    env = {} if listed is None else {"GSPAR_EMU_LIST": str(listed)}
+    alone = emu_lib if listed is None else _build_emu(**env)
+    conc = _build_emu(concurrent=True, **env)
+    r = subprocess.run([sys.executable, "-c", _CONCURRENT, alone, conc, os.path.join(HERE, "emu")],
+                       env=dict(os.environ, EMU_RESIDENT=str(resident), EMU_SHUFFLE_SEED=str(seed)),
+                       capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-2000:])
