@@ -402,11 +402,14 @@ struct Args {
   int64_t seg_chunk;  // host: histogram-pass chunk chosen from the segment lengths
   int64_t seg_tiles;  // host: sample tiles that hold coordinates, over all segments
   int64_t seg_blocks; // histogram-pass workgroups (the grid), from the host offsets
+  int64_t seg_rest;   // those of them past their segment's first
   int64_t seg_wgs;    // sample-pass workgroups (the grid), from the host offsets
   int seg_k;          // tiles per sample workgroup
   int seg_align;      // the host's offsets are multiples of 4 (and g 16-byte aligned): the device's must be too
   size_t ws_bytes;    // the workspace's size (the candidate buffers take what the rest leaves)
   int64_t cand_region;  // candidate keys per statistics workgroup (cand_cap / nb, a multiple of 64)
+  int help_step;        // histogram chunks past a row's first per helper of the solver
+  int helpers;          // helpers per row of a strided batch
 };
 
 // Start and length of row r: row r of a strided batch (offset r * ld, length d), or segment r of a
@@ -659,11 +662,15 @@ __device__ __forceinline__ uint32_t wave_prefix_bits(uint32_t x, uint32_t& total
 // has done its own, so a chunk is only ever held by a running workgroup and the leader waits only
 // for chunks that were taken: no wait depends on another workgroup being scheduled. Helpers are
 // optional (the leader alone would take every chunk); one that finds no request for long enough
-// leaves. Hand-offs use agent-scope atomics for the data itself as well as for the words that
-// announce it, each side waiting for its own accesses to complete (s_waitcnt) before it announces
-// them, so no cache write-back or invalidation is needed. Every word that all chunks would touch is
-// avoided: atomics on one address take 10-30 ns each (counting a 2^28 row's candidates through one
-// counter per wave took 150 us a request).
+// leaves. About kSolveHelpers of them are launched at most, as many as are resident at once, each for
+// every few-th chunk of its row: with one for each of the 1,025 chunks of a row of 2^30 coordinates,
+// those that found no place left their chunks to the leader, one after another, and the call took 15.4
+// ms under the variance budget and 99 ms where the greedy solver counts over an unaligned row, against
+// 3.0 and 3.5. Hand-offs use agent-scope atomics for the data itself as well as for the words that
+// announce it, each side waiting for its own accesses to complete (s_waitcnt) before it announces them,
+// so no cache write-back or invalidation is needed. Every word that all chunks would touch is avoided:
+// atomics on one address take 10-30 ns each (counting a 2^28 row's candidates through one counter per
+// wave took 150 us a request).
 //
 // Exact and variance solver: descend from binades (2^23 keys) to windows of 512 bins, of 2^14, then
 // 2^5, then single keys. At each level the highest bin whose maximum passes the criterion (b1) and
@@ -674,6 +681,13 @@ __device__ __forceinline__ uint32_t wave_prefix_bits(uint32_t x, uint32_t& total
 enum : uint32_t { kReqWindow = 1, kReqList = 2, kReqCount = 3 };
 constexpr uint32_t kReqDone = 255;      // request number: the row is solved
 constexpr int kHelperPolls = 1 << 15;   // some 20 ms without a request
+// Helpers of a call: the solver's workgroups that are resident at once (two on each of 256 compute
+// units). Calls whose chunks are shorter than kMaxChunk have fewer chunks than this, and a helper for
+// each. (A build may lower it to give a helper several chunks on small inputs.)
+#ifndef GSPAR_SOLVE_HELPERS
+#define GSPAR_SOLVE_HELPERS 512
+#endif
+constexpr int64_t kSolveHelpers = GSPAR_SOLVE_HELPERS;
 constexpr int kListBatch = 8;           // listed keys in flight per thread of the leader
 constexpr int kPassBuf = 4096;          // listed keys a workgroup gathers in LDS before it appends them
 
@@ -1001,10 +1015,11 @@ GS_DI void pass_chunk(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* 
   if (threadIdx.x == 0) st_agent(&sc->chunk[c].done, P.num);
 }
 
-// The helper of chunk c: works on it in each of the row's requests until the row is solved.
+// Helper h (from 1) of a row of n chunks and `step` - 1 helpers: works on chunks h, h + step, ... of
+// each of the row's requests until the row is solved.
 template <bool VAR>
 GS_DI void help_row(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc, int64_t row, int64_t base,
-                    int64_t len, uint32_t c) {
+                    int64_t len, uint32_t h, uint32_t step, uint32_t n) {
   uint32_t seen = 0;  // thread 0: the last request looked at
   while (true) {
     if (threadIdx.x == 0) {
@@ -1024,8 +1039,18 @@ GS_DI void help_row(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc
     __syncthreads();
     const Pass P = pass_of(uni(s.word));
     if (P.num == 0 || P.num == kReqDone) return;
-    pass_chunk<VAR>(a, s, ctl, sc, row, base, len, c, P, false);
-    __syncthreads();
+    for (uint32_t c = h; c < n; c += step) {
+      if (c != h) {
+        // (a chunk after the first may be the leader's by now: not worth reading then)
+        if (threadIdx.x == 0) s.cmd = ld_agent(&sc->chunk[c].taken) < P.num ? 1u : 0u;
+        __syncthreads();
+        const bool open = uni(s.cmd) != 0;
+        __syncthreads();
+        if (!open) continue;
+      }
+      pass_chunk<VAR>(a, s, ctl, sc, row, base, len, c, P, false);
+      __syncthreads();
+    }
   }
 }
 
@@ -2030,8 +2055,8 @@ __global__ void __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) k
   }
 }
 
-// The solver. Grid: a leading workgroup per row, then the helpers: nb - 1 per row of a strided batch,
-// one per further histogram chunk of a segmented call (its map's entries with block > 0).
+// The solver. Grid: a leading workgroup per row, then the helpers: a.helpers per row of a strided
+// batch; for a segmented call a workgroup per map entry, of which those of every help_step-th block help.
 // Two workgroups of it fit a compute unit (128 registers), so that all 512 of 16 rows' are resident:
 // with one, under the variance budget, half of the rows had no helpers until the others were solved
 // (the kernel took 140 us on 16 rows of 2^20, and takes 66).
@@ -2041,7 +2066,8 @@ __global__ void __launch_bounds__(kNT, 4) k_solve(Args a) {
   __shared__ SolveLds<VAR> sm;
   const bool lead = blockIdx.x < a.rows;
   const int64_t h = (int64_t)blockIdx.x - a.rows;
-  int64_t row = blockIdx.x, blk = 0;
+  int64_t row = blockIdx.x;
+  uint32_t help = 0;
   if (a.seg && *segok_of(a) != 1) {
     // the workgroup maps of a segmented call do not have the launched shape: no histogram pass
     // ran and the sample pass does nothing, so the row is skipped and its results written here
@@ -2063,19 +2089,28 @@ __global__ void __launch_bounds__(kNT, 4) k_solve(Args a) {
   }
   if (!lead) {
     if (!a.seg) {
-      row = h / (a.nb - 1);
-      blk = h % (a.nb - 1) + 1;
+      row = (uint32_t)h / (uint32_t)a.helpers;
+      help = (uint32_t)h % (uint32_t)a.helpers + 1u;
     } else {
       const uint64_t e = reinterpret_cast<const uint64_t*>(a.ws + a.lay.bmap)[h];
-      blk = (int64_t)(e & 0xFFFFFFFFu);
-      if (blk == 0) return;
+      const uint32_t blk = (uint32_t)e;
+      if (blk == 0 || blk % (uint32_t)a.help_step != 0) return;
+      help = blk / (uint32_t)a.help_step;
       row = (int64_t)(e >> 32);
     }
   }
   int64_t base, len;
   row_span(a, row, base, len);
-  if (lead) lead_row<SOLVER>(a, sm, ctl_of(a, row), scratch_of(a, row), row, base, len);
-  else help_row<VAR>(a, sm, ctl_of(a, row), scratch_of(a, row), row, base, len, (uint32_t)blk);
+  if (lead) {
+    lead_row<SOLVER>(a, sm, ctl_of(a, row), scratch_of(a, row), row, base, len);
+  } else {
+    uint32_t n = (uint32_t)a.nb, helpers = (uint32_t)a.helpers;
+    if (a.seg) {  // (32-bit divisions: a row is shorter than 2^31, a chunk than 2^20)
+      n = ((uint32_t)len + (uint32_t)a.chunk - 1u) / (uint32_t)a.chunk;
+      helpers = (n - 1u) / (uint32_t)a.help_step;
+    }
+    help_row<VAR>(a, sm, ctl_of(a, row), scratch_of(a, row), row, base, len, help, helpers + 1u, n);
+  }
 }
 
 // Sampling, amplification and order-preserving compaction. Workgroup t handles tile t (kTileElems
@@ -3001,6 +3036,13 @@ static void plan(Args& a) {
   a.nb = (int)((a.d + chunk - 1) / chunk);
   a.cand_region = (a.lay.cand_cap / a.nb) & ~(int64_t)63;
   if (a.cand_region == 0) a.lay.cand_cap = 0;  // no room for a band
+  // the solver's helpers: one for each chunk past a row's first while they can all be resident, else
+  // one for every few (at least one for a row of a strided batch)
+  const int64_t rest = a.seg ? a.seg_rest : a.rows * (a.nb - 1);
+  int64_t step = (rest + kSolveHelpers - 1) / kSolveHelpers;
+  if (!a.seg && step > a.nb - 1) step = a.nb - 1;
+  a.help_step = step < 1 ? 1 : (int)step;
+  a.helpers = (a.nb - 1) / a.help_step;
 }
 
 // Every row of a strided batch starts on a 16-byte boundary.
@@ -3023,7 +3065,7 @@ static int launch_solve(Args& a, hipStream_t s) {
   if (nblocks > 0) {
     launch(kcStats, sq ? k_stats<true, false> : cand ? k_stats<false, true> : k_stats<false, false>, grid, dim3(kNT), s, a);
   }
-  const int64_t helpers = a.seg ? a.seg_blocks : a.rows * (a.nb - 1);
+  const int64_t helpers = a.seg ? a.seg_blocks : a.rows * a.helpers;
   launch(kcSolve, sq ? k_solve<GSPAR_VARIANCE> : a.solver == GSPAR_GREEDY ? k_solve<GSPAR_GREEDY> : k_solve<GSPAR_EXACT>, dim3((unsigned)(a.rows + helpers)), dim3(kNT), s, a);
   return hipGetLastError() == hipSuccess ? GSPAR_OK : GSPAR_ERR_HIP;
 }
@@ -3465,6 +3507,8 @@ static void set_segments(Args& a, const int64_t* off, const int64_t* off_dev, in
   }
   a.seg_chunk = hi;
   a.seg_blocks = blocks(hi);
+  a.seg_rest = a.seg_blocks;
+  for (int64_t r = 0; r < segs; ++r) a.seg_rest -= off[r + 1] > off[r];
   // sample pass: tiles per workgroup from the tiles that hold coordinates, and the workgroups
   a.seg_tiles = 0;
   for (int64_t r = 0; r < segs; ++r) {

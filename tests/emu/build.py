@@ -17,8 +17,11 @@ def build(asan: bool = False, concurrent: bool = False) -> str:
     cmin = int(os.environ.get("GSPAR_EMU_CAND_MIN_ROW", "4096"))
     # keys of a range up to which the solver lists them; a small value exercises its windows and counts
     lst = os.environ.get("GSPAR_EMU_LIST")
+    # helpers of the solver resident at once; a small value makes each take several chunks of a row
+    hlp = os.environ.get("GSPAR_EMU_HELPERS")
     out = os.path.join(OUT_DIR, ("libgspar_emu_asan" if asan else "libgspar_emu") + (f"_r{int(res)}" if res else "")
-                       + f"_c{cmin}" + (f"_l{int(lst)}" if lst else "") + ("_conc" if concurrent else "") + ".so")
+                       + f"_c{cmin}" + (f"_l{int(lst)}" if lst else "") + (f"_h{int(hlp)}" if hlp else "")
+                       + ("_conc" if concurrent else "") + ".so")
     if os.path.exists(out) and os.path.getmtime(out) > max(os.path.getmtime(SRC),
                                                          os.path.getmtime(os.path.join(HERE, "hip", "hip_runtime.h"))):
         return out
@@ -35,6 +38,8 @@ def build(asan: bool = False, concurrent: bool = False) -> str:
            "-o", tmp]
     if lst:
         cmd.insert(1, f"-DGSPAR_LIST_CAP={int(lst)}")
+    if hlp:
+        cmd.insert(1, f"-DGSPAR_SOLVE_HELPERS={int(hlp)}")
     if concurrent:
         cmd.insert(1, "-DEMU_CONCURRENT")
     if asan:

@@ -422,16 +422,50 @@ assert n > 0
 
 
 @pytest.mark.parametrize("resident, seed", [(2, 1), (4, 3), (8, 5)])
-@pytest.mark.parametrize("listed", [None, 40])
-def test_emulated_leader_and_helpers(emu_lib, listed, resident, seed):
+@pytest.mark.parametrize("listed, helpers", [(None, None), (40, None), (40, 3)])
+def test_emulated_leader_and_helpers(emu_lib, listed, helpers, resident, seed):
     """The solver's leader and helpers resident at once, at random speeds (helpers that take chunks,
     lose them to the leader, hold an old request while the leader is at the next one, or start after
-    the row is solved), for list requests and, with at most 40 keys listed, windows and counts: all
-    results are those of the leader working alone, bit for bit."""
+    the row is solved), for list requests and, with at most 40 keys listed, windows and counts, also
+    with fewer helpers than chunks: all results are those of the leader working alone, bit for bit."""
     env = {} if listed is None else {"GSPAR_EMU_LIST": str(listed)}
     alone = emu_lib if listed is None else _build_emu(**env)
+    if helpers is not None:
+        env["GSPAR_EMU_HELPERS"] = str(helpers)
     conc = _build_emu(concurrent=True, **env)
     r = subprocess.run([sys.executable, "-c", _CONCURRENT, alone, conc, os.path.join(HERE, "emu")],
                        env=dict(os.environ, EMU_RESIDENT=str(resident), EMU_SHUFFLE_SEED=str(seed)),
                        capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-2000:])
+
+
+_SHARE = """
+import ctypes, sys
+sys.path.insert(0, sys.argv[2])
+import numpy as np
+import runner
+import workloads as W
+
+L = runner.load(sys.argv[1])
+buf = (ctypes.c_ulong * 4096)()
+lead = helped = 0
+for solver, rho in (("exact", 0.05), ("greedy", 0.1), ("variance", 1.0)):
+    g = np.ascontiguousarray(W.t_mixture(200003, 3), np.float32)
+    L.emu_waits(buf, ctypes.c_ulong(4096))
+    runner.sample_row(L, g, rho, solver, 5)
+    L.emu_waits(buf, ctypes.c_ulong(4096))
+    lead += buf[0]
+    helped += sum(buf[1:4096])
+print("leader", lead, "helpers", helped)
+assert helped >= 0.4 * (lead + helped)
+"""
+
+
+def test_emulated_more_chunks_than_helpers():
+    """A row of 25 chunks with a leader and two helpers resident at even speeds: the helpers, which are
+    as many as fit, take about two thirds of every request's chunks, where helpers bound to one chunk
+    each left all but two of them to the leader."""
+    lib = _build_emu(concurrent=True, GSPAR_EMU_HELPERS="2")
+    r = subprocess.run([sys.executable, "-c", _SHARE, lib, os.path.join(HERE, "emu")],
+                       env=dict(os.environ, EMU_RESIDENT="3", EMU_EVEN="1"), capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-2000:])

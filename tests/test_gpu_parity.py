@@ -410,6 +410,34 @@ def test_candidate_band_region_overflow(gs, solver):
         assert float(plan.lam[0].item()) == sol.lam and int(plan.k[0].item()) == sol.k
 
 
+@pytest.mark.parametrize("solver", ["greedy", "exact"])
+def test_more_chunks_than_helpers(gs, solver):
+    """A row of more histogram chunks than the solver has helpers (2^29 coordinates and a few chunks),
+    with the candidate band, and without one, where every request goes over the row: identical results."""
+    d = (1 << 29) + 3 * (1 << 20) + 12
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+    g = torch.randn(d, generator=gen, device="cuda")
+    g[::97] *= 50.0
+    g = g.reshape(1, d)
+    rho = torch.tensor([0.02], dtype=torch.float64, device="cuda")
+    seeds = torch.tensor([9], dtype=torch.int64, device="cuda")
+    _say(f"[chunks] {solver} d={d}")
+    res = []
+    for size in (gs.workspace_bytes(1, d, solver), gs.workspace_bytes(1, d, "variance")):
+        plan = gs.Plan(1, d, solver=solver, cap_per_row=gs.capacity_hint(d, 0.02))
+        plan.ws = plan.ws[:size]
+        plan.run(g, rho, seeds)
+        torch.cuda.synchronize()
+        n, k, src = int(plan.nnz[0].item()), int(plan.k[0].item()), _row_state(plan.ws)["src"]
+        _say(f"[chunks] {size} bytes: src={src} nnz={n} k={k}")
+        assert int(plan.flags[0].item()) == 0 and src == (1 if not res else 0) and k > 0
+        res.append((n, float(plan.lam[0].item()), k, plan.idx[0, :n].clone(), plan.val[0, :n].clone()))
+        del plan
+    a, b = res
+    assert a[:3] == b[:3] and torch.equal(a[3], b[3]) and torch.equal(a[4], b[4])
+
+
 def test_candidate_band_with_smaller_workspaces(gs):
     """The same long row with the full workspace (band used), a workspace with room for 2^16
     candidates only (the band overflows and is dropped) and the fixed part alone (no band): the
