@@ -780,6 +780,7 @@ struct SolveLds {
   BinOut bin[2], ans;  // the bins b1 and b2 as their owners see them; the answer so far
   uint64_t word;       // a helper's next request (0: leave)
   uint32_t cmd;        // whether the chunk at hand was taken by this workgroup
+  uint32_t err;        // kFlagInternal when a shift of the leader's exact sums lay outside its range
   uint32_t nbuf, base;  // keys of the chunk at hand that belong in the list, and their place there
   uint32_t keys[kPassBuf];  // the leader's first listed keys
   union {
@@ -826,7 +827,7 @@ GS_DI double exact_sum(S& s, int E, uint64_t part) {
   if (v) {
     int at;
     uint64_t x[3];
-    dig_split(v, binade_shift(t), 255, at, x);
+    if (dig_split(v, binade_shift(t), 255, at, x)) s.err = kFlagInternal;
 #pragma unroll
     for (int i = 0; i < 3; ++i) atomicAdd(&s.dig[at + i], (unsigned long long)x[i]);
   }
@@ -846,12 +847,13 @@ GS_DI double exact_sum_sq(S& s, int E, uint64_t ph, uint64_t pl) {
   if (vh | vl) {
     int at;
     uint64_t x[3];
-    dig_split(vh, 2 * binade_shift(t) + 24, 2 * 255 + 24, at, x);
+    uint32_t err = dig_split(vh, 2 * binade_shift(t) + 24, 2 * 255 + 24, at, x);
 #pragma unroll
     for (int i = 0; i < 3; ++i) atomicAdd(&s.dig[at + i], (unsigned long long)x[i]);
-    dig_split(vl, 2 * binade_shift(t), 2 * 255, at, x);
+    err |= dig_split(vl, 2 * binade_shift(t), 2 * 255, at, x);
 #pragma unroll
     for (int i = 0; i < 3; ++i) atomicAdd(&s.dig[at + i], (unsigned long long)x[i]);
+    if (err) s.err = err;
   }
   __syncthreads();
   const double r = uni(dig_round<kDigSq>(s.dig, -298));
@@ -1528,6 +1530,7 @@ GS_DI void lead_row(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc
   uint32_t nz = (uint32_t)cnt;
   for (int o = 32; o > 0; o >>= 1) nz += __shfl_xor(nz, o);
   if ((t & 63) == 0) s.rc[t >> 6] = nz;
+  if (t == 0) s.err = 0;
   __syncthreads();
   uint64_t nnz = 0;
 #pragma unroll
@@ -1557,6 +1560,7 @@ GS_DI void lead_row(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc
       if constexpr (VAR) A2 = exact_sum_sq(s, 254, s.qh[254], s.ql[254]);
       flags |= solve_levels<VAR>(a, s, ctl, sc, row, base, len, L, B, nnz, A2, lam, tcap);
     }
+    flags |= s.err;  // (the sums end with a barrier)
   }
   if (t == 0) {
     st_agent(&ctl->req, (uint64_t)kReqDone << 32);
