@@ -467,6 +467,17 @@ __device__ __forceinline__ uint32_t* creg_of(const Args& a, int64_t r) { return 
 
 
 
+// Orders the LDS accesses of a wave's lanes for the compiler (the wave issues them in order as it is):
+// what a lane reads or writes before, it does before any lane's accesses after. No instruction.
+__device__ __forceinline__ void wave_sync() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#endif
+  __builtin_amdgcn_wave_barrier();
+}
+// LDS bytes reused as 16-bit words.
+typedef uint16_t __attribute__((may_alias)) gs_u16;
+
 // Streaming accesses: g is read once per pass and the outputs are written once, so those loads,
 // the probabilities' stores and the sampling pass's staged stores (whole runs of consecutive words)
 // carry the non-temporal hint and do not displace what the caches keep (the level-1 copies,
@@ -2623,23 +2634,23 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
       const int32_t t0c = (int32_t)(part * (int64_t)kTileElems);
       // One round (most waves) needs no bound in its loop.
       auto staged = [&](uint64_t mask, uint32_t j, uint32_t n, auto&& more, auto&& put) {
-        uint16_t* const si = reinterpret_cast<uint16_t*>(&s_code[kk][wv * (kWaveElems / 4)]);
-        uint16_t* const sc = reinterpret_cast<uint16_t*>(&s_capb[kk][wv * (kWaveElems / 4)]);
+        gs_u16* const si = reinterpret_cast<gs_u16*>(&s_code[kk][wv * (kWaveElems / 4)]);
+        gs_u16* const sc = reinterpret_cast<gs_u16*>(&s_capb[kk][wv * (kWaveElems / 4)]);
         uint32_t m0 = (uint32_t)mask, m1 = (uint32_t)(mask >> 32);
         // this lane's survivors of one half of its coordinates
         auto enter = [&](auto bounded, uint32_t& m, uint32_t neg, uint32_t c0, uint32_t w0) {
           while (m) {
             if (decltype(bounded)::value && j - w0 >= (uint32_t)kStageEmit) break;
             const int b = __builtin_ctz(m);
-            si[j - w0] = (uint16_t)(c0 + b);
-            sc[j - w0] = (uint16_t)(((neg >> b) & 1u) << 15);
+            si[j - w0] = (gs_u16)(c0 + b);
+            sc[j - w0] = (gs_u16)(((neg >> b) & 1u) << 15);
             ++j;
             m &= m - 1u;
           }
         };
         const uint32_t n0 = (uint32_t)nm, n1 = (uint32_t)(nm >> 32), c0 = (uint32_t)(64 * tid);
         for (uint32_t w0 = 0; w0 < n; w0 += (uint32_t)kStageEmit) {
-          __builtin_amdgcn_wave_barrier();
+          wave_sync();
           if (n <= (uint32_t)kStageEmit) {
             enter(std::false_type{}, m0, n0, c0, 0u);
             enter(std::false_type{}, m1, n1, c0 + 32u, 0u);
@@ -2648,7 +2659,7 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
             if (!m0) enter(std::true_type{}, m1, n1, c0 + 32u, w0);
           }
           more(sc, w0);
-          __builtin_amdgcn_wave_barrier();
+          wave_sync();
           const uint32_t end = min(n - w0, (uint32_t)kStageEmit);
           for (uint32_t i = (uint32_t)lane; i < end; i += 64u) put(w0 + i, si[i], sc[i]);
         }
@@ -2689,7 +2700,7 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
           gchar* __restrict__ bv = uniform_ptr(ov) + 4u * (uint32_t)wpos;
           staged(
               sm, lpre, s_wsel[kk][wv],
-              [&](uint16_t* sc, uint32_t w0) {
+              [&](gs_u16* sc, uint32_t w0) {
                 while (mc) {
                   const int b = __ffsll((unsigned long long)mc) - 1;
                   const uint32_t at = lpre + (uint32_t)__popcll(sm & ((1ull << b) - 1ull)) - w0;
@@ -2697,7 +2708,7 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
                   const int gi = b >> 2;
                   const uint32_t cb = (cwd[gi >> 2] >> (8 * (gi & 3))) & 0xFFu;
                   const uint32_t slot = (cb >> 4) + (uint32_t)__popc(cb & ((1u << (b & 3)) - 1u));
-                  sc[at] = (uint16_t)(0x4000u | ((uint32_t)(nm >> b) << 15) |
+                  sc[at] = (gs_u16)(0x4000u | ((uint32_t)(nm >> b) << 15) |
                                       (uint32_t)(((16 * tid + gi) & 63) * kLaneStride + slot));
                   mc &= mc - 1;
                 }
@@ -2814,7 +2825,7 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
           if (wpos + btot <= (uint64_t)a.cap_b && wpos + btot <= ((uint64_t)1 << 30)) {
             gchar* __restrict__ bo = uniform_ptr(ob) + 4u * (uint32_t)wpos;
             staged(
-                bm, (uint32_t)(pb - wpos), btot, [](uint16_t*, uint32_t) {},
+                bm, (uint32_t)(pb - wpos), btot, [](gs_u16*, uint32_t) {},
                 [&](uint32_t i, uint32_t x, uint32_t cc) {
                   GS_STORE_STREAM((GS_GLOBAL(int32_t)*)(bo + 4u * i), (int32_t)((uint32_t)t0c + x + (cc << 16)));
                 });
