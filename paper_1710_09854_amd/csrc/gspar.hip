@@ -2222,6 +2222,15 @@ constexpr int kSampleBatch = 8;  // float4 loads in flight per lane in the sampl
 // Survivors of a wave's quarter tile (of 4096) above which emission goes by groups: the staged loops take
 // as many steps as the fullest lane of each round, which grows with the square of the density.
 constexpr int kDenseEmit = 2048;
+// Capped survivors above which the compaction of a wave that has more of them on a lane than its LDS row
+// holds, and more than kStageEmit survivors in all, goes by groups too: its other choice reads them from
+// g in a loop that stores one survivor per lane and step, and each read waits for the stores before it.
+// us a call by groups and one by one, with the capped survivors of a wave: 16 x 2^20 Student-t(2) rows,
+// greedy, 122 and 102 at 164, 131 and 118 at 213, 134 and 143 at 229, 143 and 316 at 352; 2^26
+// coordinates 290 and 240 at 164, 422 and 391 at 213, 439 and 489 at 229, 475 and 1,079 at 352; normal
+// rows under the variance budget (eps = 0.5) 177 and 407 at 303. With at most kStageEmit survivors,
+// all of them capped, one by one is better throughout (16 x 2^20: 95 and 85 at 410).
+constexpr int kGroupEmit = 224;
 // Survivors staged in LDS at a time: 4-byte entries in the quarter's 2 KB of code and capped-survivor
 // bytes, free once every lane has read its own.
 constexpr int kStageEmit = 512;
@@ -2719,7 +2728,9 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
                 GS_STORE_STREAM((GS_GLOBAL(int32_t)*)(bi + 4u * i), t0c + (int32_t)x);
                 GS_STORE_STREAM((GS_GLOBAL(float)*)(bv + 4u * i), val);
               });
-        } else if (s_wsel[kk][wv] > (uint32_t)kDenseEmit) {
+        } else if (s_wsel[kk][wv] > (uint32_t)kDenseEmit ||
+                   (!lds_values && s_wsel[kk][wv] > (uint32_t)kStageEmit &&
+                    s_wcap[kk][wv] > (uint32_t)kGroupEmit)) {
           // many survivors: lane l takes the wave's groups 64 j + l (the order of phase 1 and of
           // this lane's capped-value row), one step j at a time, so the stores of a step fall on a
           // few consecutive lines instead of one line per lane

@@ -469,3 +469,40 @@ def test_emulated_more_chunks_than_helpers():
     r = subprocess.run([sys.executable, "-c", _SHARE, lib, os.path.join(HERE, "emu")],
                        env=dict(os.environ, EMU_RESIDENT="3", EMU_EVEN="1"), capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-2000:])
+
+
+@pytest.mark.parametrize("caps, rho", [(220, 0.1), (220, 0.3), (228, 0.1), (228, 0.3), (228, 0.55), (520, 0.126), (520, 0.12)])
+@pytest.mark.parametrize("room", [1.0, 0.6])
+def test_emulated_waves_that_cannot_be_staged(emu_lib, caps, rho, room):
+    """Waves some of whose lanes have more capped values than their LDS rows hold, on both sides of the
+    capped and of the total survivor counts at which their emission goes by groups, with room for every
+    survivor and with a capacity that ends inside a wave: the compaction is the oracle's sample, the
+    hybrid coding has the same survivors, and what the capacity cuts off is the tail."""
+    L = runner.load(emu_lib)
+    import oracle
+    from oracle.compare import compare_sample
+
+    # each wave (4,096 coordinates) has `caps` large magnitudes: 12 on its first lane, the rest anywhere
+    r = np.random.default_rng(caps)
+    g = (r.standard_normal(2 * 16384 + 123) * 1e-3).astype(np.float32)
+    for w in range(8):
+        at = 4096 * w + np.concatenate([256 * np.arange(3)[:, None] + np.arange(4)]).reshape(-1)
+        rest = np.setdiff1d(np.arange(4096 * w, 4096 * (w + 1)), at)
+        at = np.concatenate([at, r.choice(rest, caps - 12, replace=False)])
+        g[at] = (100.0 + 8.0 * r.random(caps)) * r.choice([-1.0, 1.0], caps)
+    rho = max(rho, caps / 4096.0 + 1e-4)
+    sol = oracle.solve(g, rho, "exact", 2)
+    idx, val, n, lam, k, fl = runner.sample_row(L, g, rho, "exact", 17, cap=g.size)
+    assert fl == 0 and k >= 8 * caps
+    compare_sample(g, sol.p, 17, idx, val, n, lam, sol.lam)
+    cap = int(n * room)
+    i2, v2, n2, _, _, f2 = runner.sample_row(L, g, rho, "exact", 17, cap=cap)
+    assert n2 == n and f2 == (0 if cap == n else 2)
+    assert np.array_equal(i2, idx[:cap]) and np.array_equal(v2, val[:cap])
+    big = np.abs(g) * lam >= 1.0
+    ia, va, na, cb, nb, inv, q, _, f3 = runner.hybrid_batched(L, g[None, :], [rho], [17], "exact", cap=cap)
+    a, b = min(int(na[0]), cap), min(int(nb[0]), cap)
+    assert na[0] + nb[0] == n and na[0] == k and f3[0] == (0 if max(na[0], nb[0]) <= cap else 2)
+    qa, qb = idx[big[idx]], idx[~big[idx]]
+    assert np.array_equal(ia[0, :a], qa[:a]) and np.array_equal(va[0, :a], g[qa[:a]])
+    assert np.array_equal(cb[0, :b] & 0x7FFFFFFF, qb[:b]) and np.array_equal(cb[0, :b] < 0, g[qb[:b]] < 0)
