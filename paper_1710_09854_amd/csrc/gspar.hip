@@ -258,7 +258,8 @@ struct ChunkState {
   uint32_t pad;
   uint64_t qsig;
 };
-constexpr int kListMax = (int)((kScratchBytes - kWC * sizeof(WinBins) - kMaxChunks * sizeof(ChunkState)) / sizeof(uint32_t));
+constexpr int kListMax =
+    (int)((kScratchBytes - kWC * sizeof(WinBins) - kMaxChunks * sizeof(ChunkState)) / sizeof(uint32_t));
 // Keys of a range up to which it is listed instead of binned again (a build may lower it to exercise
 // the windows on small inputs).
 #ifndef GSPAR_LIST_CAP
@@ -488,9 +489,10 @@ typedef uint16_t __attribute__((may_alias)) gs_u16;
 //
 // A row may start at any float (odd leading dimensions, segments, views): global memory takes
 // 16-byte accesses at any multiple of 4 bytes, so the vector type below asks for no more and every
-// row streams through the same loops: 5 rows of 300,007 in a packed matrix take 70 us a call with
-// them against 77 with a scalar-load copy of every loop, one odd row of a few million coordinates
-// whose solver refines 98 against 159 us; rows on 16-byte boundaries issue the same instructions.
+// row streams through the same loops. With a scalar-load copy of every loop for such rows, and the
+// solver still in several launches, 5 rows of 300,007 in a packed matrix took 77 us a call against 70,
+// one odd row of a few million coordinates whose solver refines 159 against 98 us; rows on 16-byte
+// boundaries issue the same instructions.
 #if defined(__HIP_DEVICE_COMPILE__)
 typedef float gs_f4v __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ float4 load_vec(const float* p) {
@@ -539,11 +541,12 @@ __device__ __forceinline__ uint32_t load4(const float* __restrict__ row, int64_t
 
 // Visits the coordinates [beg, end) of one row (beg a multiple of 4) with the NT threads of a
 // workgroup, calling f(q, v, m) for each float4 group q (m: bit c set when coordinate 4q+c exists).
-// Blocks of U groups per thread are loaded unconditionally, all issued before any group is processed, so U loads per thread stay in flight; the last block clamps its addresses
-// to the last whole group and masks the values, and a trailing partial group is loaded by one
-// thread with scalar loads and visited by the whole first wave. No memory access sits under a
-// divergent branch, which would make the compiler wait for every outstanding load. Every call of f
-// is made by whole waves, so f may use cross-lane operations.
+// Blocks of U groups per thread are loaded unconditionally, all issued before any group is processed,
+// so U loads per thread stay in flight; the last block clamps its addresses to the last whole group
+// and masks the values, and a trailing partial group is loaded by one thread with scalar loads and
+// visited by the whole first wave. No memory access sits under a divergent branch, which would make
+// the compiler wait for every outstanding load. Every call of f is made by whole waves, so f may use
+// cross-lane operations.
 template <int U, int NT, typename F>
 __device__ __forceinline__ void stream_groups(const float* __restrict__ row, int64_t beg, int64_t end, F&& f) {
   const int64_t qfull = end / 4;  // groups [beg/4, qfull) lie entirely inside [beg, end)
@@ -1082,8 +1085,8 @@ struct Lead {
 // Makes a request, works on it and waits until all of it is done. `key`: the range's first key, for
 // kReqCount the query key; `n`: the range's number of keys. The range lies in one binade.
 template <bool VAR>
-GS_DI void request(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc, int64_t row, int64_t base, int64_t len,
-                   Lead& L, uint32_t kind, uint32_t key, uint32_t shift, uint32_t n) {
+GS_DI void request(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc, int64_t row, int64_t base,
+                   int64_t len, Lead& L, uint32_t kind, uint32_t key, uint32_t shift, uint32_t n) {
   const uint32_t e = key >> 23;
   L.from = L.banded && (e << 23) >= L.blo && ((e + 1) << 23) <= L.bhi ? 1u : 0u;
   ++L.req;
@@ -1112,7 +1115,8 @@ GS_DI void request(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc,
   for (uint32_t c0 = 0; c0 < chunks; c0 += kNT) {
     const uint32_t c = c0 + threadIdx.x;
     while (true) {
-      if (f != 0 || c0 != 0) f = block_find<false>(s, L.turn, c > 0 && c < chunks && ld_agent(&sc->chunk[c].taken) < P.num);
+      if (f != 0 || c0 != 0)
+        f = block_find<false>(s, L.turn, c > 0 && c < chunks && ld_agent(&sc->chunk[c].taken) < P.num);
       if (f == kNT) break;
       pass_chunk<VAR>(a, s, ctl, sc, row, base, len, c0 + (uint32_t)f, P, c0 + (uint32_t)f == 0);
       __syncthreads();
@@ -1162,7 +1166,8 @@ GS_DI void count_above(const Args& a, SolveLds<false>& s, RowCtl* ctl, RowScratc
                        int64_t len, Lead& L, uint32_t t, uint64_t& qc, uint64_t& qs) {
   const uint32_t lo = (t >> 23) << 23, n = s.cnt[t >> 23];
   if (L.lspan == 0 || L.llo != lo) {
-    request<false>(a, s, ctl, sc, row, base, len, L, n > kListCap ? kReqCount : kReqList, n > kListCap ? t : lo, 14, n);
+    const bool list = n <= kListCap;
+    request<false>(a, s, ctl, sc, row, base, len, L, list ? kReqList : kReqCount, list ? lo : t, 14, n);
   }
   uint32_t c = 0;
   uint64_t g = 0;
@@ -1940,7 +1945,7 @@ __global__ void __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) k
   // When some lane could not take a whole group's keys the wave flushes every lane's buffer into
   // this workgroup's own region of the row's candidate buffer, at a place taken from an LDS
   // counter, lanes in order by a wave prefix; keys that would pass the region's end are dropped and
-  // the region is marked overflowed, so the first solve does not use the band.
+  // the region is marked overflowed, so the solver does not use the band.
   uint32_t* const lbuf = &s_cand[CAND ? threadIdx.x >> 6 : 0][CAND ? lane * kCandLane : 0];
   uint32_t lcnt = 0;
   if (CAND && threadIdx.x == 0) s_rcnt = 0;
@@ -2074,7 +2079,7 @@ __global__ void __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) k
 // batch; for a segmented call a workgroup per map entry, of which those of every help_step-th block help.
 // Two workgroups of it fit a compute unit (128 registers), so that all 512 of 16 rows' are resident:
 // with one, under the variance budget, half of the rows had no helpers until the others were solved
-// (the kernel took 140 us on 16 rows of 2^20, and takes 66).
+// (the kernel took 140 us on 16 rows of 2^20, and takes 63).
 template <int SOLVER>
 __global__ void __launch_bounds__(kNT, 4) k_solve(Args a) {
   constexpr bool VAR = SOLVER == GSPAR_VARIANCE;
@@ -2207,15 +2212,15 @@ __device__ uint64_t wave_tile_aggregate(const TileCtx& c, int64_t part, int lane
 // the wave's lanes places it, and it writes only its own set bits, through an LDS staging area of
 // kStageEmit survivors that the wave then stores with consecutive lanes on consecutive slots (up to
 // kDenseEmit survivors of its 4,096; rows of the variance budget that keep a quarter of 16 x 2^20
-// coordinates take 37 us this way against 62 with one store per lane and survivor). Phase 2 reads no global memory (a load would wait for every store issued
-// before it), except in a wave where some lane kept more capped values than its LDS row holds (a
-// separate instantiation).
+// coordinates take 37 us this way against 63 with one store per lane and survivor). Phase 2 reads no
+// global memory (a load would wait for every store issued before it), except in a wave where some lane
+// kept more capped values than its LDS row holds (a separate instantiation).
 // Capped survivors' values are kept in LDS by the phase-1 lane that decided them, kLaneCap per
 // lane and tile (rows padded to kLaneStride floats so that lanes fall on different banks); a wave
 // with a lane past that reads its capped values from global memory in phase 2.
 // A group with one capped coordinate (nearly all that have any) keeps its largest magnitude, known
-// already, in one store: on 2^28 coordinates with one per cent of outliers the pass takes 242 us at
-// rho = 0.01 and 273 at 0.1 against 252 and 279 with a store for each of the four.
+// already, in one store: on 2^28 coordinates with one per cent of outliers, at rho = 0.1, the pass takes
+// 274 us against 280 with a store for each of the four.
 constexpr int kLaneCap = 8;
 constexpr int kLaneStride = kLaneCap + 1;
 constexpr int kSampleBatch = 8;  // float4 loads in flight per lane in the sampling pass
@@ -2302,11 +2307,13 @@ __device__ __forceinline__ FastCtx fast_ctx(double lam) {
 // fl(x - lamf |g|) is within 2^-24 x + 2^-23 t + its own rounding of x - t, 1024 in all where x and t are
 // at most 2^32 (and t beyond that only makes it more negative), so outside +-1024 its sign decides;
 // within (about one wave in eight thousand groups) the group is decided in fp64. Two instructions per
-// coordinate and one sign gather per group take the place of five and seven: on 2^28 coordinates the
-// pass takes 232 against 242 us (rho = 0.01) and 274 against 290 (0.1), on 16 x 2^20 18.5 against 20.
+// coordinate and one sign gather per group take the place of five and seven: by this alone the pass went
+// from 262 to 241 us on 2^28 coordinates at rho = 0.01, from 310 to 285 at 0.1, and from 20.1 to 19.1
+// on 16 x 2^20 (kernel times within a call; from run to run they differ by some 2 per cent).
 //
 // Returns bit k of byte k for each survivor.
-__device__ __forceinline__ uint32_t decide_fast(int64_t q, const float v[4], const FastCtx& f, uint32_t k0, uint32_t k1) {
+__device__ __forceinline__ uint32_t decide_fast(int64_t q, const float v[4], const FastCtx& f, uint32_t k0,
+                                                uint32_t k1) {
   // rows are shorter than 2^31 coordinates, so the counter's high word floor(i/4) >> 32 is 0; with
   // that known the first rounds fold into fewer vector operations
   uint32_t x0 = (uint32_t)q, x1 = 0, x2 = 0, x3 = 0;
@@ -2356,7 +2363,7 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
     part0 = (int64_t)(blockIdx.x % wpr) * K;
   } else {
     // the map built by k_init holds only workgroups with tiles; a map that does not have the
-    // launched shape leaves every row to the first solve
+    // launched shape leaves every row to the solver
     if (*segok_of(a) != 1) return;
     const uint64_t e = reinterpret_cast<const uint64_t*>(a.ws + a.lay.tmap)[blockIdx.x];
     row = (int64_t)(e >> 32);
@@ -3089,10 +3096,13 @@ static int launch_solve(Args& a, hipStream_t s) {
   const int64_t nblocks = a.seg ? a.seg_blocks : a.rows * a.nb;
   const dim3 grid((unsigned)nblocks);
   if (nblocks > 0) {
-    launch(kcStats, sq ? k_stats<true, false> : cand ? k_stats<false, true> : k_stats<false, false>, grid, dim3(kNT), s, a);
+    launch(kcStats, sq ? k_stats<true, false> : cand ? k_stats<false, true> : k_stats<false, false>, grid, dim3(kNT),
+           s, a);
   }
   const int64_t helpers = a.seg ? a.seg_blocks : a.rows * a.helpers;
-  launch(kcSolve, sq ? k_solve<GSPAR_VARIANCE> : a.solver == GSPAR_GREEDY ? k_solve<GSPAR_GREEDY> : k_solve<GSPAR_EXACT>, dim3((unsigned)(a.rows + helpers)), dim3(kNT), s, a);
+  launch(kcSolve,
+         sq ? k_solve<GSPAR_VARIANCE> : a.solver == GSPAR_GREEDY ? k_solve<GSPAR_GREEDY> : k_solve<GSPAR_EXACT>,
+         dim3((unsigned)(a.rows + helpers)), dim3(kNT), s, a);
   return hipGetLastError() == hipSuccess ? GSPAR_OK : GSPAR_ERR_HIP;
 }
 

@@ -217,7 +217,7 @@ def tied_boundary(d=40000, n_hi=3000, n_zero=3000, seed=5):
 
 
 def check_ties(L, verbose=True):
-    """One capped test everywhere: the compaction (fast and scalar paths), the probabilities, the
+    """One capped test everywhere: the compaction (rows on and off a 16-byte boundary), the probabilities, the
     hybrid coding and the look-back's own recount all treat a coordinate with p_i = 1 as capped."""
     g = tied_boundary()
     hi = np.flatnonzero(np.abs(g) == 2)
@@ -229,7 +229,7 @@ def check_ties(L, verbose=True):
         assert fl == 0 and lam == sol.lam and k == sol.k, (solver, lam, sol.lam, k, sol.k)
         compare_sample(g, sol.p, 13, idx, val, n, lam, sol.lam)
         assert np.all(np.isin(hi, idx))  # every capped coordinate survives
-        # the same row at an unaligned start (scalar decisions everywhere)
+        # the same row at an unaligned start
         buf = np.zeros(g.size + 16, np.float32)
         base = (-buf.ctypes.data // 4) % 4 + 1
         view = buf[base:base + g.size]
@@ -305,7 +305,7 @@ def check_candidates(L, verbose=True):
                 if solver == "exact":
                     assert lam == sol.lam and k == sol.k, (name, rho, lam, sol.lam, k, sol.k)
                 if g.size % 4:
-                    # a row length that is not a multiple of 4 takes the scalar-load path: no band
+                    # a row length that is not a multiple of 4: no band
                     assert st["band_hi"] == st["band_lo"] and st["src"] == 0, (name, st)
                     continue
                 if st["band_hi"] == st["band_lo"]:
@@ -514,8 +514,8 @@ def check_band_region_overflow(L, verbose=True):
     """A band row whose first statistics workgroup holds more band keys than its staging region:
     2^17 coordinates, a workspace with room for 2^16 candidates (16 regions of 4096 for chunks of
     8192), the first chunk's magnitudes uniform in [8, 16) and the rest 1e-3 N(0, 1), rho putting
-    1/lambda near 12. The band is predicted and collected, the overflowing region makes the first
-    solve drop it, the solver refines over the row, and the result equals the oracle's (lambda bit
+    1/lambda near 12. The band is predicted and collected, the overflowing region makes
+    the solver drop it and refine over the row, and the result equals the oracle's (lambda bit
     for bit for the exact solver)."""
     d = 1 << 17
     rng = np.random.default_rng(92)
@@ -534,7 +534,7 @@ def check_band_region_overflow(L, verbose=True):
                   f"cand={st['cand_n']} src={st['src']}", flush=True)
         assert fl == 0, fl
         # collected (the count exceeds the list's capacity: the overflowing region reserved past
-        # it), then dropped by the first solve, and no window read the candidates
+        # it), then dropped by the solver, and no window read the candidates
         assert st["cand_n"] > (1 << 16) and st["band_lo"] == st["band_hi"] == 0 and st["src"] == 0, st
         compare_sample(g, sol.p, 23, idx, val, n, lam, sol.lam)
         if solver == "exact":
@@ -636,8 +636,7 @@ def check_segmented(L, verbose=True):
     """Per-layer sparsification (Section 5.2) against the oracle segment by segment, aligned and
     unaligned offsets, empty and tiny layers, layers spanning several tiles, and device offsets
     that disagree with the host's."""
-    # offsets that are not all multiples of 4 (scalar path), then aligned ones (vector path); an
-    # unaligned g takes the scalar path too
+    # offsets that are not all multiples of 4, then aligned ones, then an unaligned g
     for lengths, shift in (([3000, 0, 3, 16384 + 8, 1, 5000, 4], 0), ([4096, 16388, 12, 12000, 0, 8], 0)):
         g, off = layered(lengths, 600 + len(lengths))
         segs = len(lengths)
@@ -771,7 +770,7 @@ def check_aggregate(L, verbose=True):
 def check_asan_subset(L, verbose=True):
     """A bounded selection for the AddressSanitizer build: every kernel family once, on shapes that
     reach the ragged ends. A padded batch whose rows end in a partial group on the vector path
-    (long enough for a candidate band in the emulation build), the scalar path, the variance budget,
+    (long enough for a candidate band in the emulation build), unaligned rows, the variance budget,
     segments on both paths with the hybrid coding, and aggregation of the batch's lists."""
     rows, d = 2, 12003
     g2 = np.stack([W.t_mixture(d, 310 + r) for r in range(rows)])
@@ -868,7 +867,7 @@ def run_extra(path, verbose=True, lite=False):
                 assert one[3] == lam[r]
     idx, val, nnz, lam, k, fl = batched(L, g2[:2], [0.1, 1.5], [1, 2], "greedy")
     assert fl[1] & 8 and nnz[1] == 0 and fl[0] == 0 and nnz[0] > 0
-    # unaligned row start (scalar-load path)
+    # unaligned row start
     g = W.t_mixture(20001, 61)
     buf = np.zeros(20002 + 16, np.float32)
     base = (-buf.ctypes.data // 4) % 4 + 1  # a start that is not 16-byte aligned

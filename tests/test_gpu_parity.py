@@ -1,6 +1,6 @@
 """GPU parity: the HIP path (through the C ABI) against the oracle, element by element, at sizes
 the oracle finishes in seconds that still span many tiles and ragged tails, plus edge cases,
-batching, determinism, capacity overflow, the unaligned (scalar-load) path and sampling
+batching, determinism, capacity overflow, rows off a 16-byte boundary and sampling
 statistics. Rule: index sets equal except where |u_i - p_i| <= 1e-6, values to rel 1e-5, lambda
 to rel 1e-9, probabilities to 1e-6 absolute."""
 import sys
@@ -400,7 +400,7 @@ def test_candidate_band_region_overflow(gs, solver):
          f"src={st['src']} nnz={n} k={int(plan.k[0].item())}")
     assert int(plan.flags[0].item()) == 0
     # collected (the count exceeds the list's capacity, d / 16 keys: the overflowing region
-    # reserved past it), then dropped by the first solve, and no window read the candidates
+    # reserved past it), then dropped by the solver, and no window read the candidates
     assert st["cand_n"] > d // 16 and st["band_lo"] == st["band_hi"] == 0 and st["src"] == 0
     sol = oracle.solve(g, rho, solver, 2)
     assert sol.k > 0
@@ -528,7 +528,8 @@ def test_capacity_boundaries(gs):
             assert torch.equal(out.idx[:cap], ref.idx[:cap]) and torch.equal(out.val[:cap], ref.val[:cap])
 
 
-def test_unaligned_scalar_path(gs):
+def test_unaligned_row(gs):
+    """A row that starts 4 bytes past a 16-byte boundary against the same row on one."""
     g = W.t_mixture(100001, 61)
     big = torch.from_numpy(np.concatenate([np.zeros(1, np.float32), g])).cuda()
     view = big[1:]
@@ -726,7 +727,7 @@ def test_random_rows_hybrid_and_probs(gs):
 
 def test_random_batches(gs):
     """Thirty seeded random batches: 1 to 24 rows of one random length (1 to ~100 K), stored with a
-    random padding of the leading dimension (so both the vector and the scalar load paths occur),
+    random padding of the leading dimension (so rows start on and off 16-byte boundaries),
     a random density per row and one solver per batch; every row against the oracle under the
     parity rule (lambda bit for bit for the exact solver)."""
     rng = np.random.default_rng(4048)
