@@ -726,8 +726,14 @@ GS_DI T uni(T v) {
 #endif
   return v;
 }
-// Every access of this wave so far has completed.
-GS_DI void wait_own() { __builtin_amdgcn_s_waitcnt(0); }
+// Every access of this wave so far has completed. (The fence is for the compiler, which may otherwise
+// take the wait to have nothing to do with memory: no instruction.)
+GS_DI void wait_own() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#endif
+  __builtin_amdgcn_s_waitcnt(0);
+}
 
 // One request. The leader announces it as one word, so that a helper needs no second look:
 // bits 0-31 the range's first key (kReqCount: the query key), 32-39 its number, 40-41 its kind, 42
