@@ -665,12 +665,11 @@ __device__ __forceinline__ uint32_t wave_prefix_bits(uint32_t x, uint32_t& total
 // inside a binade that holds several keys) the keys of that binade, which may take a pass over the
 // row. The leader decides everything; a pass over the row (or over its candidates) is a request in
 // the row's control block that every workgroup of the row takes chunks of. One launch does it all:
-// a row that needs no pass costs one short kernel (9-10 us), where a launch for every possible
-// pass and solve cost 23 us (11 us for the first solve, the rest idle kernels). A call on 65,536
-// coordinates takes 26.8 us with it against 38.9 before, the 54 layers of a residual network 73.7
-// against 96.6; 5 rows of 300,007 whose solver lists a binade 44 against 70, 2^28 coordinates 457
-// against 483 (exact, rho = 0.01) and 539 against 571 (greedy, rho = 0.1), 16 rows of 2^20 under the
-// variance budget 162 against 266.
+// a row that needs no pass costs one short kernel (8-9 us), where a launch for every possible
+// pass and solve cost 23 us (11 us for the first solve, the rest idle kernels). By this change alone a
+// call on 65,536 coordinates went from 38.9 us to 26.8, the 54 layers of a residual network from 96.6
+// to 73.7, 5 rows of 300,007 whose solver lists a binade from 70 to 44, and 2^28 coordinates from 483
+// to 457 (exact, rho = 0.01) and from 571 to 539 (greedy, rho = 0.1).
 //
 // Waiting: a chunk is taken with an atomic on its own word by its helper, or by the leader once it
 // has done its own, so a chunk is only ever held by a running workgroup and the leader waits only
