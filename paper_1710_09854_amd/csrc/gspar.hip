@@ -2232,15 +2232,16 @@ constexpr int kSampleBatch = 8;  // float4 loads in flight per lane in the sampl
 // Survivors of a wave's quarter tile (of 4096) above which emission goes by groups: the staged loops take
 // as many steps as the fullest lane of each round, which grows with the square of the density.
 constexpr int kDenseEmit = 2048;
-// Capped survivors above which the compaction of a wave that has more of them on a lane than its LDS row
-// holds, and more than kStageEmit survivors in all, goes by groups too: its other choice reads them from
-// g in a loop that stores one survivor per lane and step, and each read waits for the stores before it.
-// us a call by groups and one by one, with the capped survivors of a wave: 16 x 2^20 Student-t(2) rows,
-// greedy, 122 and 102 at 164, 131 and 118 at 213, 134 and 143 at 229, 143 and 316 at 352; 2^26
-// coordinates 290 and 240 at 164, 422 and 391 at 213, 439 and 489 at 229, 475 and 1,079 at 352; normal
-// rows under the variance budget (eps = 0.5) 177 and 407 at 303. With at most kStageEmit survivors,
-// all of them capped, one by one is better throughout (16 x 2^20: 95 and 85 at 410).
-constexpr int kGroupEmit = 224;
+// The compaction of a wave that has more capped survivors on a lane than its LDS row holds goes by groups
+// above kGroupEmit survivors of which more than kGroupCapped are capped: its other choice stores one
+// survivor per lane and step and reads every capped one from g, and each read waits for the stores
+// before it (by groups, one read serves a group). us a call by groups and one by one, with the capped
+// survivors of a wave: 16 x 2^20 Student-t(2) rows, greedy, 97 and 95 at 164, 107 and 118 at 213, 119
+// and 315 at 352; 2^26 coordinates 247 and 241 at 164, 348 and 393 at 213, 369 and 1,076 at 352; normal
+// rows under the variance budget (eps = 0.5) 151 and 407 at 303. Where all survivors are capped: 16 x
+// 2^20 72 and 70 at 328, 70 and 77 at 369, 70 and 98 at 492, 2^26 238 and 230, 237 and 250, 238 and 326.
+constexpr int kGroupEmit = 352;
+constexpr int kGroupCapped = 192;
 // Survivors staged in LDS at a time: 4-byte entries in the quarter's 2 KB of code and capped-survivor
 // bytes, free once every lane has read its own.
 constexpr int kStageEmit = 512;
@@ -2741,8 +2742,8 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
                 GS_STORE_STREAM((GS_GLOBAL(float)*)(bv + 4u * i), val);
               });
         } else if (s_wsel[kk][wv] > (uint32_t)kDenseEmit ||
-                   (!lds_values && s_wsel[kk][wv] > (uint32_t)kStageEmit &&
-                    s_wcap[kk][wv] > (uint32_t)kGroupEmit)) {
+                   (!lds_values && s_wsel[kk][wv] > (uint32_t)kGroupEmit &&
+                    s_wcap[kk][wv] > (uint32_t)kGroupCapped)) {
           // many survivors: lane l takes the wave's groups 64 j + l (the order of phase 1 and of
           // this lane's capped-value row), one step j at a time, so the stores of a step fall on a
           // few consecutive lines instead of one line per lane
@@ -2757,6 +2758,9 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
             const uint32_t sp = wave_prefix_bits<3>((uint32_t)__popc(sel), stot);
             uint64_t p = base0 + carry + sp;
             const int64_t eq = part * (int64_t)kTileElems + 4 * (int64_t)q;
+            // one read of the group for all its capped values: a read waits for the stores before it
+            float gv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (!lds_values && cap) load4(c.row, eq >> 2, c.d, gv);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
               if ((sel >> k) & 1) {
@@ -2764,7 +2768,7 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
                 if ((cap >> k) & 1)
                   val = lds_values ? signed_as(s_capl[kk][wv][lane * kLaneStride + (cb >> 4) +
                                                               __popc(cap & ((1u << k) - 1u))], (neg >> k) << 31)
-                                   : c.row[eq + k];
+                                   : gv[k];
                 if ((int64_t)p < a.cap) {
                   oi[p] = (int32_t)(eq + k);
                   ov[p] = val;
@@ -2819,13 +2823,15 @@ __global__ void __launch_bounds__(kTileThreads) k_sample(Args a) {
             uint64_t qa = pa0 + wave_prefix_bits<3>((uint32_t)__popc(cap), atot);
             uint64_t qb = pb0 + wave_prefix_bits<3>((uint32_t)__popc(oth), btot2);
             const int64_t eq = part * (int64_t)kTileElems + 4 * (int64_t)q;
+            float gv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (!lds_values && cap) load4(c.row, eq >> 2, c.d, gv);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
               if ((cap >> k) & 1) {
                 const float val =
                     lds_values ? signed_as(s_capl[kk][wv][lane * kLaneStride + (cb >> 4) +
                                                           __popc(cap & ((1u << k) - 1u))], (neg >> k) << 31)
-                               : c.row[eq + k];
+                               : gv[k];
                 if ((int64_t)qa < a.cap) {
                   oa[qa] = (int32_t)(eq + k);
                   va[qa] = val;

@@ -471,7 +471,8 @@ def test_emulated_more_chunks_than_helpers():
     assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-2000:])
 
 
-@pytest.mark.parametrize("caps, rho", [(220, 0.1), (220, 0.3), (228, 0.1), (228, 0.3), (228, 0.55), (520, 0.12), (520, 0.13)])
+@pytest.mark.parametrize("caps, rho", [(188, 0.1), (188, 0.3), (196, 0.084), (196, 0.088), (196, 0.3), (196, 0.55),
+                                       (520, 0.13)])
 @pytest.mark.parametrize("room", [1.0, 0.6])
 def test_emulated_waves_that_cannot_be_staged(emu_lib, caps, rho, room):
     """Waves some of whose lanes have more capped values than their LDS rows hold, on both sides of the
