@@ -675,15 +675,16 @@ __device__ __forceinline__ uint32_t wave_prefix_bits(uint32_t x, uint32_t& total
 // has done its own, so a chunk is only ever held by a running workgroup and the leader waits only
 // for chunks that were taken: no wait depends on another workgroup being scheduled. Helpers are
 // optional (the leader alone would take every chunk); one that finds no request for long enough
-// leaves. About kSolveHelpers of them are launched at most, as many as are resident at once, each for
-// every few-th chunk of its row: with one for each of the 1,025 chunks of a row of 2^30 coordinates,
-// those that found no place left their chunks to the leader, one after another, and the call took 15.4
-// ms under the variance budget and 99 ms where the greedy solver counts over an unaligned row, against
-// 3.0 and 3.5. Hand-offs use agent-scope atomics for the data itself as well as for the words that
-// announce it, each side waiting for its own accesses to complete (s_waitcnt) before it announces them,
-// so no cache write-back or invalidation is needed. Every word that all chunks would touch is avoided:
-// atomics on one address take 10-30 ns each (counting a 2^28 row's candidates through one counter per
-// wave took 150 us a request).
+// leaves. About kSolveHelpers of them are launched at most, as many as are resident at once, and one
+// that is done with its own chunk takes others: with helpers bound to one chunk each, the 1,025 chunks
+// of a row of 2^30 coordinates were left to the leader where they found no helper resident (15.4 ms a
+// call under the variance budget and 99 ms where the greedy solver counts over an unaligned row, against
+// 3.0 and 3.5), and so were those of calls on several streams, whose helpers held each other off the
+// compute units (one row of 2^24, exact, on four streams: 1,006 us a call against 70). Hand-offs use
+// agent-scope atomics for the data itself as well as for the words that announce it, each side waiting
+// for its own accesses to complete (s_waitcnt) before it announces them, so no cache write-back or
+// invalidation is needed. Every word that all chunks would touch is avoided: atomics on one address take
+// 10-30 ns each (counting a 2^28 row's candidates through one counter per wave took 150 us a request).
 //
 // Exact and variance solver: descend from binades (2^23 keys) to windows of 512 bins, of 2^14, then
 // 2^5, then single keys. At each level the highest bin whose maximum passes the criterion (b1) and
@@ -696,7 +697,9 @@ constexpr uint32_t kReqDone = 255;      // request number: the row is solved
 constexpr int kHelperPolls = 1 << 15;   // some 20 ms without a request
 // Helpers of a call: the solver's workgroups that are resident at once (two on each of 256 compute
 // units). Calls whose chunks are shorter than kMaxChunk have fewer chunks than this, and a helper for
-// each. (A build may lower it to give a helper several chunks on small inputs.)
+// each. With 256 of them calls that list a binade take 5 to 15 per cent longer when alone (16 x 2^20,
+// greedy, rho = 0.1: 80 us against 72) and less when several streams share the chip (on four streams 49
+// against 58). (A build may lower it to give a helper several chunks on small inputs.)
 #ifndef GSPAR_SOLVE_HELPERS
 #define GSPAR_SOLVE_HELPERS 512
 #endif
@@ -800,6 +803,7 @@ struct SolveLds {
   uint64_t word;       // a helper's next request (0: leave)
   uint32_t cmd;        // whether the chunk at hand was taken by this workgroup
   uint32_t err;        // kFlagInternal when a shift of the leader's exact sums lay outside its range
+  uint32_t next;       // a helper's next chunk (0: none)
   uint32_t nbuf, base;  // keys of the chunk at hand that belong in the list, and their place there
   uint32_t keys[kPassBuf];  // the leader's first listed keys
   union {
@@ -882,15 +886,15 @@ GS_DI double exact_sum_sq(S& s, int E, uint64_t ph, uint64_t pl) {
 
 // Works on chunk c of a request and puts the results into the row's scratch, if the chunk is this
 // workgroup's: it is taken (with an atomic whose answer is needed only at the end) unless `own`
-// says that it is already. Every thread of the workgroup calls it.
+// says that it is already. Returns the request's chunks. Every thread of the workgroup calls it.
 template <bool VAR>
-GS_DI void pass_chunk(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc, int64_t row, int64_t base,
+GS_DI uint32_t pass_chunk(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc, int64_t row, int64_t base,
                       int64_t len, uint32_t c, const Pass& P, bool own) {
   const int64_t n = P.from ? (int64_t)ccnt_of(a, row)->v : len;
   int64_t share;
   uint32_t chunks;
   pass_chunks(a, P.from, n, share, chunks);
-  if (c >= chunks) return;
+  if (c >= chunks) return chunks;
   uint32_t taken = 0;
   if (threadIdx.x == 0 && !own) taken = atomicMax(&sc->chunk[c].taken, P.num);
   const uint32_t lc = threadIdx.x & (kWC - 1);
@@ -924,7 +928,7 @@ GS_DI void pass_chunk(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* 
         }
       }
     });
-    if (!claim()) return;
+    if (!claim()) return chunks;
     const int b = threadIdx.x;
     uint64_t cnt = 0, sr = 0, s2 = 0;
     uint32_t mx = 0;
@@ -977,7 +981,7 @@ GS_DI void pass_chunk(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* 
       }
     };
     stream_blocks<4, kNT>(src, beg, end, gather);
-    if (!claim()) return;
+    if (!claim()) return chunks;
     const uint32_t m = s.nbuf;
     if (threadIdx.x == 0 && m) s.base = atomicAdd(&ctl->lcount, m);
     __syncthreads();
@@ -1021,7 +1025,7 @@ GS_DI void pass_chunk(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* 
       s.rc[threadIdx.x >> 6] = qc;
       s.rs[threadIdx.x >> 6] = qs;
     }
-    if (!claim()) return;
+    if (!claim()) return chunks;
     if (threadIdx.x == 0) {
       for (int i = 1; i < kNT / 64; ++i) {
         qc += s.rc[i];
@@ -1034,14 +1038,20 @@ GS_DI void pass_chunk(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* 
   wait_own();
   __syncthreads();  // every wave's results have landed, and the LDS may be reused
   if (threadIdx.x == 0) st_agent(&sc->chunk[c].done, P.num);
+  return chunks;
 }
 
-// Helper h (from 1) of a row of n chunks and `step` - 1 helpers: works on chunks h, h + step, ... of
-// each of the row's requests until the row is solved.
+// Helper h (from 1) of `helpers`: works on chunk h of each of the row's requests, then on chunks that
+// nobody has taken by then, until the row is solved. It looks among those that differ from h by a
+// multiple of `mod`, the helpers' number over 8 to 16 (a power of two, at most 64), with one load per
+// lane, and takes the one at its own place among the helpers that share them; so the first eighth of
+// the helpers covers every chunk where the others found no place, be it that the row has more chunks
+// than helpers fit or that other streams' kernels hold the compute units.
 template <bool VAR>
 GS_DI void help_row(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc, int64_t row, int64_t base,
-                    int64_t len, uint32_t h, uint32_t step, uint32_t n) {
+                    int64_t len, uint32_t h, uint32_t helpers) {
   uint32_t seen = 0;  // thread 0: the last request looked at
+  const uint32_t lg = 31u - (uint32_t)__builtin_clz(helpers), mod = 1u << (lg < 3 ? 0u : min(lg - 3u, 6u));
   while (true) {
     if (threadIdx.x == 0) {
       uint64_t word = 0;
@@ -1060,17 +1070,32 @@ GS_DI void help_row(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc
     __syncthreads();
     const Pass P = pass_of(uni(s.word));
     if (P.num == 0 || P.num == kReqDone) return;
-    for (uint32_t c = h; c < n; c += step) {
-      if (c != h) {
-        // (a chunk after the first may be the leader's by now: not worth reading then)
-        if (threadIdx.x == 0) s.cmd = ld_agent(&sc->chunk[c].taken) < P.num ? 1u : 0u;
-        __syncthreads();
-        const bool open = uni(s.cmd) != 0;
-        __syncthreads();
-        if (!open) continue;
-      }
-      pass_chunk<VAR>(a, s, ctl, sc, row, base, len, c, P, false);
+    uint32_t c = h;
+    while (true) {
+      const uint32_t chunks = pass_chunk<VAR>(a, s, ctl, sc, row, base, len, c, P, c != h);
       __syncthreads();
+      if (threadIdx.x < 64) {
+        uint32_t next = 0;  // 0: nothing left (chunk 0 is the leader's)
+        uint32_t b = h & (mod - 1u);
+        while (b < chunks) {
+          const uint32_t at = b + mod * threadIdx.x;
+          unsigned long long m = __ballot(at != 0 && at < chunks && ld_agent(&sc->chunk[at].taken) < P.num);
+          if (!m) {
+            b += 64u * mod;
+            continue;
+          }
+          for (uint32_t skip = (h / mod) % (uint32_t)__popcll(m); skip; --skip) m &= m - 1ull;
+          next = b + mod * (uint32_t)__builtin_ctzll(m);
+          uint32_t was = 0;
+          if (threadIdx.x == 0) was = atomicMax(&sc->chunk[next].taken, P.num);
+          if ((uint32_t)__shfl((int)was, 0) < P.num) break;  // else somebody took it in between: look again
+          next = 0;
+        }
+        if (threadIdx.x == 0) s.next = next;
+      }
+      __syncthreads();
+      c = uni(s.next);
+      if (c == 0) break;
     }
   }
 }
@@ -2129,12 +2154,12 @@ __global__ void __launch_bounds__(kNT, 4) k_solve(Args a) {
   if (lead) {
     lead_row<SOLVER>(a, sm, ctl_of(a, row), scratch_of(a, row), row, base, len);
   } else {
-    uint32_t n = (uint32_t)a.nb, helpers = (uint32_t)a.helpers;
+    uint32_t helpers = (uint32_t)a.helpers;
     if (a.seg) {  // (32-bit divisions: a row is shorter than 2^31, a chunk than 2^20)
-      n = ((uint32_t)len + (uint32_t)a.chunk - 1u) / (uint32_t)a.chunk;
+      const uint32_t n = ((uint32_t)len + (uint32_t)a.chunk - 1u) / (uint32_t)a.chunk;
       helpers = (n - 1u) / (uint32_t)a.help_step;
     }
-    help_row<VAR>(a, sm, ctl_of(a, row), scratch_of(a, row), row, base, len, help, helpers + 1u, n);
+    help_row<VAR>(a, sm, ctl_of(a, row), scratch_of(a, row), row, base, len, help, helpers);
   }
 }
 

@@ -461,11 +461,12 @@ assert helped >= 0.4 * (lead + helped)
 """
 
 
-def test_emulated_more_chunks_than_helpers():
-    """A row of 25 chunks with a leader and two helpers resident at even speeds: the helpers, which are
-    as many as fit, take about two thirds of every request's chunks, where helpers bound to one chunk
-    each left all but two of them to the leader."""
-    lib = _build_emu(concurrent=True, GSPAR_EMU_HELPERS="2")
+@pytest.mark.parametrize("helpers", [2, None])
+def test_emulated_more_chunks_than_helpers(helpers):
+    """A row of 25 chunks with a leader and two helpers resident at even speeds, because no more are
+    launched or because the others find no place: the two take most of what is not the leader's, where
+    helpers bound to one chunk each left all but two of a request's chunks to the leader."""
+    lib = _build_emu(concurrent=True, **({} if helpers is None else {"GSPAR_EMU_HELPERS": str(helpers)}))
     r = subprocess.run([sys.executable, "-c", _SHARE, lib, os.path.join(HERE, "emu")],
                        env=dict(os.environ, EMU_RESIDENT="3", EMU_EVEN="1"), capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-2000:])

@@ -438,6 +438,38 @@ def test_more_chunks_than_helpers(gs, solver):
     assert a[:3] == b[:3] and torch.equal(a[3], b[3]) and torch.equal(a[4], b[4])
 
 
+@pytest.mark.parametrize("d", [1 << 20, (1 << 24) + 3])
+def test_calls_on_several_streams(gs, d):
+    """Calls whose solver lists or bins a binade, on four streams at once, so that each finds only some of
+    its helpers resident: every result is that of the call alone."""
+    plans, alone, streams = [], [], [torch.cuda.Stream() for _ in range(4)]
+    rho = torch.tensor([0.05], dtype=torch.float64, device="cuda")
+    seeds = torch.tensor([9], dtype=torch.int64, device="cuda")
+    for i, solver in enumerate(("exact", "greedy", "variance", "exact")):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(20 + i)
+        g = torch.randn(1, d, generator=gen, device="cuda")
+        g /= torch.empty(1, d, device="cuda").exponential_(generator=gen).sqrt_().clamp_(min=1e-4)
+        p = gs.Plan(1, d, solver=solver, cap_per_row=d)
+        p.run(g, rho, seeds)
+        torch.cuda.synchronize()
+        n = int(p.nnz[0].item())
+        assert int(p.flags[0].item()) == 0 and int(p.k[0].item()) > 0
+        plans.append((p, g))
+        alone.append((n, float(p.lam[0].item()), int(p.k[0].item()), p.idx[0, :n].clone(), p.val[0, :n].clone()))
+        p.idx.zero_()
+    torch.cuda.synchronize()
+    _say(f"[streams] d={d}")
+    for _ in range(10):
+        for s, (p, g) in zip(streams, plans):
+            with torch.cuda.stream(s):
+                p.run(g, rho, seeds)
+    torch.cuda.synchronize()
+    for (p, _), (n, lam, k, idx, val) in zip(plans, alone):
+        assert int(p.nnz[0].item()) == n and float(p.lam[0].item()) == lam and int(p.k[0].item()) == k
+        assert torch.equal(p.idx[0, :n], idx) and torch.equal(p.val[0, :n], val)
+
+
 def test_candidate_band_with_smaller_workspaces(gs):
     """The same long row with the full workspace (band used), a workspace with room for 2^16
     candidates only (the band overflows and is dropped) and the fixed part alone (no band): the
