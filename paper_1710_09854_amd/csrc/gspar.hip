@@ -600,7 +600,7 @@ __device__ __forceinline__ void stream_blocks(const float* __restrict__ row, int
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t q = qb + threadIdx.x + u * NT;
-      x[u] = load_stream(row + 4 * (q < qfull ? q : qfull - 1));
+      x[u] = load_vec(row + 4 * (q < qfull ? q : qfull - 1));
     }
     __builtin_amdgcn_sched_barrier(0);
     if (!whole) {
