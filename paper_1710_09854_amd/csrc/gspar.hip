@@ -479,7 +479,10 @@ __device__ __forceinline__ void wave_sync() {
 // LDS bytes reused as 16-bit words.
 typedef uint16_t __attribute__((may_alias)) gs_u16;
 
-// Streaming accesses: g is read once per pass and the outputs are written once, so those loads,
+// Streaming accesses: g is read once per pass and the outputs are written once, so those loads (the
+// solver's list requests apart, where the hint makes 16 rows of 2^20 under the variance budget faster,
+// 130 us a call against 135, and 300 rows of 200,001 and the probabilities of 2^26 coordinates slower,
+// 209 against 203 and 339 against 328),
 // the probabilities' stores and the sampling pass's staged stores (whole runs of consecutive words)
 // carry the non-temporal hint and do not displace what the caches keep (the level-1 copies,
 // windows and status words). Stores that lanes make one word at a time to scattered places (the
@@ -680,7 +683,7 @@ __device__ __forceinline__ uint32_t wave_prefix_bits(uint32_t x, uint32_t& total
 // of a row of 2^30 coordinates were left to the leader where they found no helper resident (15.4 ms a
 // call under the variance budget and 99 ms where the greedy solver counts over an unaligned row, against
 // 3.0 and 3.5), and so were those of calls on several streams, whose helpers held each other off the
-// compute units (one row of 2^24, exact, on four streams: 1,006 us a call against 70). Hand-offs use
+// compute units (one row of 2^24, exact, on four streams: 1,033 us a call against 74). Hand-offs use
 // agent-scope atomics for the data itself as well as for the words that announce it, each side waiting
 // for its own accesses to complete (s_waitcnt) before it announces them, so no cache write-back or
 // invalidation is needed. Every word that all chunks would touch is avoided: atomics on one address take
@@ -1041,21 +1044,27 @@ GS_DI uint32_t pass_chunk(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScrat
   return chunks;
 }
 
-// Helper h (from 1) of `helpers`: works on chunk h of each of the row's requests, then on chunks that
-// nobody has taken by then, until the row is solved. It looks among those that differ from h by a
-// multiple of `mod`, the helpers' number over 8 to 16 (a power of two, at most 64), with one load per
-// lane, and takes the one at its own place among the helpers that share them; so the first eighth of
-// the helpers covers every chunk where the others found no place, be it that the row has more chunks
-// than helpers fit or that other streams' kernels hold the compute units.
+// Helper h (from 1) of `helpers`: works on chunk h of each of the row's requests and, where no new
+// request follows within kLookPolls, on chunks that nobody has taken by then, until the row is solved. It
+// looks among those that differ from h by a multiple of `mod`, the helpers' number over 8 to 16 (a
+// power of two, at most 64), with one load per lane, and takes the one at its own place among the
+// helpers that share them; so the first eighth of the helpers covers every chunk where the others found
+// no place, be it that the row has more chunks than helpers fit or that other streams' kernels hold the
+// compute units. (Looking at once took chunks from helpers that were about to begin: a call whose solver
+// counts twice over 2^22 coordinates took 46 us against 43.)
+constexpr int kLookPolls = 2;  // some 1.2 us
 template <bool VAR>
 GS_DI void help_row(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc, int64_t row, int64_t base,
                     int64_t len, uint32_t h, uint32_t helpers) {
   uint32_t seen = 0;  // thread 0: the last request looked at
   const uint32_t lg = 31u - (uint32_t)__builtin_clz(helpers), mod = 1u << (lg < 3 ? 0u : min(lg - 3u, 6u));
+  Pass P{0, 0, 0, 0, 0};
+  uint32_t chunks = 0;       // of the request P
+  int polls = kHelperPolls;  // before it looks for a chunk (fewer than kHelperPolls) or leaves
   while (true) {
     if (threadIdx.x == 0) {
       uint64_t word = 0;
-      for (int polls = 0; polls < kHelperPolls; ++polls) {
+      for (int i = 0; i < polls; ++i) {
         word = ld_agent(&ctl->req);
         const uint32_t num = (uint32_t)(word >> 32) & 0xFFu;
         if (num != seen) {
@@ -1068,12 +1077,14 @@ GS_DI void help_row(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc
       s.word = word;
     }
     __syncthreads();
-    const Pass P = pass_of(uni(s.word));
-    if (P.num == 0 || P.num == kReqDone) return;
+    const uint64_t word = uni(s.word);
     uint32_t c = h;
-    while (true) {
-      const uint32_t chunks = pass_chunk<VAR>(a, s, ctl, sc, row, base, len, c, P, c != h);
-      __syncthreads();
+    if (word) {
+      P = pass_of(word);
+      if (P.num == kReqDone) return;
+    } else if (polls == kHelperPolls) {
+      return;
+    } else {
       if (threadIdx.x < 64) {
         uint32_t next = 0;  // 0: nothing left (chunk 0 is the leader's)
         uint32_t b = h & (mod - 1u);
@@ -1095,8 +1106,14 @@ GS_DI void help_row(const Args& a, SolveLds<VAR>& s, RowCtl* ctl, RowScratch* sc
       }
       __syncthreads();
       c = uni(s.next);
-      if (c == 0) break;
+      if (c == 0) {
+        polls = kHelperPolls;
+        continue;
+      }
     }
+    chunks = pass_chunk<VAR>(a, s, ctl, sc, row, base, len, c, P, word == 0);
+    polls = word ? kLookPolls : 0;
+    __syncthreads();
   }
 }
 
