@@ -2126,7 +2126,7 @@ __global__ void __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4))) k
 // batch; for a segmented call a workgroup per map entry, of which those of every help_step-th block help.
 // Two workgroups of it fit a compute unit (128 registers), so that all 512 of 16 rows' are resident:
 // with one, under the variance budget, half of the rows had no helpers until the others were solved
-// (the kernel took 140 us on 16 rows of 2^20, and takes 63).
+// (the kernel took 140 us on 16 rows of 2^20, and takes 65).
 template <int SOLVER>
 __global__ void __launch_bounds__(kNT, 4) k_solve(Args a) {
   constexpr bool VAR = SOLVER == GSPAR_VARIANCE;
